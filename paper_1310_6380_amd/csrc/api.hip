@@ -179,7 +179,7 @@ struct mvpb_ctx_s {
   };
   std::map<std::string, GraphEntry> graphs;
   unsigned long long graph_clock = 0;
-  std::vector<EigItem> host_items;                // staging of the item table (kept alive for async copies)
+  std::vector<char> host_items;                   // staging of the item table (kept alive for async copies)
   // mvpb_solve_cells: workspace (plain device allocation, grow-only), its
   // captured graphs (keyed by the call's shape, at most MAX_CELL_GRAPHS) and
   // the staging of the per-call tables
@@ -1377,6 +1377,78 @@ static size_t item_bytes(int n, int nb, bool fp32) {
   return s;
 }
 
+// Route of an eigensolve launch sequence: shift-invert block Krylov with
+// `steps` block steps, or (0) the reduction of the whole matrix.
+struct Route {
+  int steps = 0;
+  double tol = 0.0;   // residual bar of the Krylov pairs, relative to their value
+};
+
+// Attempts at a set of points: the Krylov route, the points whose pairs miss its
+// bar (about one cell in sixty of the inclusion study, those with stiffness
+// ratios near 100) with RETRY_STEPS more, and what is left by the reduction.
+// Without a caller that waits for the results only the last.
+enum Attempt { TRY_KRYLOV = 0, TRY_LONGER, TRY_REDUCTION };
+constexpr int RETRY_STEPS = 4;
+
+// The Krylov route pays while its projection, of order m = HB steps, is small
+// against the operator: its chain of m sweeps and 4 steps launches against n
+// sweeps and n / 4 launches.  It is for FP64 solves that end with the
+// Rayleigh-Ritz step.  The bars: a frequency's error is about ten times the
+// residual's square (1e-13 at 1e-7, the rounding level of the solve), a mode's
+// is the residual over the relative gap.
+static Route krylov_route(int n_min, int nb, int dim, bool fp32, bool modes, Attempt at) {
+  Route rt;
+  if (fp32 || nb > RR_MAX_BANDS || at == TRY_REDUCTION) return rt;
+  const int s = krylov_steps(nb, dim, modes);
+  if (s + RETRY_STEPS > KRY_MAX_STEPS || 10 * HB * s > 7 * n_min) return rt;
+  rt.steps = at == TRY_LONGER ? s + RETRY_STEPS : s;
+  rt.tol = modes ? 1e-11 : 1e-7;
+  return rt;
+}
+
+// Sizes of the per-item buffers of the Krylov route (the projection's own item
+// follows them, see krylov_item_bytes).
+static void krylov_layout(int n, int nb, int steps, size_t *sz, int *count) {
+  const size_t npad = ((size_t)n + KRY_ROWS - 1) / KRY_ROWS * KRY_ROWS, nch = npad / KRY_ROWS;
+  int k = 0;
+  sz[k++] = sizeof(cd) * (size_t)n * n;              // A
+  sz[k++] = sizeof(cd) * (size_t)n * n;              // Ak
+  sz[k++] = sizeof(cd) * (size_t)n * n;              // Xi
+  sz[k++] = sizeof(cd) * (size_t)steps * npad * HB;  // Q
+  sz[k++] = sizeof(cd) * npad * HB;                  // W
+  sz[k++] = sizeof(cd) * npad * HB;                  // Z
+  sz[k++] = sizeof(cd) * (size_t)steps * HB * HB;    // P
+  sz[k++] = sizeof(cd) * nch * HB * HB;              // G
+  sz[k++] = 2 * sizeof(double);                      // shift, status
+  sz[k++] = sizeof(int) * 2;                         // flag
+  sz[k++] = sizeof(double) * nb;                     // lam
+  sz[k++] = sizeof(double) * nb;                     // omega
+  sz[k++] = sizeof(cd) * (size_t)n * nb;             // Y
+  sz[k++] = sizeof(cd) * (size_t)n * nb;             // refined vectors
+  sz[k++] = sizeof(cd) * (size_t)((n + 63) / 64) * 2 * nb * nb;  // Rayleigh-Ritz partials
+  sz[k++] = sizeof(cd) * (size_t)nb * nb;            // their Cholesky factor
+  sz[k++] = sizeof(double);                          // acc
+  *count = k;
+}
+
+// Workspace of one item on either route.
+static size_t route_item_bytes(int n, int nb, bool fp32, const Route &rt) {
+  if (!rt.steps) return item_bytes(n, nb, fp32);
+  size_t sz[32];
+  int cnt = 0;
+  krylov_layout(n, nb, rt.steps, sz, &cnt);
+  size_t s = item_bytes(HB * rt.steps, nb, false);
+  for (int i = 0; i < cnt; ++i) s += align256(sz[i]);
+  return s;
+}
+
+// Item table of a launch sequence: one EigItem per item; on the Krylov route
+// also the projections' EigItems and the KryItems.
+static size_t table_bytes(size_t n_items, const Route &rt) {
+  return n_items * (rt.steps ? 2 * sizeof(EigItem) + sizeof(KryItem) : sizeof(EigItem));
+}
+
 // Bulge-chasing control words of a launch sequence over n items (placed
 // after the items in the workspace).
 static size_t ctl_bytes(size_t n_items) { return align256(sizeof(int) * hb2st_ctl_ints((int)n_items)); }
@@ -1422,14 +1494,72 @@ static EigItem carve_item(char *base, int n, int nb, bool fp32) {
   return it;
 }
 
-// Normalise each eigenvector (length len, complex) so that its
-// largest-modulus entry (lowest index on ties) is real and positive.
-__global__ void normalize_phase(cd *U, int len, int count) {
+// Carve item i of a table of n_items (host image `table`, bytes as
+// table_bytes) from `base`; returns the item for the caller to fill in the
+// operator's fields (put_item).
+static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Route &rt, size_t n_items, size_t i,
+                                char *table) {
+  if (!rt.steps) return carve_item(base, n, nb, fp32);
+  size_t sz[32];
+  int cnt = 0;
+  krylov_layout(n, nb, rt.steps, sz, &cnt);
+  size_t o = 0;
+  int k = 0;
+  auto take = [&]() {
+    char *p = base + o;
+    o += align256(sz[k++]);
+    return p;
+  };
+  EigItem it{};
+  KryItem ky{};
+  it.A = take();
+  it.Ak = (cd *)take();
+  ky.A = (cd *)it.A;
+  ky.Ak = it.Ak;
+  ky.Xi = (cd *)take();
+  ky.Q = (cd *)take();
+  ky.W = (cd *)take();
+  ky.Z = (cd *)take();
+  ky.P = (cd *)take();
+  ky.G = (cd *)take();
+  ky.sigma = (double *)take();
+  ky.status = (int *)(ky.sigma + 1);
+  it.flag = (int *)take();
+  it.lam = (double *)take();
+  it.omega = (double *)take();
+  it.Y = (cd *)take();
+  it.Z = (cd *)take();
+  it.Gp = (cd *)take();
+  it.Lr = (cd *)take();
+  it.acc = (double *)take();
+  it.Yb = it.Y;
+  const int m = HB * rt.steps;
+  EigItem sm = carve_item(base + o, m, nb, false);
+  sm.n = m;
+  sm.N = m;
+  sm.nb = nb;
+  ky.T = (cd *)sm.A;
+  ky.Ys = sm.Y;
+  ky.lam_s = sm.lam_t;
+  ky.flag_s = sm.flag;
+  ky.Y = it.Y;
+  ky.flag = it.flag;
+  ky.n = n;
+  ky.npad = (n + KRY_ROWS - 1) / KRY_ROWS * KRY_ROWS;
+  ky.nb = nb;
+  ky.m = m;
+  memcpy(table + (n_items + i) * sizeof(EigItem), &sm, sizeof sm);
+  memcpy(table + 2 * n_items * sizeof(EigItem) + i * sizeof(KryItem), &ky, sizeof ky);
+  return it;
+}
+static void put_item(char *table, size_t i, const EigItem &it) { memcpy(table + i * sizeof(EigItem), &it, sizeof it); }
+
+// Normalise each eigenvector (length len, complex; nb per item from U[item])
+// so that its largest-modulus entry (lowest index on ties) is real and positive.
+__global__ void normalize_phase(cd *const *U, int len, int nb) {
   __shared__ double bv[256];
   __shared__ int bi[256];
-  const int v = blockIdx.x;
-  if (v >= count) return;
-  cd *u = U + (size_t)v * len;
+  cd *u = U[blockIdx.x / nb] + (size_t)(blockIdx.x % nb) * len;
   double best = -1.0;
   int idx = 0;
   for (int r = threadIdx.x; r < len; r += blockDim.x) {
@@ -1516,12 +1646,14 @@ constexpr size_t MAX_GRAPHS = 16;
 // the stage-1 parts' size ranges and the grids), the bands, the reduction
 // precision and the number of stage-1 parts.
 static std::string launch_signature(const std::vector<Job> &jobs, int nb, bool fp32, int parts,
-                                    const Stage2Shape &sh) {
+                                    const Stage2Shape &sh, const Route &rt) {
   std::string k;
   k.reserve(32 + 8 * jobs.size());
   auto put = [&](int v) { k.append(reinterpret_cast<const char *>(&v), sizeof v); };
   put(nb);
   put(fp32 ? 1 : 0);
+  put(rt.steps);
+  put(rt.steps && rt.tol < 1e-9 ? 1 : 0);   // modes or frequencies only
   put(parts);
   put(sh.group);
   put(sh.wg_max);
@@ -1553,12 +1685,16 @@ static hipError_t reserve_la_events(mvpb_ctx ctx, size_t count) {
 }
 
 // The eigensolve launch sequence over the items of a device table whose
-// operator orders are `orders` (table order): operator formation, stage 1 in
-// independent parts on the context's streams, bulge chasing, tridiagonal
-// eigenpairs, back-transform, Rayleigh-Ritz (or the tridiagonal results
-// beyond RR_MAX_BANDS).  ctl: the bulge-chasing control words.
+// operator orders are `orders` (table order).  Reduction: operator formation,
+// stage 1 in independent parts on the context's streams, bulge chasing,
+// tridiagonal eigenpairs, back-transform, Rayleigh-Ritz (or the tridiagonal
+// results beyond RR_MAX_BANDS).  Krylov: operator formation, factorisation and
+// block steps, the same bulge chasing, tridiagonal eigenpairs and band
+// back-transform on the projections, Ritz vectors, Rayleigh-Ritz.  ctl: the
+// bulge-chasing control words.
 static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const std::vector<int> &orders,
-                                     bool any_iso, bool any_general, int nb, bool fp32, int parts_wanted,
+                                     bool any_iso, bool any_general, int nb, bool fp32, const Route &rt,
+                                     int parts_wanted,
                                      const Stage2Shape &sh, int *ctl, hipStream_t st, hipEvent_t ev_fork,
                                      const hipEvent_t *ev_join, const hipEvent_t *la_ev) {
   const int n_items = (int)orders.size();
@@ -1570,6 +1706,18 @@ static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const
   hipError_t e = hipSuccess;
   if (any_iso) e = launch_form_operator(d_items, n_items, n_max, fp32, st);
   if (e == hipSuccess && any_general) e = launch_form_operator_general(d_items, n_items, n_max, fp32, st);
+  if (rt.steps) {
+    const EigItem *d_small = d_items + n_items;
+    const KryItem *d_kry = reinterpret_cast<const KryItem *>(d_items + 2 * (size_t)n_items);
+    const int m = HB * rt.steps;
+    if (e == hipSuccess) e = launch_krylov(d_kry, n_items, n_max, rt.steps, st);
+    if (e == hipSuccess) e = launch_stage2(d_small, n_items, m, false, ctl, sh, st);
+    if (e == hipSuccess) e = launch_tridiag_eig(d_small, n_items, m, nb, st, ctx->la[0], la_ev[0], la_ev[1]);
+    if (e == hipSuccess) e = launch_backtransform(d_small, n_items, m, m, nb, false, st, false);
+    if (e == hipSuccess) e = launch_krylov_ritz(d_kry, n_items, n_max, nb, rt.steps, rt.tol, st);
+    if (e == hipSuccess) e = launch_rayleigh_ritz(d_items, n_items, n_max, nb, false, st);
+    return e;
+  }
   // stage 1 in independent parts of the items, one per stream
   ItemPart parts[MAX_SIDE + 1];
   const int n_parts = std::max(1, std::min(parts_wanted, n_items));
@@ -1610,7 +1758,7 @@ static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const
 }
 
 static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double *omega_dev, double *U_dev,
-                     bool use_graph) {
+                     bool use_graph, const Route &rt) {
   // the reduction precision is shared by every item of one launch sequence
   const bool fp32 = jobs.empty() ? false : (jobs[0].plan->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
   hipStream_t st = ctx->stream;
@@ -1626,7 +1774,7 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
     const int n = j.plan->n;
     any_iso = any_iso || j.plan->dim == 0;
     any_general = any_general || j.plan->dim != 0;
-    total += item_bytes(n, nb, fp32);
+    total += route_item_bytes(n, nb, fp32, rt);
     n_max = std::max(n_max, n);
     n_min = std::min(n_min, n);
   }
@@ -1645,7 +1793,8 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
   total += ctl_bytes(n_items);
   if (ctx->cap && total > ctx->cap)
     return set_err(MVPB_E_NOMEM, "workspace %zu bytes exceeds the cap of %zu bytes", total, ctx->cap);
-  const bool realloc = total > ctx->ws.bytes || sizeof(EigItem) * n_items > ctx->items.bytes;
+  const size_t tbytes = table_bytes(n_items, rt);
+  const bool realloc = total > ctx->ws.bytes || tbytes > ctx->items.bytes;
   if (realloc) {
     // captured graphs point into the old buffers
     HIP_TRY(hipStreamSynchronize(st));
@@ -1653,17 +1802,18 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
     ctx->graphs.clear();
   }
   HIP_TRY(ctx->ws.reserve(total));
-  HIP_TRY(ctx->items.reserve(sizeof(EigItem) * n_items));
+  HIP_TRY(ctx->items.reserve(tbytes));
   // the staging vector may still feed an earlier asynchronous copy
   HIP_TRY(hipStreamSynchronize(st));
-  std::vector<EigItem> &items = ctx->host_items;
-  items.assign(n_items, EigItem{});
+  std::vector<char> &table = ctx->host_items;
+  table.assign(tbytes, 0);
+  std::vector<cd *> vecs(n_items);   // refined vectors (Z) or, beyond RR_MAX_BANDS, the back-transformed ones (Y)
   size_t off = 0;
   for (int i = 0; i < n_items; ++i) {
     const Job &j = jobs[i];
     const int n = j.plan->n;
-    EigItem it = carve_item(ctx->ws.as<char>() + off, n, nb, fp32);
-    off += item_bytes(n, nb, fp32);
+    EigItem it = carve_route_item(ctx->ws.as<char>() + off, n, nb, fp32, rt, n_items, i, table.data());
+    off += route_item_bytes(n, nb, fp32, rt);
     it.coef = j.plan->coef.as<cd>();
     it.N = j.plan->N;
     it.n = n;
@@ -1681,9 +1831,10 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
     it.kap1 = kap[0];
     it.kap2 = kap[1];
     it.kap3 = kap[2];
-    items[i] = it;
+    put_item(table.data(), i, it);
+    vecs[i] = nb <= RR_MAX_BANDS ? it.Z : it.Y;
   }
-  HIP_TRY(hipMemcpyAsync(ctx->items.p, items.data(), sizeof(EigItem) * n_items, hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(ctx->items.p, table.data(), tbytes, hipMemcpyHostToDevice, st));
   const EigItem *d_items = ctx->items.as<EigItem>();
 
   std::vector<int> orders(n_items);
@@ -1691,11 +1842,11 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
   int *ctl = reinterpret_cast<int *>(ctx->ws.as<char>() + ctl_off);
   HIP_TRY(reserve_la_events(ctx, la_events_needed(n_max, parts_wanted)));
   auto enqueue = [&]() -> hipError_t {
-    return enqueue_eigensolve(ctx, d_items, orders, any_iso, any_general, nb, fp32, parts_wanted, sh, ctl, st,
+    return enqueue_eigensolve(ctx, d_items, orders, any_iso, any_general, nb, fp32, rt, parts_wanted, sh, ctl, st,
                               ctx->ev_fork, ctx->ev_join, ctx->la_events.data());
   };
   if (use_graph) {
-    const std::string graph_key = launch_signature(jobs, nb, fp32, parts_wanted, sh);
+    const std::string graph_key = launch_signature(jobs, nb, fp32, parts_wanted, sh, rt);
     auto found = ctx->graphs.find(graph_key);
     hipGraphExec_t exec = nullptr;
     if (found == ctx->graphs.end()) {
@@ -1743,9 +1894,8 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
     // table per component c: [A: n_items][B: n_items][C: n_items]
     for (int c = 0; c < dmax; ++c) {
       for (int i = 0; i < n_items; ++i) hp.push_back(jobs[i].plan->linvR.p);
-      for (int i = 0; i < n_items; ++i)   // refined vectors (Z) or, beyond RR_MAX_BANDS, the back-transformed ones (Y)
-        hp.push_back((nb <= RR_MAX_BANDS ? items[i].Z : items[i].Y) +
-                     (size_t)std::min(c, jobs[i].plan->n / jobs[i].plan->N - 1) * jobs[i].plan->N);
+      for (int i = 0; i < n_items; ++i)
+        hp.push_back(vecs[i] + (size_t)std::min(c, jobs[i].plan->n / jobs[i].plan->N - 1) * jobs[i].plan->N);
       for (int i = 0; i < n_items; ++i) {
         const Job &jb = jobs[i];
         const int dd = jb.plan->n / jb.plan->N;
@@ -1771,8 +1921,7 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
                      nullptr, N, n, n};
         HIP_TRY(launch_zgemm(OP_C, OP_N, N, nb, N, mk(1.0, 0.0), bt, mk(0.0, 0.0), cnt, st));
       }
-      cd *u0 = (cd *)(U_dev + (same_n ? 0 : (size_t)jobs[i0].out_index * nb * n * 2));
-      hipLaunchKernelGGL(normalize_phase, dim3(cnt * nb), dim3(256), 0, st, u0, n, cnt * nb);
+      hipLaunchKernelGGL(normalize_phase, dim3(cnt * nb), dim3(256), 0, st, (cd *const *)at(0, 2, i0), n, nb);
       HIP_TRY(hipGetLastError());
     }
     HIP_TRY(hipStreamSynchronize(st));
@@ -1948,6 +2097,61 @@ static bool q_ok(const double *Q, int count) {
   return true;
 }
 
+// Run jobs (largest operators first) in chunks within the workspace budget:
+// items of one chunk stay within a factor ~1.5 in order, so that the launch
+// sequence sized for the largest wastes little on the rest.  *krylov: whether
+// any chunk took the Krylov route.
+static int run_sorted(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double *om, double *U, size_t budget,
+                      bool use_graph, Attempt at, bool *krylov) {
+  *krylov = false;
+  if (jobs.empty()) return MVPB_OK;
+  const bool fp32 = (jobs[0].plan->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
+  for (size_t j0 = 0, j1 = 0; j0 < jobs.size(); j0 = j1) {
+    const int n0 = jobs[j0].plan->n;
+    size_t end = j0;
+    int dim = 0, n_min = n0;
+    while (end < jobs.size() && 3 * jobs[end].plan->n >= 2 * n0) {
+      dim = std::max(dim, jobs[end].plan->dim);
+      n_min = std::min(n_min, jobs[end].plan->n);
+      ++end;
+    }
+    Route rt = krylov_route(n_min, nb, dim, fp32, U != nullptr, at);
+    if (solve_bytes(1, route_item_bytes(n0, nb, fp32, rt)) > budget) rt = Route{};
+    *krylov = *krylov || rt.steps > 0;
+    size_t bytes = 0;
+    for (j1 = j0; j1 < end; ++j1) {
+      const size_t b = route_item_bytes(jobs[j1].plan->n, nb, fp32, rt);
+      if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > budget) break;
+      bytes += b;
+    }
+    if (bytes + ctl_bytes(j1 - j0) > budget)
+      return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, cap is %zu", bytes + ctl_bytes(j1 - j0), budget);
+    const std::vector<Job> part(jobs.begin() + j0, jobs.begin() + j1);
+    const int rc = run_items(ctx, part, nb, om, U, use_graph, rt);
+    if (rc) return rc;
+  }
+  return MVPB_OK;
+}
+
+// Every attempt from `first` on at those of the jobs whose frequencies are NaN
+// (om: device, n_om doubles, rows by out_index).  Waits for the stream.
+static int run_attempts(mvpb_ctx ctx, std::vector<Job> jobs, int nb, double *om, size_t n_om, double *U, size_t budget,
+                        bool use_graph, int first) {
+  std::vector<double> seen;
+  for (int at = first; !jobs.empty(); ++at) {
+    bool krylov = false;
+    const int rc = run_sorted(ctx, jobs, nb, om, U, budget, use_graph, (Attempt)at, &krylov);
+    if (rc || !krylov) return rc;
+    seen.resize(n_om);
+    HIP_TRY(hipMemcpyAsync(seen.data(), om, sizeof(double) * n_om, hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    jobs.erase(std::remove_if(jobs.begin(), jobs.end(),
+                              [&](const Job &j) { return !isnan(seen[(size_t)j.out_index * nb]); }),
+               jobs.end());
+  }
+  return MVPB_OK;
+}
+
 extern "C" int mvpb_solve(mvpb_plan p, int n_k, const double *Q, int n_bands, double *omega, double *U,
                           unsigned flags) {
   if (!p || !Q || !omega) return set_err(MVPB_E_INVALID, "NULL argument");
@@ -1970,8 +2174,6 @@ extern "C" int mvpb_solve(mvpb_plan p, int n_k, const double *Q, int n_bands, do
   const size_t budget = ctx->cap ? ctx->cap : (size_t)32 << 30;
   if (solve_bytes(1, per) > budget)
     return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, cap is %zu", solve_bytes(1, per), budget);
-  int chunk = (int)std::min<size_t>((size_t)n_k, budget / per);
-  while (chunk > 1 && solve_bytes(chunk, per) > budget) --chunk;
   const bool graph = !(ctx->prof.on);
   const bool fp32 = (p->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
   int rc = acc_begin(ctx);
@@ -1987,17 +2189,15 @@ extern "C" int mvpb_solve(mvpb_plan p, int n_k, const double *Q, int n_bands, do
       u_out = u_dev.as<double>();
     }
   }
-  for (int k0 = 0; k0 < n_k; k0 += chunk) {
-    const int kc = std::min(chunk, n_k - k0);
-    std::vector<Job> jobs(kc);
-    for (int t = 0; t < kc; ++t) {
-      const double *q = Q + (size_t)qd * (k0 + t);
-      jobs[t] = Job{p, q[0], q[1], qd == 3 ? q[2] : 0.0, t};
-    }
-    rc = run_items(ctx, jobs, n_bands, om_out + (size_t)k0 * n_bands,
-                   u_out ? u_out + 2 * (size_t)k0 * n_bands * n : nullptr, graph);
-    if (rc) return rc;
+  std::vector<Job> jobs(n_k);
+  for (int t = 0; t < n_k; ++t) {
+    const double *q = Q + (size_t)qd * t;
+    jobs[t] = Job{p, q[0], q[1], qd == 3 ? q[2] : 0.0, t};
   }
+  const bool waits = !dev || !(flags & MVPB_F_ASYNC);
+  rc = run_attempts(ctx, std::move(jobs), n_bands, om_out, (size_t)n_k * n_bands, u_out, budget, graph,
+                    waits && !fp32 ? TRY_KRYLOV : TRY_REDUCTION);
+  if (rc) return rc;
   if (!dev) {
     HIP_TRY(hipMemcpyAsync(omega, om_out, sizeof(double) * (size_t)n_k * n_bands, hipMemcpyDeviceToHost, st));
     if (U)
@@ -2049,26 +2249,11 @@ extern "C" int mvpb_solve_batch(mvpb_ctx ctx, int n_plans, const mvpb_plan *plan
   if (rc) return rc;
   DevBuf om(&ctx->pool);
   HIP_TRY(om.alloc(sizeof(double) * base[n_plans] * n_bands));
-  size_t j0 = 0;
-  while (j0 < jobs.size()) {
-    size_t j1 = j0, bytes = 0;
-    const int n0 = jobs[j0].plan->n;
-    while (j1 < jobs.size()) {
-      const size_t b = item_bytes(jobs[j1].plan->n, n_bands, fp32);
-      // keep items of one chunk within a factor ~1.5 in order so that the
-      // launch sequence sized for the largest wastes little on the rest
-      if (j1 > j0 && (bytes + b + ctl_bytes(j1 - j0 + 1) > budget || 3 * jobs[j1].plan->n < 2 * n0)) break;
-      bytes += b;
-      ++j1;
-    }
-    if (bytes + ctl_bytes(j1 - j0) > budget)
-      return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, cap is %zu", bytes + ctl_bytes(j1 - j0), budget);
-    std::vector<Job> part(jobs.begin() + j0, jobs.begin() + j1);
-    rc = run_items(ctx, part, n_bands, om.as<double>(), nullptr, true);
-    if (rc) return rc;
-    j0 = j1;
-  }
   const bool dev = flags & MVPB_F_DEVICE_PTRS;
+  const bool waits = !dev || !(flags & MVPB_F_ASYNC);
+  rc = run_attempts(ctx, std::move(jobs), n_bands, om.as<double>(), base[n_plans] * n_bands, nullptr, budget, true,
+                    waits && !fp32 ? TRY_KRYLOV : TRY_REDUCTION);
+  if (rc) return rc;
   for (int i = 0; i < n_plans; ++i) {
     if (n_k[i] == 0) continue;
     HIP_TRY(hipMemcpyAsync(omega[i], om.as<double>() + base[i] * n_bands, sizeof(double) * n_k[i] * n_bands,
@@ -2108,6 +2293,7 @@ struct CellChunk {                    // eigensolve launch sequence over sorted 
   size_t j0, j1;
   size_t t_items;                     // item table
   TuneParams tp;
+  Route rt;
 };
 }  // namespace
 
@@ -2220,17 +2406,20 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   std::vector<CellChunk> chunks;
   size_t item_region = 0;
   for (size_t j0 = 0; j0 < jobs.size();) {
-    size_t j1 = j0, bytes = 0;
     const int n0 = order_of(jobs[j0]);
-    while (j1 < jobs.size()) {
-      const size_t b = item_bytes(order_of(jobs[j1]), n_bands, fp32);
-      if (j1 > j0 && (bytes + b + ctl_bytes(j1 - j0 + 1) > budget || 3 * order_of(jobs[j1]) < 2 * n0)) break;
+    size_t j1 = j0, bytes = 0;
+    while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0) ++j1;
+    Route rt = krylov_route(order_of(jobs[j1 - 1]), n_bands, 0, fp32, false, TRY_KRYLOV);
+    if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > budget) rt = Route{};
+    const size_t end = j1;
+    for (j1 = j0; j1 < end; ++j1) {
+      const size_t b = route_item_bytes(order_of(jobs[j1]), n_bands, fp32, rt);
+      if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > budget) break;
       bytes += b;
-      ++j1;
     }
     bytes += ctl_bytes(j1 - j0);
     if (bytes > budget) return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, the budget is %zu", bytes, budget);
-    CellChunk ch{j0, j1, take_tab(sizeof(EigItem) * (j1 - j0)), TuneParams{}};
+    CellChunk ch{j0, j1, take_tab(table_bytes(j1 - j0, rt)), TuneParams{}, rt};
     auto f = ctx->tune.find(size_class(n0));
     if (f != ctx->tune.end()) ch.tp = f->second;
     chunks.push_back(ch);
@@ -2350,8 +2539,9 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       const int ci = ord[jb.s];
       const CellGroup &g = groups[grp_of[jb.s]];
       const int n = 2 * g.N;
-      EigItem it = carve_item(W + o_items + off, n, n_bands, fp32);
-      off += item_bytes(n, n_bands, fp32);
+      char *table = stage.data() + ch.t_items;
+      EigItem it = carve_route_item(W + o_items + off, n, n_bands, fp32, ch.rt, ch.j1 - ch.j0, j - ch.j0, table);
+      off += route_item_bytes(n, n_bands, fp32, ch.rt);
       it.coef = reinterpret_cast<cd *>(W + o_coef + g.o_coef) + (size_t)(jb.s - g.c0) * 15 * g.N * g.N;
       it.N = g.N;
       it.n = n;
@@ -2364,7 +2554,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       it.kap1 = 2.0 * M_PI * (T[0] * q[0] + T[1] * q[1]);
       it.kap2 = 2.0 * M_PI * (T[2] * q[0] + T[3] * q[1]);
       it.kap3 = 0.0;
-      memcpy(stage.data() + ch.t_items + (j - ch.j0) * sizeof(EigItem), &it, sizeof it);
+      put_item(table, j - ch.j0, it);
     }
   }
   // fork/join events of every chunk's stage 1 (one set per chunk, so that the
@@ -2438,7 +2628,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       std::vector<int> orders(cnt);
       for (int i = 0; i < cnt; ++i) orders[i] = order_of(jobs[ch.j0 + i]);
       size_t item_sum = 0;
-      for (int n : orders) item_sum += item_bytes(n, n_bands, fp32);
+      for (int n : orders) item_sum += route_item_bytes(n, n_bands, fp32, ch.rt);
       ctl = reinterpret_cast<int *>(W + o_items + item_sum);
       const EigItem *d_items = reinterpret_cast<const EigItem *>(W + ch.t_items);
       Stage2Shape sh;
@@ -2448,7 +2638,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       const int parts = std::max(1, std::min(ch.tp.parts, MAX_SIDE + 1));
       const hipEvent_t *ev = ctx->cell_events.data() + (size_t)(&ch - chunks.data()) * (MAX_SIDE + 1);
       if (e == hipSuccess)
-        e = enqueue_eigensolve(ctx, d_items, orders, true, false, n_bands, fp32, parts, sh, ctl, st, ev[0], ev + 1,
+        e = enqueue_eigensolve(ctx, d_items, orders, true, false, n_bands, fp32, ch.rt, parts, sh, ctl, st, ev[0], ev + 1,
                                ctx->la_events.data() + la_base[&ch - chunks.data()]);
       if (e == hipSuccess) {
         hipLaunchKernelGGL(gather_omega, dim3((cnt * n_bands + 255) / 256), dim3(256), 0, st, d_items, cnt, n_bands, om);
@@ -2479,6 +2669,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       put(ch.tp.parts);
       put(ch.tp.group);
       put(ch.tp.wg_max);
+      put(ch.rt.steps);
     }
   }
   hipGraphExec_t exec = nullptr;
@@ -2526,6 +2717,32 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       if (hstat[3 * (size_t)pos[i] + m])
         return set_err(MVPB_E_NOT_PD, "cell %d: %s is not positive definite (pivot %d)", i, names[m],
                        hstat[3 * (size_t)pos[i] + m] - 1);
+  if (std::any_of(chunks.begin(), chunks.end(), [](const CellChunk &c) { return c.rt.steps > 0; })) {
+    // points whose Krylov pairs do not stand (NaN): again from a plan of their cell
+    std::vector<double> seen(base[n_cells] * n_bands);
+    HIP_TRY(hipMemcpyAsync(seen.data(), om, sizeof(double) * seen.size(), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    for (int i = 0; i < n_cells; ++i) {
+      std::vector<int> bad;
+      for (int t = 0; t < n_k[i]; ++t)
+        if (isnan(seen[(base[i] + t) * n_bands])) bad.push_back(t);
+      if (bad.empty()) continue;
+      mvpb_plan p = nullptr;
+      rc = mvpb_plan_create(cells[i], M1[i], M2[i], precision, &p);
+      if (rc) return rc;
+      std::vector<Job> part;
+      for (int t : bad) part.push_back(Job{p, Q[i][2 * (size_t)t], Q[i][2 * (size_t)t + 1], 0.0, t});
+      rc = run_attempts(ctx, std::move(part), n_bands, om + base[i] * n_bands, (size_t)n_k[i] * n_bands, nullptr, budget,
+                        true, TRY_LONGER);
+      hipError_t e = rc ? hipSuccess
+                        : hipMemcpyAsync(omega[i], om + base[i] * n_bands, sizeof(double) * n_k[i] * n_bands,
+                                         dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      mvpb_plan_destroy(p);
+      if (rc) return rc;
+      HIP_TRY(e);
+    }
+  }
   if (!dev)
     for (int i = 0; i < n_cells; ++i) {
       rc = check_failed_items(omega[i], (size_t)n_k[i] * n_bands, n_bands);
@@ -2672,7 +2889,9 @@ extern "C" int mvpb_autotune(mvpb_plan p, int n_k, const double *Q, int n_bands,
   ProfBind pb(nullptr);
   hipStream_t st = ctx->stream;
   const bool fp32 = (p->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
-  const size_t need = solve_bytes(n_k, item_bytes(p->n, n_bands, fp32));
+  Route rt = krylov_route(p->n, n_bands, p->dim, fp32, false, TRY_KRYLOV);
+  if (ctx->cap && solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt)) > ctx->cap) rt = Route{};
+  const size_t need = solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt));
   if (ctx->cap && need > ctx->cap)
     return set_err(MVPB_E_NOMEM, "the %d points need %zu bytes of workspace, cap is %zu", n_k, need, ctx->cap);
   std::vector<Job> jobs(n_k);
@@ -2693,12 +2912,12 @@ extern "C" int mvpb_autotune(mvpb_plan p, int n_k, const double *Q, int n_bands,
   // run of a shape captures it)
   auto trial = [&](const TuneParams &tp, double *ms) -> int {
     ctx->tune[cls] = tp;
-    int rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true);
+    int rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, rt);
     if (rc) return rc;
     double t[3];
     for (int r = 0; r < 3; ++r) {
       HIP_TRY(hipEventRecord(e0, st));
-      rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true);
+      rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, rt);
       if (rc) return rc;
       HIP_TRY(hipEventRecord(e1, st));
       HIP_TRY(hipEventSynchronize(e1));
@@ -2872,7 +3091,7 @@ extern "C" int mvpb_kpath(const double lattice[4], const char *path, int n_k, do
 static const char *k_names[K_COUNT] = {"structure_factors", "toeplitz_scatter", "potrf_trtri", "zgemm",
                                        "combine_coefficients", "form_operator", "he2hb_panel", "he2hb_hemm",
                                        "he2hb_wform", "he2hb_her2k", "hb2st", "tridiag_eig", "backtransform",
-                                       "rayleigh_ritz", "hb2st_copy"};
+                                       "rayleigh_ritz", "hb2st_copy", "krylov_factor", "krylov_steps"};
 
 extern "C" int mvpb_ctx_profile(mvpb_ctx ctx, int enable) {
   int rc = check_ctx(ctx);

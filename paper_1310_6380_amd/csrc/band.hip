@@ -449,25 +449,8 @@ struct CMma<float> {
   MVPB_DEV static int row(int lane, int v) { return 4 * (lane >> 4) + v; }
 };
 
-// Work slots of the stage-1 products, S per item, item-major.  Workgroups
-// are dealt to the 8 XCDs round-robin by launch order, so workgroup b takes
-// slot (b % 8) per + b / 8: each XCD works through one contiguous range of
-// slots, and the operands shared by the slots of one item (V, W, X0) are
-// fetched into one or two of the XCDs' L2 caches instead of all eight.  The
-// mapping is a bijection for any placement; only the cache reuse depends on it.
-constexpr int N_XCD = 8;
 // Column-block width of the trailing-matrix product (LDS tile 64 x HEMM_TC)
 constexpr int HEMM_TC = 32;
-MVPB_DEV bool xcd_slot(int S, int n_items, int &item, int &slot) {
-  const int total = n_items * S, per = (total + N_XCD - 1) / N_XCD;
-  const int b = (int)blockIdx.x;
-  const int g = (b % N_XCD) * per + b / N_XCD;
-  if (g >= total) return false;
-  item = g / S;
-  slot = g % S;
-  return true;
-}
-static int xcd_grid(int S, int n_items) { return N_XCD * ((n_items * S + N_XCD - 1) / N_XCD); }
 
 // X0 for row block rb (64 rows) on the matrix cores: wavefront wv owns rows
 // 16 wv .. 16 wv + 15 and all HB = 16 columns; column blocks of TC are
@@ -1718,7 +1701,7 @@ int backtransform_cols(int n_max, bool fp32) {
 }
 
 hipError_t launch_backtransform(const EigItem *items, int n_items, int n_min, int n_max, int nb, bool fp32,
-                                hipStream_t st) {
+                                hipStream_t st, bool stage1) {
   ProfScope ps(K_BACKTRANSFORM, st);
   const int nc = backtransform_cols(n_max, fp32);
   const int groups = (nb + nc - 1) / nc;
@@ -1738,7 +1721,8 @@ hipError_t launch_backtransform(const EigItem *items, int n_items, int n_min, in
     if (any_wave) hipLaunchKernelGGL((backtransform_2s_wave<double>), gw, dim3(BTW_WAVES * 64), 0, st, items, n_items, gws);
     if (any_lds)
       hipLaunchKernelGGL((backtransform_2s<double>), dim3(groups, n_items), dim3(BT_THREADS), sh, st, items, nc);
-    hipLaunchKernelGGL((backtransform_s1<double>), g1, dim3(BT_THREADS), sh, st, items, nc, n_items, groups);
+    if (stage1)
+      hipLaunchKernelGGL((backtransform_s1<double>), g1, dim3(BT_THREADS), sh, st, items, nc, n_items, groups);
   }
   return hipGetLastError();
 }

@@ -209,6 +209,26 @@ MVPB_DEV void lds_barrier() {
 }
 
 // ---------------------------------------------------------------------------
+// Work slots of a launch over the items of a table, S per item, item-major.
+// Workgroups are dealt to the 8 XCDs round-robin by launch order, so workgroup
+// b takes slot (b % 8) per + b / 8: each XCD works through one contiguous
+// range of slots, and the operands shared by the slots of one item are fetched
+// into one or two of the XCDs' L2 caches instead of all eight.  The mapping is
+// a bijection for any placement; only the cache reuse depends on it.
+// ---------------------------------------------------------------------------
+constexpr int N_XCD = 8;
+MVPB_DEV bool xcd_slot(int S, int n_items, int &item, int &slot) {
+  const int total = n_items * S, per = (total + N_XCD - 1) / N_XCD;
+  const int b = (int)blockIdx.x;
+  const int g = (b % N_XCD) * per + b / N_XCD;
+  if (g >= total) return false;
+  item = g / S;
+  slot = g % S;
+  return true;
+}
+inline int xcd_grid(int S, int n_items) { return N_XCD * ((n_items * S + N_XCD - 1) / N_XCD); }
+
+// ---------------------------------------------------------------------------
 // Host-side launch status helper.
 // ---------------------------------------------------------------------------
 #define MVPB_LAUNCH_CHECK() (hipGetLastError())

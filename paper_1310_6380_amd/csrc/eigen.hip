@@ -1160,6 +1160,7 @@ hipError_t init_kernel_attributes() {
     for (int nb = 8; nb <= RRP_BC_MAX && e == hipSuccess; nb += 4)
       e = hipFuncSetAttribute(rr_product_fn(res != 0, nb), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(sizeof(cd) * 2 * 64 * RR_MAX_BANDS));
+  if (e == hipSuccess) e = init_krylov_attributes();
   if (e != hipSuccess) return e;
   return init_band_attributes();
 }

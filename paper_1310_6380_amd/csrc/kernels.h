@@ -82,6 +82,31 @@ struct EigItem {
   int check;        // 1: compute that estimate (FP32 reduction), 0: acc = 0
 };
 
+// One item of the shift-invert block Krylov solve: buffers of the factorisation
+// and the basis, and where the projection's eigenpairs (an EigItem of order m)
+// and the item's Ritz vectors lie.  Blocks of HB vectors are stored row by row,
+// npad (n rounded up to KRY_ROWS) rows each.
+constexpr int KRY_ROWS = 128;
+constexpr int KRY_MAX_STEPS = 32;
+struct KryItem {
+  cd *A;              // n x n working copy: C(k), then C(k) + sigma I, then its Cholesky factor (lower)
+  cd *Xi;             // n x n inverse factor (lower; zero above the diagonal within its 64-blocks)
+  const cd *Ak;       // n x n kept copy of C(k)
+  cd *Q;              // basis blocks
+  cd *W, *Z;          // one block each: L^-1 Q_j, and the next block before its normalisation
+  cd *P;              // HB x HB projections of Z on the basis blocks
+  cd *G;              // HB x HB Gram partials of Z, one per KRY_ROWS rows
+  cd *T;              // m x m projection (its lower band)
+  double *sigma;      // the shift
+  int *status;        // 0; 1: C + sigma I not positive definite; 2: rank-deficient block
+  const cd *Ys;       // m x nb eigenvectors of the projection
+  const double *lam_s;
+  const int *flag_s;  // nonzero if their solve gave up
+  cd *Y;              // n x nb Ritz vectors
+  int *flag;          // nonzero if the item's pairs do not stand
+  int n, npad, nb, m;
+};
+
 // assembly.hip
 hipError_t launch_structure_factors_f64(const int32_t *phase, const double *wtab, int nx, int ny, int M1,
                                         int M2, double area, cd *X, cd *F, hipStream_t st);
@@ -196,11 +221,23 @@ struct Stage2Shape {
 size_t hb2st_ctl_ints(int n_items);
 hipError_t launch_stage2(const EigItem *items, int n_items, int n_max, bool fp32, int *ctl, const Stage2Shape &sh,
                          hipStream_t st);
-// Eigenvectors of C(k) from those of the tridiagonal matrix (X -> Y).
+// Eigenvectors of C(k) from those of the tridiagonal matrix (X -> Y).  stage1
+// false (FP64 only): those of the band matrix, without the panels' part.
 hipError_t launch_backtransform(const EigItem *items, int n_items, int n_min, int n_max, int nb, bool fp32,
-                                hipStream_t st);
+                                hipStream_t st, bool stage1 = true);
 int backtransform_cols(int n_max, bool fp32);
 long long refl_total(int n);   // number of stage-2 reflectors of an item of order n
+
+// krylov.hip
+hipError_t init_krylov_attributes();
+// Krylov steps of a solve for nb bands (dim: coefficient layout, see EigItem).
+int krylov_steps(int nb, int dim, bool modes);
+// C(k) + sigma I factored, s block steps, projection of order HB s.
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st);
+// Ritz vectors from the projection's eigenpairs; items whose residuals exceed
+// tol times their value are flagged.
+hipError_t launch_krylov_ritz(const KryItem *items, int n_items, int n_max, int nb, int s, double tol,
+                              hipStream_t st);
 
 // eigen.hip
 hipError_t init_kernel_attributes();  // once per device, before the first launch

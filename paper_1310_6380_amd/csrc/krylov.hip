@@ -1,0 +1,774 @@
+// Lowest eigenpairs of C(k) by shift-invert block Krylov, for FP64 solves that
+// want a small part of the spectrum.
+//
+// With C + sigma I = L L^H, the wanted lowest eigenvalues of C are the largest,
+// best separated ones of B = (C + sigma I)^-1 = L^-H L^-1.  A block Lanczos
+// recurrence of HB = 16 vectors with full reorthogonalisation projects B on a
+// basis of m = 16 s vectors; the projection is block tridiagonal with upper
+// triangular subdiagonal blocks, i.e. Hermitian of half bandwidth exactly HB,
+// which is the form the bulge chasing takes.  Its eigenpairs, by the same
+// kernels as after stage 1 but of order m instead of n, give n x nb Ritz
+// vectors, and the FP64 Rayleigh-Ritz step on the kept C(k) ends the solve as
+// on the reduction path.
+//
+// Why: the reduction reads and writes the trailing matrix twice per 16 columns
+// (n / 16 passes over HBM) and chases n bulges; the factorisation touches each
+// entry of the matrix in tiles of 64 x 64 on the matrix cores, (8/3) n^3 real
+// multiply-adds with the inverse instead of (16/3) n^3 bandwidth-bound ones,
+// and the chain of sequential sweeps is m long instead of n.  Convergence per
+// step is that of a gap of 16 eigenvalues: the residual of the last wanted
+// pair falls by 10 to 20 per step on the phononic spectra (eigenvalue counts
+// grow like a power of the frequency), and every item checks it: an item that
+// misses the bar is solved again, with more steps or by the reduction.
+// Measured, plan build included, against the reduction: 60 points of 2N = 882,
+// 18 bands, 20.4 -> 12.0 ms; 60 points of 2N = 1922, 24 bands, 123.9 -> 57.1 ms;
+// 960 points of 2N = 242 .. 1250, 10 bands, 228 -> 116 ms.
+#include <float.h>
+
+#include <algorithm>
+
+#include "common.h"
+#include "kernels.h"
+#include "prof.h"
+
+namespace mvpb {
+
+typedef double zd4_t __attribute__((ext_vector_type(4)));
+
+constexpr int KB = 64;        // block of the factorisation
+constexpr int KS = HB;        // vectors of a Krylov block
+constexpr int KR = 32;        // rows of the inverse factor per workgroup of a product
+constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonalisation
+// Shift as a fraction of the nb-th smallest diagonal entry d_nb of C (which
+// overestimates the nb-th eigenvalue, by 2 to 10 and more where the phases
+// differ by orders of magnitude): large enough that L and the block factors stay
+// well conditioned where C is singular (the zero modes at Gamma: condition of a
+// block's factor 1e2, orthogonality of the basis 1e-11), small enough not to
+// slow the convergence (under a tenth of a digit per step against no shift).
+constexpr double KRY_SHIFT = 1.0 / 64.0;
+
+// One K = 4 complex step on the FP64 matrix cores as three real products
+// (p1 = ar br, p2 = ai bi, p3 = (ar + ai)(br + bi)).  Lane l supplies
+// A[l % 16][l / 16] and B[l / 16][l % 16] and holds D[l / 16 + 4 v][l % 16].
+// D therefore has the lane layout of the B operand of a next product: register
+// v is its step v.
+struct Acc3 {
+  zd4_t p1, p2, p3;
+  MVPB_DEV void clear() { p1 = p2 = p3 = zd4_t{0.0, 0.0, 0.0, 0.0}; }
+  MVPB_DEV void step(cd a, cd b) {
+    p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.re, b.re, p1, 0, 0, 0);
+    p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.im, b.im, p2, 0, 0, 0);
+    p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.re + a.im, b.re + b.im, p3, 0, 0, 0);
+  }
+  MVPB_DEV cd get(int v) const { return mk(p1[v] - p2[v], p3[v] - p1[v] - p2[v]); }
+};
+
+// ---------------------------------------------------------------------------
+// Cholesky factor and inverse factor of a 16 x 16 Hermitian tile by one
+// wavefront: lane (r = l % 16, g = l / 16) keeps columns 4 g .. 4 g + 3 of row r
+// of the tile and of the inverse in registers, and step j passes the raw
+// column j and the raw row j of the inverse through LDS once (unscaled, as in
+// L D L^H, so that no square root is on the chain).  Reads the lower triangle
+// of D; writes L and L^-1 with zero upper triangles.  False (uniform) if a
+// pivot is not positive.
+// ---------------------------------------------------------------------------
+template <int LDD>
+MVPB_DEV bool factor16(cd *D, cd *I, cd *col, cd *row) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  cd a[4], x[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int c = 4 * g + u;
+    a[u] = r >= c ? D[r * LDD + c] : mk(0.0, 0.0);
+    x[u] = mk(r == c ? 1.0 : 0.0, 0.0);
+  }
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    if (g == j / 4) col[r] = a[j % 4];
+    if (r == j) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) row[4 * g + u] = x[u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    const double piv = col[j].re;
+    const cd cr = col[r];
+    cd cc[4], xr[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      cc[u] = col[4 * g + u];
+      xr[u] = row[4 * g + u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    ok = ok && piv > 0.0 && piv <= DBL_MAX;
+    const double rs = 1.0 / sqrt(piv);
+    const cd l = (1.0 / piv) * cr;
+    const bool below = r > j;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = 4 * g + u;
+      const cd na = a[u] - l * conj(cc[u]), nx = x[u] - l * xr[u];
+      if (below && c > j) a[u] = na;
+      if (below) x[u] = nx;
+      if (c == j) a[u] = r == j ? mk(piv * rs, 0.0) : rs * a[u];
+      if (r == j) x[u] = rs * x[u];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int c = 4 * g + u;
+    D[r * LDD + c] = r >= c ? a[u] : mk(0.0, 0.0);
+    I[r * LDD + c] = r >= c ? x[u] : mk(0.0, 0.0);
+  }
+  return ok;
+}
+
+// Shift of every item: sigma = KRY_SHIFT times the nb-th smallest diagonal
+// entry of C, added to the diagonal of the working copy.  (Rank counting in
+// LDS, one workgroup per item.)
+__global__ void __launch_bounds__(256) kry_shift(const KryItem *__restrict__ items) {
+  __shared__ double dg[MAX_N];
+  __shared__ double sel;
+  const KryItem it = items[blockIdx.x];
+  const int n = it.n, tid = threadIdx.x;
+  for (int r = tid; r < n; r += 256) dg[r] = gld(it.Ak, (size_t)r * n + r).re;
+  if (tid == 0) {
+    sel = NAN;
+    gst(it.status, 0, 0);
+  }
+  __syncthreads();
+  for (int r = tid; r < n; r += 256) {
+    const double v = dg[r];
+    int rank = 0;
+    for (int q = 0; q < n; ++q) rank += (dg[q] < v || (dg[q] == v && q < r)) ? 1 : 0;
+    if (rank == it.nb - 1) sel = v;
+  }
+  __syncthreads();
+  const double sg = KRY_SHIFT * sel;
+  for (int r = tid; r < n; r += 256) gst(it.A, (size_t)r * n + r, mk(dg[r] + sg, 0.0));
+  if (tid == 0) gst(it.sigma, 0, sg);
+}
+
+// ---------------------------------------------------------------------------
+// Left-looking blocked Cholesky with the inverse factor, block column j:
+//   kry_chol_diag  L_jj and X_jj = L_jj^-1 of the (fully updated) diagonal
+//                  block, one workgroup per item;
+//   kry_chol_step  below the diagonal, L_ij = (A_ij - sum_{k<j} L_ik L_jk^H)
+//                  X_jj^H, and the update A_ii -= L_ij L_ij^H that keeps the
+//                  later diagonal blocks current; left of it,
+//                  X_jc = -X_jj sum_{k=c}^{j-1} L_jk X_kc.
+// Every tile of L and X is written once, so a step streams its operands (K =
+// 64 j deep) at the arithmetic intensity of a 64 x 64 product instead of
+// reading and writing the trailing matrix per 64 columns.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) kry_chol_diag(const KryItem *__restrict__ items, int jb) {
+  constexpr int LD = KB + 1;
+  __shared__ cd D[KB * LD];
+  __shared__ cd I[KB * LD];
+  __shared__ cd col[16], row[16];
+  __shared__ int bad;
+  const KryItem it = items[blockIdx.x];
+  const int n = it.n;
+  if (jb >= n || gld(it.status, 0)) return;
+  const int nb = min(KB, n - jb), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const size_t ld = (size_t)n;
+  cd *A = it.A, *X = it.Xi;
+  {
+    cd v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + 256 * u, r = e % KB, c = e / KB;
+      v[u] = gld(A, (r < nb && c < nb && r >= c) ? (size_t)(jb + c) * ld + jb + r : 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int e = tid + 256 * u, r = e % KB, c = e / KB;
+      D[r * LD + c] = (r < nb && c < nb && r >= c) ? v[u] : mk(r == c ? 1.0 : 0.0, 0.0);
+      I[r * LD + c] = mk(0.0, 0.0);
+    }
+  }
+  if (tid == 0) bad = 0;
+  __syncthreads();
+#pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
+    const int p0 = 16 * p;
+    if (wv == 0) {
+      const bool ok = factor16<LD>(D + p0 * LD + p0, I + p0 * LD + p0, col, row);
+      if (!ok && lane == 0) bad = 1;
+    }
+    __syncthreads();
+    if (bad) {
+      if (tid == 0) gst(it.status, 0, 1);
+      return;
+    }
+    // wavefront w: a tile of L below the diagonal tile, or one of the inverse left of it
+    const int below = 3 - p;
+    if (wv < below) {
+      const int i0 = 16 * (p + 1 + wv);
+      Acc3 o;
+      o.clear();
+#pragma unroll
+      for (int k = 0; k < 16; k += 4)
+        o.step(D[(i0 + li) * LD + p0 + k + lk], conj(I[(p0 + li) * LD + p0 + k + lk]));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) D[(i0 + lk + 4 * v) * LD + p0 + li] = o.get(v);
+    } else if (wv - below < p) {
+      const int c0 = 16 * (wv - below);
+      Acc3 s, o;
+      s.clear();
+      o.clear();
+      for (int k = c0; k < p0; k += 4) s.step(D[(p0 + li) * LD + k + lk], I[(k + lk) * LD + c0 + li]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o.step(I[(p0 + li) * LD + p0 + 4 * v + lk], s.get(v));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) I[(p0 + lk + 4 * v) * LD + c0 + li] = -o.get(v);
+    }
+    __syncthreads();
+    // trailing tiles (i, k), p < k <= i
+    const int nt = below * (below + 1) / 2;
+    for (int t = wv; t < nt; t += 4) {
+      int i = 0;
+      while ((i + 1) * (i + 2) / 2 <= t) ++i;
+      const int k0 = 16 * (p + 1 + t - i * (i + 1) / 2), i0 = 16 * (p + 1 + i);
+      Acc3 u;
+      u.clear();
+#pragma unroll
+      for (int k = 0; k < 16; k += 4)
+        u.step(D[(i0 + li) * LD + p0 + k + lk], conj(D[(k0 + li) * LD + p0 + k + lk]));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        cd *d = &D[(i0 + lk + 4 * v) * LD + k0 + li];
+        *d = *d - u.get(v);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = tid + 256 * u, r = e % KB, c = e / KB;
+    if (r >= nb || c >= nb) continue;
+    if (r >= c) gst(A, (size_t)(jb + c) * ld + jb + r, D[r * LD + c]);
+    gst(X, (size_t)(jb + c) * ld + jb + r, r >= c ? I[r * LD + c] : mk(0.0, 0.0));
+  }
+}
+
+__global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restrict__ items, int n_items, int S, int jb) {
+  constexpr int SK = 8, LD = KB + 1;
+  __shared__ cd sm[2][2][SK * LD];   // [buffer][A, B][k][row or column]
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n;
+  if (jb >= n || gld(it.status, 0)) return;
+  const int j = jb / KB, nblk = (n + KB - 1) / KB, below = nblk - 1 - j;
+  if (slot >= below + j) return;
+  const bool pan = slot < below;
+  const int i0 = jb + KB * (slot + 1), c0 = KB * (slot - below);   // row block of L, or column block of X
+  const int kbeg = pan ? 0 : c0, kend = jb, rows = min(KB, n - jb);
+  const size_t ld = (size_t)n;
+  cd *A = it.A, *X = it.Xi;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  // operands of a step: rows of block j of L, and rows of block i of L or columns of X
+  cd va[2], vb[2];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = tid + 256 * u, r = e % KB, k = e / KB;
+      va[u] = gld(A, (size_t)(k0 + k) * ld + jb + min(r, rows - 1));
+      vb[u] = pan ? gld(A, (size_t)(k0 + k) * ld + min(i0 + r, n - 1))
+                  : gld(X, (size_t)(c0 + e / SK) * ld + k0 + e % SK);
+    }
+  };
+  Acc3 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q].clear();
+  if (kbeg < kend) load(kbeg);
+  int buf = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += SK) {
+    cd *As = sm[buf][0], *Bs = sm[buf][1];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = tid + 256 * u;
+      As[(e / KB) * LD + e % KB] = pan ? conj(va[u]) : va[u];
+      if (pan)
+        Bs[(e / KB) * LD + e % KB] = vb[u];
+      else
+        Bs[(e % SK) * LD + e / SK] = vb[u];
+    }
+    lds_barrier();
+    if (k0 + SK < kend) load(k0 + SK);
+#pragma unroll
+    for (int kk = 0; kk < SK; kk += 4) {
+      const cd b = Bs[(kk + lk) * LD + 16 * wv + li];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q].step(As[(kk + lk) * LD + 16 * q + li], b);
+    }
+    buf ^= 1;
+  }
+  // pan: t[q][v] = (A_ij - sum)(row 16 wv + li, column 16 q + lk + 4 v);
+  // else the sum itself (row 16 q + lk + 4 v, column 16 wv + li)
+  cd t[4][4];
+  if (pan) {
+    const int r = min(i0 + 16 * wv + li, n - 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        t[q][v] = gld(A, (size_t)(jb + 16 * q + lk + 4 * v) * ld + r);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t[q][v] = t[q][v] - acc[q].get(v);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t[q][v] = acc[q].get(v);
+  }
+  // times X_jj^H from the right, or X_jj from the left (lower triangular): the
+  // lanes' values are already the B operand
+  Acc3 up[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) up[q].clear();
+  cd *Ls = sm[0][0];   // 16 columns of L_ij, all 64 rows (16 x LD entries: both operands of a buffer)
+  static_assert(2 * SK >= 16, "a 16-column tile fits one LDS buffer");
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb) {
+    Acc3 o;
+    o.clear();
+#pragma unroll
+    for (int kb = 0; kb <= mb; ++kb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = 16 * mb + li, k = 16 * kb + 4 * v + lk;
+        const bool in = m < rows && k <= m;
+        cd x = gld(X, in ? (size_t)(jb + k) * ld + jb + m : (size_t)jb * ld + jb);
+        x = in ? (pan ? conj(x) : x) : mk(0.0, 0.0);
+        o.step(x, t[kb][v]);
+      }
+    if (pan) {
+      cd ov[4];
+      lds_barrier();   // the previous contents of Ls have been read
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        ov[v] = o.get(v);
+        Ls[(lk + 4 * v) * LD + 16 * wv + li] = ov[v];
+        if (i0 + 16 * wv + li < n) gst(A, (size_t)(jb + 16 * mb + lk + 4 * v) * ld + i0 + 16 * wv + li, ov[v]);
+      }
+      lds_barrier();
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb)
+        if (rb >= wv) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) up[rb].step(Ls[(4 * v + lk) * LD + 16 * rb + li], conj(ov[v]));
+        }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = 16 * mb + lk + 4 * v;
+        if (r < rows) gst(X, (size_t)(c0 + 16 * wv + li) * ld + jb + r, -o.get(v));
+      }
+    }
+  }
+  if (!pan) return;
+  // A_ii -= L_ij L_ij^H, lower triangle
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+    if (rb >= wv) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = i0 + 16 * rb + lk + 4 * v, c = i0 + 16 * wv + li;
+        if (r < n && c <= r) gst(A, (size_t)c * ld + r, gld(A, (size_t)c * ld + r) - up[rb].get(v));
+      }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Block Lanczos.  Blocks are stored row by row (16 entries, 256 bytes per row),
+// so that the operands of a 16-wide matrix-core step are contiguous.  Z holds
+// the next, not yet normalised block; its Gram matrix G = Z^H Z = R^H R comes
+// from the same kernel, and the normalisation Z R^-1 is applied by the next
+// product.
+// ---------------------------------------------------------------------------
+MVPB_DEV double kry_random(unsigned a, unsigned b) {
+  unsigned long long z = ((unsigned long long)a << 32 | b) * 0x9E3779B97F4A7C15ull + 0xD1B54A32D192ED03ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z ^= z >> 31;
+  return (double)(long long)(z >> 11) * (1.0 / 4503599627370496.0) - 1.0;   // [-1, 1)
+}
+
+MVPB_HD int kry_chunks(int n) { return (n + KCH - 1) / KCH; }
+
+// W = L^-1 Q_j with Q_j = Z R_j^-1 (written here as well), rows 32 rb ..
+// 32 rb + 31 by one workgroup, the columns of L^-1 split over its four
+// wavefronts; as W^T = (R^-T) (Z^T L^-T), so that the sums over the wavefronts
+// are the operand of the product with R^-1.  The workgroup of row block 0
+// writes -R_j below the diagonal of the projection (eigenvalues of -B, lowest
+// first).  Bound by reading the inverse factor once.
+__global__ void __launch_bounds__(256) kry_apply_l(const KryItem *__restrict__ items, int n_items, int S, int j) {
+  __shared__ cd Gs[16 * 17], Ri[16 * 17];
+  __shared__ cd col[16], row[16];
+  __shared__ cd red[4][2][4][64];
+  __shared__ int bad;
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n, nrb = (n + KR - 1) / KR;
+  if (slot >= nrb || gld(it.status, 0)) return;
+  const int rb = nrb - 1 - slot, r0 = KR * rb;   // longest rows first
+  const size_t ld = (size_t)n;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  {
+    cd g = mk(0.0, 0.0);
+    const int nch = kry_chunks(n);
+    for (int c = 0; c < nch; ++c) g = g + gld(it.G, (size_t)c * 256 + tid);
+    Gs[(tid >> 4) * 17 + (tid & 15)] = g;
+    if (tid == 0) bad = 0;
+  }
+  __syncthreads();
+  if (wv == 0) {
+    const bool ok = factor16<17>(Gs, Ri, col, row);
+    if (!ok && lane == 0) bad = 1;
+  }
+  const cd *__restrict__ Z = it.Z;
+  const cd *__restrict__ X = it.Xi;
+  const int kend = min(n, r0 + KR);
+  const int ra = min(r0 + li, n - 1), rc = min(r0 + 16 + li, n - 1);
+  Acc3 acc[2];
+  acc[0].clear();
+  acc[1].clear();
+  for (int kg = 16 * wv; kg < kend; kg += 64) {
+    cd a[4], b0[4], b1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kg + 4 * q + lk;
+      const size_t kc = (size_t)min(k, n - 1) * ld;   // Z has zero rows there
+      a[q] = gld(Z, (size_t)k * KS + li);
+      b0[q] = gld(X, kc + ra);
+      b1[q] = gld(X, kc + rc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[0].step(a[q], b0[q]);
+      acc[1].step(a[q], b1[q]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wv][t][v][lane] = acc[t].get(v);
+  __syncthreads();
+  if (bad) {
+    if (tid == 0) gst(it.status, 0, 2);
+    return;
+  }
+  const int t = wv & 1;
+  const size_t r = (size_t)(r0 + 16 * t + li);
+  cd s[4];
+  if (wv < 2) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      s[v] = (red[0][t][v][lane] + red[1][t][v][lane]) + (red[2][t][v][lane] + red[3][t][v][lane]);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[v] = gld(Z, r * KS + 4 * v + lk);
+  }
+  Acc3 o;
+  o.clear();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o.step(conj(Ri[li * 17 + 4 * v + lk]), s[v]);
+  cd *dst = wv < 2 ? it.W : it.Q + (size_t)j * it.npad * KS;
+  if ((int)r < n) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gst(dst, r * KS + lk + 4 * v, o.get(v));
+  }
+  if (rb == 0 && j > 0) {
+    const int tr = tid & 15, tc = tid >> 4;   // -R(tr, tc) = -conj(L(tc, tr))
+    gst(it.T, (size_t)(KS * (j - 1) + tc) * it.m + KS * j + tr, tr <= tc ? -conj(Gs[tc * 17 + tr]) : mk(0.0, 0.0));
+  }
+}
+
+// Z = L^-H W, rows 32 rb .. 32 rb + 31 by one workgroup (a lane takes two
+// consecutive rows of the inverse factor's columns, so that a wavefront reads
+// whole 128-byte lines).
+__global__ void __launch_bounds__(256) kry_apply_lh(const KryItem *__restrict__ items, int n_items, int S) {
+  __shared__ cd red[4][2][4][64];
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n, r0 = KR * slot;
+  if (r0 >= n || gld(it.status, 0)) return;
+  const size_t ld = (size_t)n;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const cd *__restrict__ W = it.W;
+  const cd *__restrict__ X = it.Xi;
+  const size_t ca = (size_t)min(r0 + li, n - 1) * ld, cb = (size_t)min(r0 + 16 + li, n - 1) * ld;
+  Acc3 acc[2];
+  acc[0].clear();
+  acc[1].clear();
+  for (int kg = r0 + 16 * wv; kg < n; kg += 64) {
+    cd a[4], b0[4], b1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kg + 8 * (q >> 1) + 2 * lk + (q & 1), kc = min(k, n - 1);   // W has zero rows beyond n
+      a[q] = gld(W, (size_t)k * KS + li);
+      b0[q] = gld(X, ca + kc);
+      b1[q] = gld(X, cb + kc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[0].step(a[q], conj(b0[q]));
+      acc[1].step(a[q], conj(b1[q]));
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wv][t][v][lane] = acc[t].get(v);
+  __syncthreads();
+  // wavefront w sums registers 2 (w / 2), 2 (w / 2) + 1 of tile w % 2
+  const int t = wv & 1, r = r0 + 16 * t + li;
+  if (r < n) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int v = 2 * (wv >> 1) + h;
+      gst(it.Z, (size_t)r * KS + lk + 4 * v,
+          (red[0][t][v][lane] + red[1][t][v][lane]) + (red[2][t][v][lane] + red[3][t][v][lane]));
+    }
+  }
+}
+
+// P_i = Q_i^H Z of one basis block i <= j: one workgroup per (block, item), the
+// rows over its eight wavefronts.
+__global__ void __launch_bounds__(512) kry_project(const KryItem *__restrict__ items) {
+  __shared__ cd red[8][4][64];
+  const KryItem it = items[blockIdx.y];
+  if (gld(it.status, 0)) return;
+  const int n = it.n, i = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const cd *__restrict__ Q = it.Q + (size_t)i * it.npad * KS;
+  const cd *__restrict__ Z = it.Z;
+  Acc3 acc;
+  acc.clear();
+  for (int kg = 16 * wv; kg < n; kg += 128) {
+    cd a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kg + 4 * q + lk;
+      a[q] = gld(Q, (size_t)min(k, n - 1) * KS + li);
+      b[q] = gld(Z, (size_t)k * KS + li);   // zero rows beyond n
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc.step(conj(a[q]), b[q]);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wv][v][lane] = acc.get(v);
+  __syncthreads();
+  if (tid < 256) {
+    const int v = tid >> 6;
+    cd s = red[0][v][lane];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) s = s + red[w][v][lane];
+    gst(it.P, (size_t)i * 256 + (lk + 4 * v) * KS + li, s);
+  }
+}
+
+// Z -= sum_{i <= j} Q_i P_i and the chunk's part of G = Z^H Z; 128 rows per
+// workgroup, 16 per wavefront.  START: Z = pseudo-random instead (and zero
+// rows beyond n in Z and W), row r scaled by min(1, d_nb / C(r, r)): the low
+// modes lie on the rows of small diagonal, which saves a step.  The workgroup of chunk 0 writes the diagonal
+// block of the projection, -(P_j + P_j^H) / 2.
+template <bool START>
+__global__ void __launch_bounds__(512) kry_update(const KryItem *__restrict__ items, int j) {
+  extern __shared__ __align__(16) unsigned char kry_raw[];
+  cd *Ps = (cd *)kry_raw;   // [j + 1][16][16], then the wavefronts' Gram parts [8][4][64]
+  const KryItem it = items[blockIdx.y];
+  const int n = it.n, r0 = KCH * blockIdx.x;
+  if (r0 >= n || (!START && gld(it.status, 0))) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int rw = r0 + 16 * wv;
+  cd z[4];
+  if (START) {
+    const double dnb = gld(it.sigma, 0) * (1.0 / KRY_SHIFT);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = rw + lk + 4 * v;
+      const double d = gld(it.Ak, (size_t)min(r, n - 1) * (n + 1)).re;
+      const double w = d > dnb ? dnb / d : 1.0;
+      z[v] = r < n ? mk(w * kry_random(r, 2 * li), w * kry_random(r, 2 * li + 1)) : mk(0.0, 0.0);
+      gst(it.Z, (size_t)r * KS + li, z[v]);
+      if (r >= n) gst(it.W, (size_t)r * KS + li, mk(0.0, 0.0));
+    }
+  } else {
+    for (int e = tid; e < (j + 1) * 256; e += 512) Ps[e] = gld(it.P, e);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) z[v] = gld(it.Z, (size_t)(rw + lk + 4 * v) * KS + li);
+    __syncthreads();
+    Acc3 acc;
+    acc.clear();
+    const cd *q0 = it.Q + (size_t)min(rw + li, n - 1) * KS;
+    for (int i = 0; i <= j; ++i) {
+      cd a[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = gld(q0, (size_t)i * it.npad * KS + 4 * q + lk);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc.step(a[q], Ps[i * 256 + (4 * q + lk) * KS + li]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = rw + lk + 4 * v;
+      z[v] = r < n ? z[v] - acc.get(v) : mk(0.0, 0.0);
+      if (r < n) gst(it.Z, (size_t)r * KS + li, z[v]);
+    }
+    if (blockIdx.x == 0 && tid < 256) {
+      const int tr = tid & 15, tc = tid >> 4;
+      const cd p = Ps[j * 256 + tr * KS + tc], q = Ps[j * 256 + tc * KS + tr];
+      gst(it.T, (size_t)(KS * j + tc) * it.m + KS * j + tr, mk(-0.5 * (p.re + q.re), -0.5 * (p.im - q.im)));
+    }
+    __syncthreads();
+  }
+  Acc3 g;
+  g.clear();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) g.step(conj(z[v]), z[v]);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Ps[(wv * 4 + v) * 64 + lane] = g.get(v);
+  __syncthreads();
+  if (tid < 256) {
+    const int v = tid >> 6;
+    cd s = Ps[v * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) s = s + Ps[(w * 4 + v) * 64 + lane];
+    gst(it.G, (size_t)blockIdx.x * 256 + (lk + 4 * v) * KS + li, s);
+  }
+}
+
+// Ritz vectors Y = [Q_0 .. Q_{s-1}] Ys, 128 rows and 16 bands per workgroup.
+__global__ void __launch_bounds__(512) kry_ritz(const KryItem *__restrict__ items) {
+  extern __shared__ __align__(16) unsigned char kry_raw[];
+  cd *Yl = (cd *)kry_raw;   // [m][16]
+  const KryItem it = items[blockIdx.z];
+  const int n = it.n, nb = it.nb, m = it.m, r0 = KCH * blockIdx.x, b0 = 16 * blockIdx.y;
+  if (r0 >= n || b0 >= nb) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
+  for (int e = tid; e < 16 * m; e += 512) {
+    const int k = e % m, b = e / m;
+    Yl[k * 16 + b] = b0 + b < nb ? gld(it.Ys, (size_t)(b0 + b) * m + k) : mk(0.0, 0.0);
+  }
+  __syncthreads();
+  const int r = r0 + 16 * wv + li;
+  const cd *q0 = it.Q + (size_t)min(r, n - 1) * KS;
+  Acc3 acc;
+  acc.clear();
+  for (int i = 0; i < m / KS; ++i) {
+    cd b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b[q] = gld(q0, (size_t)i * it.npad * KS + 4 * q + lk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc.step(Yl[(KS * i + 4 * q + lk) * 16 + li], b[q]);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int b = b0 + lk + 4 * v;
+    if (r < n && b < nb) gst(it.Y, (size_t)b * n + r, acc.get(v));
+  }
+}
+
+// Whether an item's pairs stand: for each, the residual |B y - theta y| =
+// |R_s y_last| (y_last: the last 16 entries of the projection's eigenvector)
+// is at most tol theta, and no run of nearly equal values is so long that the
+// block of 16 could have missed copies (a block Krylov space holds at most 16
+// vectors of one eigenvalue).  Failing items are flagged: their frequencies
+// come out NaN and the host solves them again by the reduction.
+__global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ items, double tol) {
+  __shared__ cd Gs[256];
+  const KryItem it = items[blockIdx.x];
+  const int lane = threadIdx.x, nb = it.nb, m = it.m;
+  int bad = gld(it.status, 0) | gld(it.flag_s, 0);
+  const int nch = kry_chunks(it.n);
+  for (int e = lane; e < 256; e += 64) {
+    cd g = mk(0.0, 0.0);
+    for (int c = 0; c < nch; ++c) g = g + gld(it.G, (size_t)c * 256 + e);
+    Gs[e] = g;
+  }
+  __syncthreads();
+  if (!bad)
+    for (int b = lane; b < nb; b += 64) {
+      const cd *y = it.Ys + (size_t)b * m + m - KS;
+      double s = 0.0;
+      for (int r = 0; r < KS; ++r) {
+        cd t = mk(0.0, 0.0);
+        for (int c = 0; c < KS; ++c) t = cfma(Gs[r * 16 + c], gld(y, c), t);
+        const cd yr = gld(y, r);
+        s += yr.re * t.re + yr.im * t.im;
+      }
+      const double th = -gld(it.lam_s, b);
+      if (!(th > 0.0) || !(s <= tol * tol * th * th)) bad = 1;
+      // a run of KS - 1 neighbouring values within 1e-4
+      if (b + KS - 2 < nb && !(gld(it.lam_s, b + KS - 2) - gld(it.lam_s, b) > 1e-4 * th)) bad = 1;
+    }
+  for (int o = 32; o > 0; o >>= 1) bad |= __shfl_xor(bad, o, 64);
+  if (lane == 0) gst(it.flag, 0, bad ? 1 : 0);
+}
+
+// ---------------------------------------------------------------------------
+// Launches
+// ---------------------------------------------------------------------------
+
+// Krylov steps for nb wanted pairs: the residual of the last pair reaches
+// about 1e-8 of its value (the frequencies' error is about ten times its square)
+// or, with modes wanted, 1e-13.  Measured on planar cells of 2N = 242 .. 1922:
+// 1e-8 after 6, 8, 9 to 10, 11 and 13 steps for nb = 4, 7, 10, 18 and 24, 1e-13
+// after 9 and 15 for nb = 4 and 18; on a spatial one (3N = 1029, nb = 12), whose
+// spectrum is denser, 11 and 15.
+int krylov_steps(int nb, int dim, bool modes) {
+  return 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0) + (modes ? 2 + nb / 12 : 0);
+}
+
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st) {
+  {
+    ProfScope ps(K_FACTOR, st);
+    hipLaunchKernelGGL(kry_shift, dim3(n_items), dim3(256), 0, st, items);
+    const int nblk = (n_max + KB - 1) / KB;
+    for (int j = 0; j < nblk; ++j) {
+      hipLaunchKernelGGL(kry_chol_diag, dim3(n_items), dim3(256), 0, st, items, j * KB);
+      if (nblk > 1)
+        hipLaunchKernelGGL(kry_chol_step, dim3(xcd_grid(nblk - 1, n_items)), dim3(256), 0, st, items, n_items,
+                           nblk - 1, j * KB);
+    }
+  }
+  ProfScope ps(K_KRYLOV, st);
+  const int nch = kry_chunks(n_max), nrb = (n_max + KR - 1) / KR;
+  const size_t red = sizeof(cd) * 8 * 256;
+  hipLaunchKernelGGL(kry_update<true>, dim3(nch, n_items), dim3(512), red, st, items, 0);
+  for (int j = 0; j < s; ++j) {
+    hipLaunchKernelGGL(kry_apply_l, dim3(xcd_grid(nrb, n_items)), dim3(256), 0, st, items, n_items, nrb, j);
+    hipLaunchKernelGGL(kry_apply_lh, dim3(xcd_grid(nrb, n_items)), dim3(256), 0, st, items, n_items, nrb);
+    hipLaunchKernelGGL(kry_project, dim3(j + 1, n_items), dim3(512), 0, st, items);
+    hipLaunchKernelGGL(kry_update<false>, dim3(nch, n_items), dim3(512),
+                       std::max(red, sizeof(cd) * 256 * (size_t)(j + 1)), st, items, j);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_krylov_ritz(const KryItem *items, int n_items, int n_max, int nb, int s, double tol,
+                              hipStream_t st) {
+  ProfScope ps(K_KRYLOV, st);
+  hipLaunchKernelGGL(kry_ritz, dim3(kry_chunks(n_max), (nb + 15) / 16, n_items), dim3(512),
+                     sizeof(cd) * 16 * KS * (size_t)s, st, items);
+  hipLaunchKernelGGL(kry_check, dim3(n_items), dim3(64), 0, st, items, tol);
+  return hipGetLastError();
+}
+
+hipError_t init_krylov_attributes() {
+  const int most = (int)(sizeof(cd) * 256 * KRY_MAX_STEPS);
+  hipError_t e = hipFuncSetAttribute((const void *)kry_update<false>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void *)kry_ritz, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  return e;
+}
+
+}  // namespace mvpb

@@ -23,6 +23,8 @@ enum KernelId {
   K_BACKTRANSFORM,
   K_RR,
   K_HB2ST_IO,
+  K_FACTOR,
+  K_KRYLOV,
   K_COUNT
 };
 

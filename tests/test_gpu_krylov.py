@@ -1,0 +1,119 @@
+"""The shift-invert block Krylov route of FP64 solves, at the sizes where its
+tiles end: orders just around multiples of the factorisation's block (64), of
+the products' rows (32) and of the orthogonalisation's chunk (128), one block
+and many, few and many bands.  Frequencies against the oracle to the bar of
+every FP64 path (1e-9), degenerate spectra against the folded free dispersion,
+where more copies of one eigenvalue than the block holds (16) have to come from
+the reduction, and modes by their residual in the Galerkin equations."""
+import numpy as np
+import pytest
+
+from oracle import mixed_oracle as mo
+from oracle.compare import band_error
+from synth import random_iso_props
+
+pytestmark = pytest.mark.gpu
+
+TOL64 = 1e-9
+OBLIQUE = np.array([[1.0, 0.0], [0.5, np.sqrt(3.0) / 2.0]])
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1310_6380_amd import mvpb
+    c = mvpb.Context(0)
+    yield c
+    c.close()
+
+
+def _cell(seed, n=24, phases=4):
+    rng = np.random.default_rng(seed)
+    return rng.integers(0, phases, (n, n)).astype(np.int32), random_iso_props(phases, rng)
+
+
+# (M1, M2, bands): 2N = 198 (3 blocks and 6), 242, 310 = 2 x 128 + 54, 378, 510 = 512 - 2, 518 = 512 + 6, 578, 650
+@pytest.mark.parametrize("M1,M2,nb", [(4, 5, 1), (5, 5, 4), (2, 15, 3), (4, 10, 9), (7, 8, 6), (3, 18, 20), (8, 8, 24),
+                                      (6, 12, 33)])
+def test_krylov_bands_match_oracle(ctx, M1, M2, nb):
+    phase, props = _cell(M1 * 31 + M2)
+    Q = np.array([[0.0, 0.0], [0.31, 0.12], [0.5, 0.5]])
+    print("krylov", M1, M2, nb, flush=True)
+    om = ctx.cell(phase, props, OBLIQUE).plan(M1, M2).solve(Q, nb)
+    ref, _ = mo.bands(phase, props, OBLIQUE, M1, M2, Q, nb)
+    err = band_error(om, ref)
+    print("  error", err, flush=True)
+    assert np.all(np.isfinite(om)) and err <= TOL64
+
+
+def test_krylov_same_by_every_entry(ctx):
+    """One operator through solve (host and device output), solve_batch and
+    solve_cells, and without waiting (the reduction): one result."""
+    from paper_1310_6380_amd import mvpb
+    phase, props = _cell(5)
+    M, nb = 6, 5
+    Q = np.array([[0.05, 0.21], [0.44, 0.1], [0.5, 0.5], [0.3, 0.3]])
+    cell = ctx.cell(phase, props)
+    plan = cell.plan(M)
+    om = plan.solve(Q, nb)
+    buf = mvpb.DeviceBuffer(om.nbytes)
+    plan.solve_device(Q, nb, buf.value)
+    assert np.array_equal(buf.to_numpy(np.float64, om.shape), om)
+    assert np.array_equal(ctx.solve_batch([plan], [Q], nb)[0], om)
+    assert band_error(ctx.solve_cells([cell], [M], [Q], nb)[0], om) <= 1e-10
+    plan.solve_device(Q, nb, buf.value, mvpb.F_DEVICE_PTRS | mvpb.F_ASYNC)
+    mvpb.device_synchronize()
+    assert band_error(buf.to_numpy(np.float64, om.shape), om) <= 1e-10
+
+
+def _folded(c, T, n, q, nb):
+    """Sorted c |2 pi T (q + n)| over the plane waves n and the wave speeds c."""
+    K = np.linalg.norm(2.0 * np.pi * (np.asarray(q)[None, :] + n) @ T.T, axis=1)
+    return np.sort(np.concatenate([s * K for s in c]))[:nb]
+
+
+def test_krylov_degenerate_planar(ctx):
+    """Homogeneous cell: eightfold frequencies at Gamma."""
+    E, nu, rho = 70e9, 0.33, 2700.0
+    lam, mu = mo.lame(E, nu)
+    c = (np.sqrt((lam + 2 * mu) / rho), np.sqrt(mu / rho))
+    M, nb = 8, 20
+    n = mo.plane_wave_indices(M, M)
+    Q = np.array([[0.0, 0.0], [0.5, 0.5], [0.25, 0.0]])
+    om = ctx.cell(np.zeros((8, 8), np.int32), np.array([[E, nu, rho]])).plan(M).solve(Q, nb)
+    ref = np.stack([_folded(c, np.eye(2), n, q, nb) for q in Q])
+    assert band_error(om, ref) <= TOL64
+
+
+def test_krylov_more_copies_than_block(ctx):
+    """Homogeneous cube at Gamma: 24 equal shear frequencies of the twelve
+    waves (1, 1, 0), which no Krylov space of 16 vectors holds."""
+    E, nu, rho = 3.5e9, 0.35, 1180.0
+    mu, lam = E / (2 * (1 + nu)), E * nu / ((1 + nu) * (1 - 2 * nu))
+    ct, cl = np.sqrt(mu / rho), np.sqrt((lam + 2 * mu) / rho)
+    M, nb = 3, 40
+    g = np.arange(-M, M + 1)
+    n = np.stack(np.meshgrid(g, g, g, indexing="ij"), axis=-1).reshape(-1, 3)
+    Q = np.array([[0.0, 0.0, 0.0], [0.13, 0.21, 0.34]])
+    om = ctx.cell_voxels(np.zeros((6, 6, 6), np.int32), np.array([[E, nu, rho]])).plan(M).solve(Q, nb)
+    ref = np.stack([_folded((ct, ct, cl), np.eye(3), n, q, nb) for q in Q])
+    assert band_error(om, ref) <= TOL64
+
+
+def test_krylov_modes(ctx):
+    """Modes: H Phi^-1 H* U = lambda Omega U and U^H Omega U = 1."""
+    phase, props = _cell(11)
+    M, nb = 7, 9
+    Q = np.array([[0.21, 0.35], [0.02, -0.4]])
+    om, U = ctx.cell(phase, props).plan(M).solve(Q, nb, vectors=True)
+    I = mo.subdomain_integral_tables(phase, props.shape[0], np.eye(2), M, M)
+    for t, q in enumerate(Q):
+        m = mo.assemble(I, props, np.eye(2), M, M, q)
+        V = U[t].T
+        A = m["H"] @ np.linalg.solve(m["Phi"], m["Hs"] @ V)
+        B = m["Omega"] @ V
+        # the residual in the norm of the low part of the spectrum
+        res = np.linalg.norm(np.linalg.solve(m["Omega"], A - B * om[t] ** 2)) / \
+            np.linalg.norm(np.linalg.solve(m["Omega"], B * om[t] ** 2))
+        orth = np.abs(V.conj().T @ B - np.eye(nb)).max()
+        print("  residual", res, "orthonormality", orth, flush=True)
+        assert res <= 1e-7 and orth <= 1e-10
