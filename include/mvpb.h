@@ -431,13 +431,13 @@ int mvpb_sur_load(mvpb_ctx ctx, const char *path, int max_batch, mvpb_sur *out);
  * 5 form_operator, 6 he2hb_panel, 7 he2hb_hemm, 8 he2hb_wform,
  * 9 he2hb_her2k, 10 hb2st (the bulge chasing itself), 11 tridiag_eig,
  * 12 backtransform, 13 rayleigh_ritz, 14 hb2st_copy (band copy in and
- * tridiagonal out around hb2st), 15 krylov_factor, 16 krylov_steps
- * (MVPB_N_KERNELS in total).  Launches
+ * tridiagonal out around hb2st), 15 krylov_factor, 16 krylov_steps,
+ * 17 small_tridiag (MVPB_N_KERNELS in total).  Launches
  * inside the HIP graph of mvpb_solve_batch are not timed.
  * mvpb_ctx_profile(ctx, 1) clears the totals and starts timing, 0 stops.
  * mvpb_ctx_profile_read waits for the recorded events and returns the total
  * milliseconds, the number of launches and a static name string. */
-#define MVPB_N_KERNELS 17
+#define MVPB_N_KERNELS 18
 int mvpb_ctx_profile(mvpb_ctx ctx, int enable);
 /* As mvpb_ctx_profile(ctx, 1), but only the kernels whose bit (1 << id) is
  * set in mask are bracketed by events (mask 0 stops timing), so that timing

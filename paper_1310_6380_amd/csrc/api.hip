@@ -1718,6 +1718,19 @@ static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const
     if (e == hipSuccess) e = launch_rayleigh_ritz(d_items, n_items, n_max, nb, false, st);
     return e;
   }
+  // Small operators in FP64: the one-workgroup reduction.  The line is where the
+  // matrix stops fitting the registers of a CU; at n = 98 a call of one point
+  // takes 434 us against 1107 us by the two stages, of 30 points with their plan
+  // 622 against 1340 us.
+  if (!fp32 && n_max <= SMALL_MAX_N) {
+    if (e == hipSuccess) e = launch_small_tridiag(d_items, n_items, n_min, n_max, st);
+    if (e == hipSuccess) e = launch_tridiag_eig(d_items, n_items, n_max, nb, st, ctx->la[0], la_ev[0], la_ev[1]);
+    if (e == hipSuccess) e = launch_small_back(d_items, n_items, nb, st);
+    if (e == hipSuccess)
+      e = nb <= RR_MAX_BANDS ? launch_rayleigh_ritz(d_items, n_items, n_max, nb, fp32, st)
+                             : launch_tridiag_results(d_items, n_items, nb, st);
+    return e;
+  }
   // stage 1 in independent parts of the items, one per stream
   ItemPart parts[MAX_SIDE + 1];
   const int n_parts = std::max(1, std::min(parts_wanted, n_items));
@@ -3091,7 +3104,8 @@ extern "C" int mvpb_kpath(const double lattice[4], const char *path, int n_k, do
 static const char *k_names[K_COUNT] = {"structure_factors", "toeplitz_scatter", "potrf_trtri", "zgemm",
                                        "combine_coefficients", "form_operator", "he2hb_panel", "he2hb_hemm",
                                        "he2hb_wform", "he2hb_her2k", "hb2st", "tridiag_eig", "backtransform",
-                                       "rayleigh_ritz", "hb2st_copy", "krylov_factor", "krylov_steps"};
+                                       "rayleigh_ritz", "hb2st_copy", "krylov_factor", "krylov_steps",
+                                       "small_tridiag"};
 
 extern "C" int mvpb_ctx_profile(mvpb_ctx ctx, int enable) {
   int rc = check_ctx(ctx);

@@ -133,10 +133,9 @@ __global__ void __launch_bounds__(BISI_THREADS) tridiag_bisect_item(const EigIte
   extern __shared__ double shd[];   // dd (n), ee (n), e2p (n + 1)
   __shared__ double red[3 * (BISI_THREADS / 64)];
   __shared__ double xs[BISI_THREADS];
-  __shared__ int cnt_s[BISI_THREADS];
   __shared__ int first_s[BISI_THREADS / 64][BISI_MAX];
   __shared__ double lo_s[BISI_MAX], hi_s[BISI_MAX];
-  __shared__ int act_s[BISI_MAX];
+  __shared__ int act_s[BISI_MAX], low_s[BISI_MAX];
   __shared__ int nact_s;
   const EigItem it = items[blockIdx.y];
   const int n = it.n, nb_all = it.nb, g0 = blockIdx.x;
@@ -197,23 +196,20 @@ __global__ void __launch_bounds__(BISI_THREADS) tridiag_bisect_item(const EigIte
     if (na == 0) break;
     const int P = BISI_THREADS / na;   // probes per open eigenvalue (>= 4 for nb <= MAX_BANDS)
     const int a = tid / P, pq = tid % P;
+    if (tid < na) low_s[tid] = P;
+    __syncthreads();
     if (a < na) {
       const int j = act_s[a];
       const double lo = lo_s[j], hi = hi_s[j];
       const double x = lo + (hi - lo) * (double)(pq + 1) / (double)(P + 1);
       xs[tid] = x;
-      cnt_s[tid] = sturm_count_minors(dd, e2p, n, x);
+      // first probe of the bracket with more than jg eigenvalues below it
+      if (sturm_count_minors(dd, e2p, n, x) > g0 + BISI_GROUPS * j) atomicMin(&low_s[a], pq);
     }
     __syncthreads();
     if (tid < na) {
       const int j = act_s[tid];
-      const int jg = g0 + BISI_GROUPS * j;   // index among all eigenvalues
-      int g = P;
-      for (int q = 0; q < P; ++q)
-        if (cnt_s[tid * P + q] > jg) {
-          g = q;
-          break;
-        }
+      const int g = low_s[tid];
       const double lo = lo_s[j], hi = hi_s[j];
       lo_s[j] = (g > 0) ? xs[tid * P + g - 1] : lo;
       hi_s[j] = (g < P) ? xs[tid * P + g] : hi;

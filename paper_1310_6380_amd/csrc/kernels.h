@@ -228,6 +228,13 @@ hipError_t launch_backtransform(const EigItem *items, int n_items, int n_min, in
 int backtransform_cols(int n_max, bool fp32);
 long long refl_total(int n);   // number of stage-2 reflectors of an item of order n
 
+// small.hip: items of order at most SMALL_MAX_N
+constexpr int SMALL_MAX_N = 128;
+// Kept C(k) (Ak) to d, e; reflectors in A, their scalars in tau2.
+hipError_t launch_small_tridiag(const EigItem *items, int n_items, int n_min, int n_max, hipStream_t st);
+// Eigenvectors of C(k) from those of the tridiagonal matrix (X -> Y).
+hipError_t launch_small_back(const EigItem *items, int n_items, int nb, hipStream_t st);
+
 // krylov.hip
 hipError_t init_krylov_attributes();
 // Krylov steps of a solve for nb bands (dim: coefficient layout, see EigItem).

@@ -25,6 +25,7 @@ enum KernelId {
   K_HB2ST_IO,
   K_FACTOR,
   K_KRYLOV,
+  K_SMALL,
   K_COUNT
 };
 

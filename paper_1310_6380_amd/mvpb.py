@@ -56,7 +56,7 @@ EXPORTS = [
     "mvpb_band_sensitivities", "mvpb_autotune", "mvpb_ctx_load_tuning", "mvpb_ctx_set_wait_limit",
     "mvpb_ctx_set_launch_shape", "mvpb_ctx_get_launch_shape", "mvpb_solve_cells",
 ]
-N_KERNELS = 17
+N_KERNELS = 18
 
 
 class MvpbError(RuntimeError):
