@@ -1710,7 +1710,9 @@ static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const
     const EigItem *d_small = d_items + n_items;
     const KryItem *d_kry = reinterpret_cast<const KryItem *>(d_items + 2 * (size_t)n_items);
     const int m = HB * rt.steps;
-    if (e == hipSuccess) e = launch_krylov(d_kry, n_items, n_max, rt.steps, st);
+    double n3 = 0.0;
+    for (int n : orders) n3 += (double)n * n * n;
+    if (e == hipSuccess) e = launch_krylov(d_kry, n_items, n_max, n3, rt.steps, st);
     if (e == hipSuccess) e = launch_stage2(d_small, n_items, m, false, ctl, sh, st);
     if (e == hipSuccess) e = launch_tridiag_eig(d_small, n_items, m, nb, st, ctx->la[0], la_ev[0], la_ev[1]);
     if (e == hipSuccess) e = launch_backtransform(d_small, n_items, m, m, nb, false, st, false);

@@ -90,7 +90,7 @@ constexpr int KRY_ROWS = 128;
 constexpr int KRY_MAX_STEPS = 32;
 struct KryItem {
   cd *A;              // n x n working copy: C(k), then C(k) + sigma I, then its Cholesky factor (lower)
-  cd *Xi;             // n x n inverse factor (lower; zero above the diagonal within its 64-blocks)
+  cd *Xi;             // n x n inverse factor within each part (lower; zero above the diagonal in its 64-blocks)
   const cd *Ak;       // n x n kept copy of C(k)
   cd *Q;              // basis blocks
   cd *W, *Z;          // one block each: L^-1 Q_j, and the next block before its normalisation
@@ -240,7 +240,8 @@ hipError_t init_krylov_attributes();
 // Krylov steps of a solve for nb bands (dim: coefficient layout, see EigItem).
 int krylov_steps(int nb, int dim, bool modes);
 // C(k) + sigma I factored, s block steps, projection of order HB s.
-hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st);
+// n3_sum: sum of the items' cubed orders.
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, double n3_sum, int s, hipStream_t st);
 // Ritz vectors from the projection's eigenpairs; items whose residuals exceed
 // tol times their value are flagged.
 hipError_t launch_krylov_ritz(const KryItem *items, int n_items, int n_max, int nb, int s, double tol,

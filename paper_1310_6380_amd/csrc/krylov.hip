@@ -37,7 +37,7 @@ typedef double zd4_t __attribute__((ext_vector_type(4)));
 
 constexpr int KB = 64;        // block of the factorisation
 constexpr int KS = HB;        // vectors of a Krylov block
-constexpr int KR = 32;        // rows of the inverse factor per workgroup of a product
+constexpr int KR = 32;        // rows of the factor per workgroup of a product
 constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonalisation
 // Shift as a fraction of the nb-th smallest diagonal entry d_nb of C (which
 // overestimates the nb-th eigenvalue, by 2 to 10 and more where the phases
@@ -66,88 +66,107 @@ struct Acc3 {
 // ---------------------------------------------------------------------------
 // Cholesky factor and inverse factor of a 16 x 16 Hermitian tile by one
 // wavefront: lane (r = l % 16, g = l / 16) keeps columns 4 g .. 4 g + 3 of row r
-// of the tile and of the inverse in registers, and step j passes the raw
-// column j and the raw row j of the inverse through LDS once (unscaled, as in
-// L D L^H, so that no square root is on the chain).  Reads the lower triangle
-// of D; writes L and L^-1 with zero upper triangles.  False (uniform) if a
-// pivot is not positive.
+// of the tile and of the inverse in registers, and step j passes column j (zero
+// down to row j) and row j of the inverse through LDS once, unscaled as in
+// L D L^H: the update then needs no selects, and the scalings by the square roots
+// of the pivots wait until the end.  One wavefront issues an instruction every
+// four to five cycles, so the instructions of a step are its time (with selects
+// and scalings in the step 1000 cycles, without 400).  Reads the lower triangle
+// of D; writes L and L^-1 with zero upper triangles.  False (uniform) if a pivot
+// is not positive.
 // ---------------------------------------------------------------------------
+struct Factor16 {
+  cd col[16], row[16];
+  double piv[16];
+};
 template <int LDD>
-MVPB_DEV bool factor16(cd *D, cd *I, cd *col, cd *row) {
+MVPB_DEV bool factor16(cd *D, cd *I, Factor16 &sm) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   cd a[4], x[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = 4 * g + u;
-    a[u] = r >= c ? D[r * LDD + c] : mk(0.0, 0.0);
+    const cd v = D[r * LDD + c];
+    a[u] = r >= c ? v : mk(0.0, 0.0);
     x[u] = mk(r == c ? 1.0 : 0.0, 0.0);
   }
   bool ok = true;
+#pragma unroll 1
+  for (int jg = 0; jg < 4; ++jg)
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    if (g == j / 4) col[r] = a[j % 4];
-    if (r == j) {
+    for (int ju = 0; ju < 4; ++ju) {
+      const int j = 4 * jg + ju;
+      if (g == jg) {
+        sm.col[r] = r > j ? a[ju] : mk(0.0, 0.0);
+        if (r == j) sm.piv[j] = a[ju].re;
+      }
+      if (r == j) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) row[4 * g + u] = x[u];
+        for (int u = 0; u < 4; ++u) sm.row[4 * g + u] = x[u];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      const double piv = sm.piv[j];
+      const cd cr = sm.col[r];
+      cd cc[4], xr[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        cc[u] = conj(sm.col[4 * g + u]);
+        xr[u] = sm.row[4 * g + u];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      ok = ok && piv > 0.0 && piv <= DBL_MAX;
+      const cd l = -quick_rcp(piv) * cr;   // zero for r <= j
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        a[u] = cfma(l, cc[u], a[u]);
+        x[u] = cfma(l, xr[u], x[u]);
+      }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    const double piv = col[j].re;
-    const cd cr = col[r];
-    cd cc[4], xr[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      cc[u] = col[4 * g + u];
-      xr[u] = row[4 * g + u];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    ok = ok && piv > 0.0 && piv <= DBL_MAX;
-    const double rs = 1.0 / sqrt(piv);
-    const cd l = (1.0 / piv) * cr;
-    const bool below = r > j;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = 4 * g + u;
-      const cd na = a[u] - l * conj(cc[u]), nx = x[u] - l * xr[u];
-      if (below && c > j) a[u] = na;
-      if (below) x[u] = nx;
-      if (c == j) a[u] = r == j ? mk(piv * rs, 0.0) : rs * a[u];
-      if (r == j) x[u] = rs * x[u];
-    }
-  }
+  double t, sr;
+  sqrt_rcp(sm.piv[r], t, sr);
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = 4 * g + u;
-    D[r * LDD + c] = r >= c ? a[u] : mk(0.0, 0.0);
-    I[r * LDD + c] = r >= c ? x[u] : mk(0.0, 0.0);
+    double sc;
+    sqrt_rcp(sm.piv[c], t, sc);
+    D[r * LDD + c] = r > c ? sc * a[u] : mk(r == c ? t : 0.0, 0.0);
+    I[r * LDD + c] = r >= c ? sr * x[u] : mk(0.0, 0.0);
   }
   return ok;
 }
 
 // Shift of every item: sigma = KRY_SHIFT times the nb-th smallest diagonal
 // entry of C, added to the diagonal of the working copy.  (Rank counting in
-// LDS, one workgroup per item.)
-__global__ void __launch_bounds__(256) kry_shift(const KryItem *__restrict__ items) {
-  __shared__ double dg[MAX_N];
+// LDS, one workgroup per item, one entry per thread and pass.)
+__global__ void __launch_bounds__(1024) kry_shift(const KryItem *__restrict__ items) {
+  __shared__ double dg[MAX_N + 8];
   __shared__ double sel;
   const KryItem it = items[blockIdx.x];
   const int n = it.n, tid = threadIdx.x;
-  for (int r = tid; r < n; r += 256) dg[r] = gld(it.Ak, (size_t)r * n + r).re;
+  for (int r = tid; r < n; r += 1024) dg[r] = gld(it.Ak, (size_t)r * n + r).re;
+  if (tid < 8) dg[n + tid] = INFINITY;
   if (tid == 0) {
     sel = NAN;
     gst(it.status, 0, 0);
   }
   __syncthreads();
-  for (int r = tid; r < n; r += 256) {
+  for (int r = tid; r < n; r += 1024) {
     const double v = dg[r];
     int rank = 0;
-    for (int q = 0; q < n; ++q) rank += (dg[q] < v || (dg[q] == v && q < r)) ? 1 : 0;
+    for (int q0 = 0; q0 < n; q0 += 8) {
+      double w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = dg[q0 + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) rank += (w[u] < v) | ((w[u] == v) & (q0 + u < r));
+    }
     if (rank == it.nb - 1) sel = v;
   }
   __syncthreads();
   const double sg = KRY_SHIFT * sel;
-  for (int r = tid; r < n; r += 256) gst(it.A, (size_t)r * n + r, mk(dg[r] + sg, 0.0));
+  for (int r = tid; r < n; r += 1024) gst(it.A, (size_t)r * n + r, mk(dg[r] + sg, 0.0));
   if (tid == 0) gst(it.sigma, 0, sg);
 }
 
@@ -157,7 +176,8 @@ __global__ void __launch_bounds__(256) kry_shift(const KryItem *__restrict__ ite
 //                  block, one workgroup per item;
 //   kry_chol_step  below the diagonal, L_ij = (A_ij - sum_{k<j} L_ik L_jk^H)
 //                  X_jj^H, and the update A_ii -= L_ij L_ij^H that keeps the
-//                  later diagonal blocks current; left of it,
+//                  later diagonal blocks current; left of it, within the part
+//                  of the inverse that block j belongs to,
 //                  X_jc = -X_jj sum_{k=c}^{j-1} L_jk X_kc.
 // Every tile of L and X is written once, so a step streams its operands (K =
 // 64 j deep) at the arithmetic intensity of a 64 x 64 product instead of
@@ -167,7 +187,7 @@ __global__ void __launch_bounds__(256) kry_chol_diag(const KryItem *__restrict__
   constexpr int LD = KB + 1;
   __shared__ cd D[KB * LD];
   __shared__ cd I[KB * LD];
-  __shared__ cd col[16], row[16];
+  __shared__ Factor16 fs;
   __shared__ int bad;
   const KryItem it = items[blockIdx.x];
   const int n = it.n;
@@ -195,7 +215,7 @@ __global__ void __launch_bounds__(256) kry_chol_diag(const KryItem *__restrict__
   for (int p = 0; p < 4; ++p) {
     const int p0 = 16 * p;
     if (wv == 0) {
-      const bool ok = factor16<LD>(D + p0 * LD + p0, I + p0 * LD + p0, col, row);
+      const bool ok = factor16<LD>(D + p0 * LD + p0, I + p0 * LD + p0, fs);
       if (!ok && lane == 0) bad = 1;
     }
     __syncthreads();
@@ -254,63 +274,77 @@ __global__ void __launch_bounds__(256) kry_chol_diag(const KryItem *__restrict__
   }
 }
 
-__global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restrict__ items, int n_items, int S, int jb) {
-  constexpr int SK = 8, LD = KB + 1;
-  __shared__ cd sm[2][2][SK * LD];   // [buffer][A, B][k][row or column]
-  int item, slot;
-  if (!xcd_slot(S, n_items, item, slot)) return;
-  const KryItem it = items[item];
-  const int n = it.n;
-  if (jb >= n || gld(it.status, 0)) return;
-  const int j = jb / KB, nblk = (n + KB - 1) / KB, below = nblk - 1 - j;
-  if (slot >= below + j) return;
-  const bool pan = slot < below;
-  const int i0 = jb + KB * (slot + 1), c0 = KB * (slot - below);   // row block of L, or column block of X
-  const int kbeg = pan ? 0 : c0, kend = jb, rows = min(KB, n - jb);
+constexpr int SK = 8;         // columns of an operand step
+constexpr int SLD = KB + 1;
+
+// One tile of block column j: PAN: row block at i0 of L and the update of its
+// diagonal block; else: column block at c0 of row block j of X.
+template <bool PAN>
+MVPB_DEV void chol_tile(const KryItem &it, int jb, int i0, int c0, cd (&sm)[2][2][SK * SLD]) {
+  const int n = it.n, rows = PAN ? KB : min(KB, n - jb);
+  const int kbeg = PAN ? 0 : c0, kend = jb;
   const size_t ld = (size_t)n;
   cd *A = it.A, *X = it.Xi;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
-  // operands of a step: rows of block j of L, and rows of block i of L or columns of X
-  cd va[2], vb[2];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int e = tid + 256 * u, r = e % KB, k = e / KB;
-      va[u] = gld(A, (size_t)(k0 + k) * ld + jb + min(r, rows - 1));
-      vb[u] = pan ? gld(A, (size_t)(k0 + k) * ld + min(i0 + r, n - 1))
-                  : gld(X, (size_t)(c0 + e / SK) * ld + k0 + e % SK);
-    }
+  // operands of a step: SK columns of rows of block j of L, and of rows of block i
+  // of L or SK rows of columns of X; thread t takes entries t and t + 256.  PF
+  // steps are in flight; the loads are unconditional (the last ones are repeated),
+  // as a conditional load makes the compiler wait for it at the end of its branch.
+  constexpr int PF = 2;
+  static_assert(KB / SK % PF == 0, "whole rounds of the prefetch registers");
+  const int e1 = tid + 256;
+  const cd *pa = A + (size_t)(tid / KB) * ld + jb + min(tid % KB, rows - 1);
+  const cd *pb = PAN ? A + (size_t)(tid / KB) * ld + min(i0 + tid % KB, n - 1)
+                     : X + (size_t)(c0 + tid / SK) * ld + tid % SK;
+  const size_t da = (256 / KB) * ld, db = PAN ? (256 / KB) * ld : (256 / SK) * ld;
+  cd va[PF][2], vb[PF][2];
+  auto load = [&](int k, cd *a, cd *b) {
+    const int kc = min(k, kend - SK);
+    const cd *qa = pa + (size_t)kc * ld, *qb = PAN ? pb + (size_t)kc * ld : pb + kc;
+    a[0] = gld(qa, 0);
+    a[1] = gld(qa, da);
+    b[0] = gld(qb, 0);
+    b[1] = gld(qb, db);
+  };
+  auto store = [&](cd *As, cd *Bs, const cd *a, const cd *b) {
+    As[(tid / KB) * SLD + tid % KB] = PAN ? conj(a[0]) : a[0];
+    As[(e1 / KB) * SLD + e1 % KB] = PAN ? conj(a[1]) : a[1];
+    Bs[PAN ? (tid / KB) * SLD + tid % KB : (tid % SK) * SLD + tid / SK] = b[0];
+    Bs[PAN ? (e1 / KB) * SLD + e1 % KB : (e1 % SK) * SLD + e1 / SK] = b[1];
   };
   Acc3 acc[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q].clear();
-  if (kbeg < kend) load(kbeg);
-  int buf = 0;
-  for (int k0 = kbeg; k0 < kend; k0 += SK) {
-    cd *As = sm[buf][0], *Bs = sm[buf][1];
+  if (kbeg < kend) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int e = tid + 256 * u;
-      As[(e / KB) * LD + e % KB] = pan ? conj(va[u]) : va[u];
-      if (pan)
-        Bs[(e / KB) * LD + e % KB] = vb[u];
-      else
-        Bs[(e % SK) * LD + e / SK] = vb[u];
+    for (int f = 0; f < PF; ++f) load(kbeg + f * SK, va[f], vb[f]);
+    for (int k0 = kbeg; k0 < kend; k0 += PF * SK) {
+#pragma unroll
+      for (int f = 0; f < PF; ++f) {
+        cd *As = sm[f & 1][0], *Bs = sm[f & 1][1];
+        store(As, Bs, va[f], vb[f]);
+        lds_barrier();
+        load(k0 + (f + PF) * SK, va[f], vb[f]);
+        // every LDS read of the step is issued before its first product
+        cd fa[SK / 4][4], fb[SK / 4];
+#pragma unroll
+        for (int kk = 0; kk < SK / 4; ++kk) {
+          fb[kk] = Bs[(4 * kk + lk) * SLD + 16 * wv + li];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) fa[kk][q] = As[(4 * kk + lk) * SLD + 16 * q + li];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < SK / 4; ++kk)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[q].step(fa[kk][q], fb[kk]);
+      }
     }
-    lds_barrier();
-    if (k0 + SK < kend) load(k0 + SK);
-#pragma unroll
-    for (int kk = 0; kk < SK; kk += 4) {
-      const cd b = Bs[(kk + lk) * LD + 16 * wv + li];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q].step(As[(kk + lk) * LD + 16 * q + li], b);
-    }
-    buf ^= 1;
   }
-  // pan: t[q][v] = (A_ij - sum)(row 16 wv + li, column 16 q + lk + 4 v);
+  // PAN: t[q][v] = (A_ij - sum)(row 16 wv + li, column 16 q + lk + 4 v);
   // else the sum itself (row 16 q + lk + 4 v, column 16 wv + li)
   cd t[4][4];
-  if (pan) {
+  if (PAN) {
     const int r = min(i0 + 16 * wv + li, n - 1);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -332,10 +366,11 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
   Acc3 up[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) up[q].clear();
-  cd *Ls = sm[0][0];   // 16 columns of L_ij, all 64 rows (16 x LD entries: both operands of a buffer)
+  cd *Ls = sm[0][0];   // 16 columns of L_ij, all 64 rows (both operands of a buffer)
   static_assert(2 * SK >= 16, "a 16-column tile fits one LDS buffer");
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) {
+    __builtin_amdgcn_sched_barrier(0);   // one block row of X_jj in registers at a time
     Acc3 o;
     o.clear();
 #pragma unroll
@@ -345,16 +380,16 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
         const int m = 16 * mb + li, k = 16 * kb + 4 * v + lk;
         const bool in = m < rows && k <= m;
         cd x = gld(X, in ? (size_t)(jb + k) * ld + jb + m : (size_t)jb * ld + jb);
-        x = in ? (pan ? conj(x) : x) : mk(0.0, 0.0);
+        x = in ? (PAN ? conj(x) : x) : mk(0.0, 0.0);
         o.step(x, t[kb][v]);
       }
-    if (pan) {
+    if (PAN) {
       cd ov[4];
       lds_barrier();   // the previous contents of Ls have been read
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         ov[v] = o.get(v);
-        Ls[(lk + 4 * v) * LD + 16 * wv + li] = ov[v];
+        Ls[(lk + 4 * v) * SLD + 16 * wv + li] = ov[v];
         if (i0 + 16 * wv + li < n) gst(A, (size_t)(jb + 16 * mb + lk + 4 * v) * ld + i0 + 16 * wv + li, ov[v]);
       }
       lds_barrier();
@@ -362,7 +397,7 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
       for (int rb = 0; rb < 4; ++rb)
         if (rb >= wv) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) up[rb].step(Ls[(4 * v + lk) * LD + 16 * rb + li], conj(ov[v]));
+          for (int v = 0; v < 4; ++v) up[rb].step(Ls[(4 * v + lk) * SLD + 16 * rb + li], conj(ov[v]));
         }
     } else {
 #pragma unroll
@@ -372,7 +407,7 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
       }
     }
   }
-  if (!pan) return;
+  if (!PAN) return;
   // A_ii -= L_ij L_ij^H, lower triangle
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
@@ -383,6 +418,26 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
         if (r < n && c <= r) gst(A, (size_t)c * ld + r, gld(A, (size_t)c * ld + r) - up[rb].get(v));
       }
     }
+}
+
+// Blocks per part of the inverse factor (the parts of an item: see kry_forward).
+MVPB_HD int kry_part_blocks(int n, int parts) { return ((n + KB - 1) / KB + parts - 1) / parts; }
+
+__global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restrict__ items, int n_items, int S, int jb,
+                                                        int parts) {
+  __shared__ cd sm[2][2][SK * SLD];   // [buffer][A, B][k][row or column]
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n;
+  if (jb >= n || gld(it.status, 0)) return;
+  const int j = jb / KB, below = (n + KB - 1) / KB - 1 - j;
+  const int pb = kry_part_blocks(n, parts), j0 = j / pb * pb;   // first block of j's part
+  if (slot >= below + j - j0) return;
+  if (slot < below)
+    chol_tile<true>(it, jb, jb + KB * (slot + 1), 0, sm);
+  else
+    chol_tile<false>(it, jb, 0, KB * (j0 + slot - below), sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -402,141 +457,204 @@ MVPB_DEV double kry_random(unsigned a, unsigned b) {
 
 MVPB_HD int kry_chunks(int n) { return (n + KCH - 1) / KCH; }
 
-// W = L^-1 Q_j with Q_j = Z R_j^-1 (written here as well), rows 32 rb ..
-// 32 rb + 31 by one workgroup, the columns of L^-1 split over its four
-// wavefronts; as W^T = (R^-T) (Z^T L^-T), so that the sums over the wavefronts
-// are the operand of the product with R^-1.  The workgroup of row block 0
-// writes -R_j below the diagonal of the projection (eigenvalues of -B, lowest
-// first).  Bound by reading the inverse factor once.
-__global__ void __launch_bounds__(256) kry_apply_l(const KryItem *__restrict__ items, int n_items, int S, int j) {
+// Entry e of G = Z^H Z: the chunks' parts, eight loads in flight, added in order.
+MVPB_DEV cd kry_gram(const KryItem &it, int e) {
+  const int nch = kry_chunks(it.n);
+  cd g = mk(0.0, 0.0);
+  for (int c0 = 0; c0 < nch; c0 += 8) {
+    cd p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] = gld(it.G, (size_t)min(c0 + u, nch - 1) * 256 + e);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (c0 + u < nch) g = g + p[u];
+  }
+  return g;
+}
+
+// Q_j = Z R_j^-1 from the Gram matrix G = Z^H Z = R_j^H R_j, KCH rows per
+// workgroup (each factors G itself: a sixteen-step chain in one wavefront).  The
+// workgroup of the first rows writes -R_j below the diagonal of the projection
+// (eigenvalues of -B, lowest first).
+__global__ void __launch_bounds__(512, 4) kry_norm(const KryItem *__restrict__ items, int j) {
   __shared__ cd Gs[16 * 17], Ri[16 * 17];
-  __shared__ cd col[16], row[16];
-  __shared__ cd red[4][2][4][64];
+  __shared__ Factor16 fs;
   __shared__ int bad;
-  int item, slot;
-  if (!xcd_slot(S, n_items, item, slot)) return;
-  const KryItem it = items[item];
-  const int n = it.n, nrb = (n + KR - 1) / KR;
-  if (slot >= nrb || gld(it.status, 0)) return;
-  const int rb = nrb - 1 - slot, r0 = KR * rb;   // longest rows first
-  const size_t ld = (size_t)n;
+  const KryItem it = items[blockIdx.y];
+  const int n = it.n, r0 = KCH * blockIdx.x;
+  if (r0 >= n || gld(it.status, 0)) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
-  {
-    cd g = mk(0.0, 0.0);
-    const int nch = kry_chunks(n);
-    for (int c = 0; c < nch; ++c) g = g + gld(it.G, (size_t)c * 256 + tid);
-    Gs[(tid >> 4) * 17 + (tid & 15)] = g;
+  const size_t r = (size_t)(r0 + 16 * wv + li);
+  cd z[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) z[v] = gld(it.Z, r * KS + 4 * v + lk);
+  if (tid < 256) {
+    Gs[(tid >> 4) * 17 + (tid & 15)] = kry_gram(it, tid);
     if (tid == 0) bad = 0;
   }
   __syncthreads();
   if (wv == 0) {
-    const bool ok = factor16<17>(Gs, Ri, col, row);
+    const bool ok = factor16<17>(Gs, Ri, fs);
     if (!ok && lane == 0) bad = 1;
   }
-  const cd *__restrict__ Z = it.Z;
-  const cd *__restrict__ X = it.Xi;
-  const int kend = min(n, r0 + KR);
-  const int ra = min(r0 + li, n - 1), rc = min(r0 + 16 + li, n - 1);
-  Acc3 acc[2];
-  acc[0].clear();
-  acc[1].clear();
-  for (int kg = 16 * wv; kg < kend; kg += 64) {
-    cd a[4], b0[4], b1[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = kg + 4 * q + lk;
-      const size_t kc = (size_t)min(k, n - 1) * ld;   // Z has zero rows there
-      a[q] = gld(Z, (size_t)k * KS + li);
-      b0[q] = gld(X, kc + ra);
-      b1[q] = gld(X, kc + rc);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[0].step(a[q], b0[q]);
-      acc[1].step(a[q], b1[q]);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) red[wv][t][v][lane] = acc[t].get(v);
   __syncthreads();
   if (bad) {
     if (tid == 0) gst(it.status, 0, 2);
     return;
   }
-  const int t = wv & 1;
-  const size_t r = (size_t)(r0 + 16 * t + li);
-  cd s[4];
-  if (wv < 2) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      s[v] = (red[0][t][v][lane] + red[1][t][v][lane]) + (red[2][t][v][lane] + red[3][t][v][lane]);
-  } else {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) s[v] = gld(Z, r * KS + 4 * v + lk);
-  }
   Acc3 o;
   o.clear();
 #pragma unroll
-  for (int v = 0; v < 4; ++v) o.step(conj(Ri[li * 17 + 4 * v + lk]), s[v]);
-  cd *dst = wv < 2 ? it.W : it.Q + (size_t)j * it.npad * KS;
-  if ((int)r < n) {
+  for (int v = 0; v < 4; ++v) o.step(conj(Ri[li * 17 + 4 * v + lk]), z[v]);
+  cd *Q = it.Q + (size_t)j * it.npad * KS;   // zero rows beyond n, as in Z
 #pragma unroll
-    for (int v = 0; v < 4; ++v) gst(dst, r * KS + lk + 4 * v, o.get(v));
-  }
-  if (rb == 0 && j > 0) {
+  for (int v = 0; v < 4; ++v) gst(Q, r * KS + lk + 4 * v, o.get(v));
+  if (blockIdx.x == 0 && j > 0 && tid < 256) {
     const int tr = tid & 15, tc = tid >> 4;   // -R(tr, tc) = -conj(L(tc, tr))
     gst(it.T, (size_t)(KS * (j - 1) + tc) * it.m + KS * j + tr, tr <= tc ? -conj(Gs[tc * 17 + tr]) : mk(0.0, 0.0));
   }
 }
 
-// Z = L^-H W, rows 32 rb .. 32 rb + 31 by one workgroup (a lane takes two
-// consecutive rows of the inverse factor's columns, so that a wavefront reads
-// whole 128-byte lines).
-__global__ void __launch_bounds__(256) kry_apply_lh(const KryItem *__restrict__ items, int n_items, int S) {
-  __shared__ cd red[4][2][4][64];
-  int item, slot;
-  if (!xcd_slot(S, n_items, item, slot)) return;
-  const KryItem it = items[item];
-  const int n = it.n, r0 = KR * slot;
-  if (r0 >= n || gld(it.status, 0)) return;
-  const size_t ld = (size_t)n;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
-  const cd *__restrict__ W = it.W;
-  const cd *__restrict__ X = it.Xi;
-  const size_t ca = (size_t)min(r0 + li, n - 1) * ld, cb = (size_t)min(r0 + 16 + li, n - 1) * ld;
-  Acc3 acc[2];
+// The two solves of B = L^-H L^-1, in `parts` parts of the rows: L^-1 is at hand
+// only within each part (a whole inverse costs as much again as the
+// factorisation, one of p parts 1 / p^2 of that), so the forward solve runs
+//   W_0 = X_00 Q_0;   Z_I = Q_I - L_I,<I W_<I (SUB),  W_I = X_II Z_I
+// and the backward one
+//   Z_p = X_pp^H W_p;   W_I -= L_>I,I^H Z_>I (SUB),   Z_I = X_II^H W_I.
+// 32 rows (or columns of the factor) by 16 per workgroup, the depth dealt to its
+// four wavefronts 16 at a time, the operands of the next 16 in flight during the
+// products; computed transposed (D^T = V^T M^T), so that a lane's loads of the
+// factor run down its columns, 256 bytes (forward) or, with two consecutive rows
+// per lane, 128 bytes (backward) at a time.  Bound by reading the factor and the
+// parts of its inverse once.
+struct KrySum {
+  cd red[4][2][4][64];
+};
+template <typename L>
+MVPB_DEV void kry_depth(int klo, int khi, const L &load, Acc3 (&acc)[2]) {
+  const int wv = threadIdx.x >> 6, last = klo + (khi - klo - 1) / 16 * 16;
   acc[0].clear();
   acc[1].clear();
-  for (int kg = r0 + 16 * wv; kg < n; kg += 64) {
-    cd a[4], b0[4], b1[4];
+  int kg = klo + 16 * wv;
+  if (kg >= khi) return;
+  cd a0[4], b0[4], c0[4], a1[4], b1[4], c1[4];
+  load(kg, a0, b0, c0);
+  for (; kg < khi; kg += 128) {
+    load(min(kg + 64, last), a1, b1, c1);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int k = kg + 8 * (q >> 1) + 2 * lk + (q & 1), kc = min(k, n - 1);   // W has zero rows beyond n
-      a[q] = gld(W, (size_t)k * KS + li);
-      b0[q] = gld(X, ca + kc);
-      b1[q] = gld(X, cb + kc);
+      acc[0].step(a0[q], b0[q]);
+      acc[1].step(a0[q], c0[q]);
     }
+    load(min(kg + 128, last), a0, b0, c0);
+    if (kg + 64 < khi) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[0].step(a[q], conj(b0[q]));
-      acc[1].step(a[q], conj(b1[q]));
+      for (int q = 0; q < 4; ++q) {
+        acc[0].step(a1[q], b1[q]);
+        acc[1].step(a1[q], c1[q]);
+      }
     }
   }
+}
+// Sum over the wavefronts: wavefront w receives registers 2 (w / 2) + h of tile w % 2.
+MVPB_DEV void kry_sum(KrySum &sm, const Acc3 (&acc)[2], cd (&out)[2]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) red[wv][t][v][lane] = acc[t].get(v);
+    for (int v = 0; v < 4; ++v) sm.red[wv][t][v][lane] = acc[t].get(v);
   __syncthreads();
-  // wavefront w sums registers 2 (w / 2), 2 (w / 2) + 1 of tile w % 2
-  const int t = wv & 1, r = r0 + 16 * t + li;
+  const int t = wv & 1;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int v = 2 * (wv >> 1) + h;
+    out[h] = (sm.red[0][t][v][lane] + sm.red[1][t][v][lane]) + (sm.red[2][t][v][lane] + sm.red[3][t][v][lane]);
+  }
+}
+
+template <bool SUB>
+__global__ void __launch_bounds__(256, 2) kry_forward(const KryItem *__restrict__ items, int n_items, int S, int part,
+                                                      int parts, int j) {
+  __shared__ KrySum sm;
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n, w = KB * kry_part_blocks(n, parts), start = w * part, end = min(start + w, n);
+  const int nrb = (end - start + KR - 1) / KR;   // <= 0: the item has fewer parts
+  if (slot >= nrb || gld(it.status, 0)) return;
+  const int r0 = start + KR * (nrb - 1 - slot);   // longest rows first
+  const size_t ld = (size_t)n;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const cd *Q = it.Q + (size_t)j * it.npad * KS;
+  const cd *__restrict__ M = SUB ? it.A : it.Xi;
+  const cd *__restrict__ V = SUB ? it.W : (part == 0 ? Q : it.Z);
+  const int ra = min(r0 + li, n - 1), rc = min(r0 + 16 + li, n - 1);
+  Acc3 acc[2];
+  kry_depth(SUB ? 0 : start, SUB ? start : min(r0 + KR, end),
+            [&](int kg, cd *a, cd *b, cd *c) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const int k = kg + 4 * q + lk;
+                const size_t kc = (size_t)min(k, n - 1) * ld;   // V has zero rows beyond n
+                a[q] = gld(V, (size_t)k * KS + li);
+                b[q] = gld(M, kc + ra);
+                c[q] = gld(M, kc + rc);
+              }
+            },
+            acc);
+  cd s[2];
+  kry_sum(sm, acc, s);
+  const int r = r0 + 16 * (wv & 1) + li;
   if (r < n) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int v = 2 * (wv >> 1) + h;
-      gst(it.Z, (size_t)r * KS + lk + 4 * v,
-          (red[0][t][v][lane] + red[1][t][v][lane]) + (red[2][t][v][lane] + red[3][t][v][lane]));
+      const size_t e = (size_t)r * KS + lk + 4 * (2 * (wv >> 1) + h);
+      if (SUB)
+        gst(it.Z, e, gld(Q, e) - s[h]);
+      else
+        gst(it.W, e, s[h]);
+    }
+  }
+}
+
+template <bool SUB>
+__global__ void __launch_bounds__(256, 2) kry_backward(const KryItem *__restrict__ items, int n_items, int S, int part,
+                                                       int parts) {
+  __shared__ KrySum sm;
+  int item, slot;
+  if (!xcd_slot(S, n_items, item, slot)) return;
+  const KryItem it = items[item];
+  const int n = it.n, w = KB * kry_part_blocks(n, parts), start = w * part, end = min(start + w, n);
+  const int r0 = start + KR * slot;
+  if (r0 >= end || (SUB && end >= n) || gld(it.status, 0)) return;
+  const size_t ld = (size_t)n;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  const cd *__restrict__ M = SUB ? it.A : it.Xi;
+  const cd *__restrict__ V = SUB ? it.Z : it.W;
+  const size_t ca = (size_t)min(r0 + li, n - 1) * ld, cb = (size_t)min(r0 + 16 + li, n - 1) * ld;
+  Acc3 acc[2];
+  kry_depth(SUB ? end : r0, SUB ? n : end,
+            [&](int kg, cd *a, cd *b, cd *c) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const int k = kg + 8 * (q >> 1) + 2 * lk + (q & 1), kc = min(k, n - 1);   // V: zero rows beyond n
+                a[q] = gld(V, (size_t)k * KS + li);
+                b[q] = conj(gld(M, ca + kc));
+                c[q] = conj(gld(M, cb + kc));
+              }
+            },
+            acc);
+  cd s[2];
+  kry_sum(sm, acc, s);
+  const int r = r0 + 16 * (wv & 1) + li;
+  if (r < n) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const size_t e = (size_t)r * KS + lk + 4 * (2 * (wv >> 1) + h);
+      if (SUB)
+        gst(it.W, e, gld(it.W, e) - s[h]);
+      else
+        gst(it.Z, e, s[h]);
     }
   }
 }
@@ -688,11 +806,8 @@ __global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ item
   const KryItem it = items[blockIdx.x];
   const int lane = threadIdx.x, nb = it.nb, m = it.m;
   int bad = gld(it.status, 0) | gld(it.flag_s, 0);
-  const int nch = kry_chunks(it.n);
   for (int e = lane; e < 256; e += 64) {
-    cd g = mk(0.0, 0.0);
-    for (int c = 0; c < nch; ++c) g = g + gld(it.G, (size_t)c * 256 + e);
-    Gs[e] = g;
+    Gs[e] = kry_gram(it, e);
   }
   __syncthreads();
   if (!bad)
@@ -728,25 +843,48 @@ int krylov_steps(int nb, int dim, bool modes) {
   return 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0) + (modes ? 2 + nb / 12 : 0);
 }
 
-hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st) {
+// Parts of the inverse factor: the time of the whole inverse (a third of n^3
+// multiply-adds per item at the rate of kry_chol_step, 50 TFLOP/s counting four
+// real products per complex one) falls with the square of the parts, and every
+// part adds four launches to a Krylov step (about 7 us each, with the tail of a
+// launch).  At 60 items of n = 882: 1 part 11.4 ms, 2 parts (chosen) 10.6; of
+// n = 1922: 1 part 52.1, 4 parts (chosen) 41.8 ms per call.
+static int krylov_parts(double n3_sum, int n_max, int s) {
+  const double inv = 8.0 / 6.0 * n3_sum / 50e12, step = 4.0 * 7e-6 * s;
+  int best = 1;
+  for (int p = 2; p <= 8 && p * 2 * KB <= n_max; ++p)
+    if (inv / (p * p) + (p - 1) * step < inv / (best * best) + (best - 1) * step) best = p;
+  return best;
+}
+
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, double n3_sum, int s, hipStream_t st) {
+  const int nblk = (n_max + KB - 1) / KB, parts = krylov_parts(n3_sum, n_max, s);
   {
     ProfScope ps(K_FACTOR, st);
-    hipLaunchKernelGGL(kry_shift, dim3(n_items), dim3(256), 0, st, items);
-    const int nblk = (n_max + KB - 1) / KB;
+    hipLaunchKernelGGL(kry_shift, dim3(n_items), dim3(1024), 0, st, items);
     for (int j = 0; j < nblk; ++j) {
       hipLaunchKernelGGL(kry_chol_diag, dim3(n_items), dim3(256), 0, st, items, j * KB);
       if (nblk > 1)
         hipLaunchKernelGGL(kry_chol_step, dim3(xcd_grid(nblk - 1, n_items)), dim3(256), 0, st, items, n_items,
-                           nblk - 1, j * KB);
+                           nblk - 1, j * KB, parts);
     }
   }
   ProfScope ps(K_KRYLOV, st);
-  const int nch = kry_chunks(n_max), nrb = (n_max + KR - 1) / KR;
+  // rows of a part: items of fewer blocks have parts of at most as many
+  const int nch = kry_chunks(n_max), nrb = KB / KR * kry_part_blocks(n_max, parts);
   const size_t red = sizeof(cd) * 8 * 256;
+  const dim3 g(xcd_grid(nrb, n_items)), b(256);
   hipLaunchKernelGGL(kry_update<true>, dim3(nch, n_items), dim3(512), red, st, items, 0);
   for (int j = 0; j < s; ++j) {
-    hipLaunchKernelGGL(kry_apply_l, dim3(xcd_grid(nrb, n_items)), dim3(256), 0, st, items, n_items, nrb, j);
-    hipLaunchKernelGGL(kry_apply_lh, dim3(xcd_grid(nrb, n_items)), dim3(256), 0, st, items, n_items, nrb);
+    hipLaunchKernelGGL(kry_norm, dim3(nch, n_items), dim3(512), 0, st, items, j);
+    for (int p = 0; p < parts; ++p) {
+      if (p > 0) hipLaunchKernelGGL(kry_forward<true>, g, b, 0, st, items, n_items, nrb, p, parts, j);
+      hipLaunchKernelGGL(kry_forward<false>, g, b, 0, st, items, n_items, nrb, p, parts, j);
+    }
+    for (int p = parts - 1; p >= 0; --p) {
+      if (p < parts - 1) hipLaunchKernelGGL(kry_backward<true>, g, b, 0, st, items, n_items, nrb, p, parts);
+      hipLaunchKernelGGL(kry_backward<false>, g, b, 0, st, items, n_items, nrb, p, parts);
+    }
     hipLaunchKernelGGL(kry_project, dim3(j + 1, n_items), dim3(512), 0, st, items);
     hipLaunchKernelGGL(kry_update<false>, dim3(nch, n_items), dim3(512),
                        std::max(red, sizeof(cd) * 256 * (size_t)(j + 1)), st, items, j);

@@ -39,29 +39,6 @@ namespace mvpb {
 // n = 98), of which the FP64 issue of 12 FMAs per entry is the smaller part.
 constexpr int SQ = 4;   // threads per row
 
-// 1 / x: hardware reciprocal and two Newton steps.
-MVPB_DEV double quick_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-// sqrt(x) and its reciprocal: hardware reciprocal square root and two Newton
-// steps (a shorter chain than a square root and a division); the plain functions
-// where the products could leave the range of normal numbers.
-MVPB_DEV void sqrt_rcp(double x, double &s, double &rs) {
-  if (x > 1e-250 && x < 1e250) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    const double q = x * y;
-    s = fma(0.5 * y, fma(-q, q, x), q);
-    rs = y;
-  } else {
-    s = sqrt(x);
-    rs = 1.0 / s;
-  }
-}
-
 template <int ROWS>
 __global__ void __launch_bounds__(SQ * ROWS) small_tridiag(const EigItem *__restrict__ items) {
   constexpr int NE = ROWS / SQ, RW = ROWS / 64;
