@@ -1391,20 +1391,32 @@ struct Route {
 enum Attempt { TRY_KRYLOV = 0, TRY_LONGER, TRY_REDUCTION };
 constexpr int RETRY_STEPS = 4;
 
-// The Krylov route pays while its projection, of order m = HB steps, is small
-// against the operator: its chain of m sweeps and 4 steps launches against n
-// sweeps and n / 4 launches.  It is for FP64 solves that end with the
-// Rayleigh-Ritz step.  The bars: a frequency's error is about ten times the
-// residual's square (1e-13 at 1e-7, the rounding level of the solve), a mode's
-// is the residual over the relative gap.
-static Route krylov_route(int n_min, int nb, int dim, bool fp32, bool modes, Attempt at) {
+// The Krylov route pays while its projection, of order m = HB steps, is smaller
+// than the operator: its chain of m sweeps and 4 steps launches against n
+// sweeps and n / 4 launches.  Measured, one point and 30, Krylov against the
+// reduction, ms: n = 162, m / n = 0.79, 1.33 and 1.47 against 1.77 and 1.82;
+// n = 242, 0.79, 2.15 and 2.36 against 2.78 and 2.94; n = 450, 0.75, 4.96 and 5.86
+// against 6.38 and 6.75; the line at 0.85 leaves room for the basis among n
+// vectors, as a longer attempt has to.  The route is for FP64 solves that end with
+// the Rayleigh-Ritz step.  The bars: a frequency's error is about ten times the
+// residual's square (1e-13 at 1e-7, the rounding level of the solve), a mode's is
+// the residual over the relative gap.
+static Route krylov_route(int n, int nb, int dim, bool fp32, bool modes, Attempt at) {
   Route rt;
   if (fp32 || nb > RR_MAX_BANDS || at == TRY_REDUCTION) return rt;
-  const int s = krylov_steps(nb, dim, modes);
-  if (s + RETRY_STEPS > KRY_MAX_STEPS || 10 * HB * s > 7 * n_min) return rt;
-  rt.steps = at == TRY_LONGER ? s + RETRY_STEPS : s;
+  int s = krylov_steps(nb, dim, modes);
+  if (s + RETRY_STEPS > KRY_MAX_STEPS || 20 * HB * s > 17 * n) return rt;
+  if (at == TRY_LONGER && 10 * HB * (s += RETRY_STEPS) > 9 * n) return rt;
+  rt.steps = s;
   rt.tol = modes ? 1e-11 : 1e-7;
   return rt;
+}
+
+// What an operator of order n is solved by (0 and -1 the reductions, else the
+// Krylov steps): the operators of one launch sequence share it, so that a point
+// takes the same route alone and among others.
+static int route_class(int n, int nb, int dim, bool fp32, bool modes, Attempt at) {
+  return !fp32 && n <= SMALL_MAX_N ? -1 : krylov_route(n, nb, dim, fp32, modes, at).steps;
 }
 
 // Sizes of the per-item buffers of the Krylov route (the projection's own item
@@ -1710,9 +1722,7 @@ static hipError_t enqueue_eigensolve(mvpb_ctx ctx, const EigItem *d_items, const
     const EigItem *d_small = d_items + n_items;
     const KryItem *d_kry = reinterpret_cast<const KryItem *>(d_items + 2 * (size_t)n_items);
     const int m = HB * rt.steps;
-    double n3 = 0.0;
-    for (int n : orders) n3 += (double)n * n * n;
-    if (e == hipSuccess) e = launch_krylov(d_kry, n_items, n_max, n3, rt.steps, st);
+    if (e == hipSuccess) e = launch_krylov(d_kry, n_items, n_max, rt.steps, st);
     if (e == hipSuccess) e = launch_stage2(d_small, n_items, m, false, ctl, sh, st);
     if (e == hipSuccess) e = launch_tridiag_eig(d_small, n_items, m, nb, st, ctx->la[0], la_ev[0], la_ev[1]);
     if (e == hipSuccess) e = launch_backtransform(d_small, n_items, m, m, nb, false, st, false);
@@ -2113,8 +2123,8 @@ static bool q_ok(const double *Q, int count) {
 }
 
 // Run jobs (largest operators first) in chunks within the workspace budget:
-// items of one chunk stay within a factor ~1.5 in order, so that the launch
-// sequence sized for the largest wastes little on the rest.  *krylov: whether
+// items of one chunk take one route and stay within a factor ~1.5 in order, so
+// that the launch sequence sized for the largest wastes little on the rest.  *krylov: whether
 // any chunk took the Krylov route.
 static int run_sorted(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double *om, double *U, size_t budget,
                       bool use_graph, Attempt at, bool *krylov) {
@@ -2124,13 +2134,10 @@ static int run_sorted(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double
   for (size_t j0 = 0, j1 = 0; j0 < jobs.size(); j0 = j1) {
     const int n0 = jobs[j0].plan->n;
     size_t end = j0;
-    int dim = 0, n_min = n0;
-    while (end < jobs.size() && 3 * jobs[end].plan->n >= 2 * n0) {
-      dim = std::max(dim, jobs[end].plan->dim);
-      n_min = std::min(n_min, jobs[end].plan->n);
-      ++end;
-    }
-    Route rt = krylov_route(n_min, nb, dim, fp32, U != nullptr, at);
+    auto cls = [&](const Job &j) { return route_class(j.plan->n, nb, j.plan->dim, fp32, U != nullptr, at); };
+    const int c0 = cls(jobs[j0]);
+    while (end < jobs.size() && 3 * jobs[end].plan->n >= 2 * n0 && cls(jobs[end]) == c0) ++end;
+    Route rt = krylov_route(n0, nb, jobs[j0].plan->dim, fp32, U != nullptr, at);
     if (solve_bytes(1, route_item_bytes(n0, nb, fp32, rt)) > budget) rt = Route{};
     *krylov = *krylov || rt.steps > 0;
     size_t bytes = 0;
@@ -2423,8 +2430,9 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   for (size_t j0 = 0; j0 < jobs.size();) {
     const int n0 = order_of(jobs[j0]);
     size_t j1 = j0, bytes = 0;
-    while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0) ++j1;
-    Route rt = krylov_route(order_of(jobs[j1 - 1]), n_bands, 0, fp32, false, TRY_KRYLOV);
+    auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, fp32, false, TRY_KRYLOV); };
+    while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
+    Route rt = krylov_route(n0, n_bands, 0, fp32, false, TRY_KRYLOV);
     if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > budget) rt = Route{};
     const size_t end = j1;
     for (j1 = j0; j1 < end; ++j1) {

@@ -240,8 +240,7 @@ hipError_t init_krylov_attributes();
 // Krylov steps of a solve for nb bands (dim: coefficient layout, see EigItem).
 int krylov_steps(int nb, int dim, bool modes);
 // C(k) + sigma I factored, s block steps, projection of order HB s.
-// n3_sum: sum of the items' cubed orders.
-hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, double n3_sum, int s, hipStream_t st);
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st);
 // Ritz vectors from the projection's eigenpairs; items whose residuals exceed
 // tol times their value are flagged.
 hipError_t launch_krylov_ritz(const KryItem *items, int n_items, int n_max, int nb, int s, double tol,

@@ -21,8 +21,8 @@
 // grow like a power of the frequency), and every item checks it: an item that
 // misses the bar is solved again, with more steps or by the reduction.
 // Measured, plan build included, against the reduction: 60 points of 2N = 882,
-// 18 bands, 20.4 -> 12.0 ms; 60 points of 2N = 1922, 24 bands, 123.9 -> 57.1 ms;
-// 960 points of 2N = 242 .. 1250, 10 bands, 228 -> 116 ms.
+// 18 bands, 20.4 -> 10.8 ms; 60 points of 2N = 1922, 24 bands, 123.6 -> 45.7 ms;
+// 960 points of 2N = 242 .. 1250, 10 bands, 229 -> 95.6 ms.
 #include <float.h>
 
 #include <algorithm>
@@ -37,7 +37,9 @@ typedef double zd4_t __attribute__((ext_vector_type(4)));
 
 constexpr int KB = 64;        // block of the factorisation
 constexpr int KS = HB;        // vectors of a Krylov block
-constexpr int KR = 32;        // rows of the factor per workgroup of a product
+constexpr int KPB = 9;        // most blocks of a part of the inverse factor
+constexpr int KT = 1;         // 16-row tiles of the factor per workgroup of a product
+constexpr int KR = 16 * KT;
 constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonalisation
 // Shift as a fraction of the nb-th smallest diagonal entry d_nb of C (which
 // overestimates the nb-th eigenvalue, by 2 to 10 and more where the phases
@@ -71,7 +73,7 @@ struct Acc3 {
 // L D L^H: the update then needs no selects, and the scalings by the square roots
 // of the pivots wait until the end.  One wavefront issues an instruction every
 // four to five cycles, so the instructions of a step are its time (with selects
-// and scalings in the step 1000 cycles, without 400).  Reads the lower triangle
+// and scalings in the step 1016 cycles, without 660).  Reads the lower triangle
 // of D; writes L and L^-1 with zero upper triangles.  False (uniform) if a pivot
 // is not positive.
 // ---------------------------------------------------------------------------
@@ -239,6 +241,7 @@ __global__ void __launch_bounds__(256) kry_chol_diag(const KryItem *__restrict__
       Acc3 s, o;
       s.clear();
       o.clear();
+#pragma unroll 4
       for (int k = c0; k < p0; k += 4) s.step(D[(p0 + li) * LD + k + lk], I[(k + lk) * LD + c0 + li]);
 #pragma unroll
       for (int v = 0; v < 4; ++v) o.step(I[(p0 + li) * LD + p0 + 4 * v + lk], s.get(v));
@@ -420,11 +423,17 @@ MVPB_DEV void chol_tile(const KryItem &it, int jb, int i0, int c0, cd (&sm)[2][2
     }
 }
 
-// Blocks per part of the inverse factor (the parts of an item: see kry_forward).
-MVPB_HD int kry_part_blocks(int n, int parts) { return ((n + KB - 1) / KB + parts - 1) / parts; }
+// Parts of the inverse factor of an operator of order n (see kry_forward) and the
+// blocks of one.  By the order alone, so that a point's result does not depend on
+// the points solved with it.  A part saves most of its blocks' inverse and costs
+// four launches per Krylov step (about 7 us each).  60 points of n = 882, 18
+// bands, in 2 parts of 7 blocks (chosen) 10.7 ms, in 3 of 5 10.9, whole 11.35; of
+// n = 1922, 24 bands, in 4 of 8 (chosen) 45.7, in 6 of 6 46.3, whole 52.1; 30
+// points of a spatial n = 1029 in 2 of 9 (chosen) 19.2, in 3 of 6 20.1, whole 19.1.
+MVPB_HD int kry_parts(int n) { return ((n + KB - 1) / KB + KPB - 1) / KPB; }
+MVPB_HD int kry_part_blocks(int n) { return ((n + KB - 1) / KB + kry_parts(n) - 1) / kry_parts(n); }
 
-__global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restrict__ items, int n_items, int S, int jb,
-                                                        int parts) {
+__global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restrict__ items, int n_items, int S, int jb) {
   __shared__ cd sm[2][2][SK * SLD];   // [buffer][A, B][k][row or column]
   int item, slot;
   if (!xcd_slot(S, n_items, item, slot)) return;
@@ -432,7 +441,7 @@ __global__ void __launch_bounds__(256, 2) kry_chol_step(const KryItem *__restric
   const int n = it.n;
   if (jb >= n || gld(it.status, 0)) return;
   const int j = jb / KB, below = (n + KB - 1) / KB - 1 - j;
-  const int pb = kry_part_blocks(n, parts), j0 = j / pb * pb;   // first block of j's part
+  const int pb = kry_part_blocks(n), j0 = j / pb * pb;   // first block of j's part
   if (slot >= below + j - j0) return;
   if (slot < below)
     chol_tile<true>(it, jb, jb + KB * (slot + 1), 0, sm);
@@ -515,7 +524,7 @@ __global__ void __launch_bounds__(512, 4) kry_norm(const KryItem *__restrict__ i
   }
 }
 
-// The two solves of B = L^-H L^-1, in `parts` parts of the rows: L^-1 is at hand
+// The two solves of B = L^-H L^-1, in kry_parts parts of the rows: L^-1 is at hand
 // only within each part (a whole inverse costs as much again as the
 // factorisation, one of p parts 1 / p^2 of that), so the forward solve runs
 //   W_0 = X_00 Q_0;   Z_I = Q_I - L_I,<I W_<I (SUB),  W_I = X_II Z_I
@@ -528,58 +537,59 @@ __global__ void __launch_bounds__(512, 4) kry_norm(const KryItem *__restrict__ i
 // per lane, 128 bytes (backward) at a time.  Bound by reading the factor and the
 // parts of its inverse once.
 struct KrySum {
-  cd red[4][2][4][64];
+  cd red[4][KT][4][64];
 };
+// acc += the depth [klo, khi) dealt to this wavefront; load(kg, a, b) fetches the
+// 16 deep from kg: a[q] of V, b[t][q] of tile t of the factor.
 template <typename L>
-MVPB_DEV void kry_depth(int klo, int khi, const L &load, Acc3 (&acc)[2]) {
+MVPB_DEV void kry_depth(int klo, int khi, const L &load, Acc3 (&acc)[KT]) {
   const int wv = threadIdx.x >> 6, last = klo + (khi - klo - 1) / 16 * 16;
-  acc[0].clear();
-  acc[1].clear();
+#pragma unroll
+  for (int t = 0; t < KT; ++t) acc[t].clear();
   int kg = klo + 16 * wv;
   if (kg >= khi) return;
-  cd a0[4], b0[4], c0[4], a1[4], b1[4], c1[4];
-  load(kg, a0, b0, c0);
+  cd a0[4], a1[4], b0[KT][4], b1[KT][4];
+  load(kg, a0, b0);
   for (; kg < khi; kg += 128) {
-    load(min(kg + 64, last), a1, b1, c1);
+    load(min(kg + 64, last), a1, b1);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[0].step(a0[q], b0[q]);
-      acc[1].step(a0[q], c0[q]);
-    }
-    load(min(kg + 128, last), a0, b0, c0);
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < KT; ++t) acc[t].step(a0[q], b0[t][q]);
+    load(min(kg + 128, last), a0, b0);
     if (kg + 64 < khi) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc[0].step(a1[q], b1[q]);
-        acc[1].step(a1[q], c1[q]);
-      }
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < KT; ++t) acc[t].step(a1[q], b1[t][q]);
     }
   }
 }
-// Sum over the wavefronts: wavefront w receives registers 2 (w / 2) + h of tile w % 2.
-MVPB_DEV void kry_sum(KrySum &sm, const Acc3 (&acc)[2], cd (&out)[2]) {
+// Sum over the wavefronts: wavefront w receives KT of the 4 KT registers:
+// register v = KT w' + h of tile w % KT, w' = w / KT.
+MVPB_DEV void kry_sum(KrySum &sm, const Acc3 (&acc)[KT], cd (&out)[KT]) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < KT; ++t)
 #pragma unroll
     for (int v = 0; v < 4; ++v) sm.red[wv][t][v][lane] = acc[t].get(v);
   __syncthreads();
-  const int t = wv & 1;
+  const int t = wv % KT;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int v = 2 * (wv >> 1) + h;
+  for (int h = 0; h < KT; ++h) {
+    const int v = KT * (wv / KT) + h;
     out[h] = (sm.red[0][t][v][lane] + sm.red[1][t][v][lane]) + (sm.red[2][t][v][lane] + sm.red[3][t][v][lane]);
   }
 }
 
 template <bool SUB>
-__global__ void __launch_bounds__(256, 2) kry_forward(const KryItem *__restrict__ items, int n_items, int S, int part,
-                                                      int parts, int j) {
+__global__ void __launch_bounds__(256) kry_forward(const KryItem *__restrict__ items, int n_items, int S, int part,
+                                                   int j) {
   __shared__ KrySum sm;
   int item, slot;
   if (!xcd_slot(S, n_items, item, slot)) return;
   const KryItem it = items[item];
-  const int n = it.n, w = KB * kry_part_blocks(n, parts), start = w * part, end = min(start + w, n);
+  const int n = it.n, w = KB * kry_part_blocks(n), start = w * part, end = min(start + w, n);
   const int nrb = (end - start + KR - 1) / KR;   // <= 0: the item has fewer parts
   if (slot >= nrb || gld(it.status, 0)) return;
   const int r0 = start + KR * (nrb - 1 - slot);   // longest rows first
@@ -588,27 +598,26 @@ __global__ void __launch_bounds__(256, 2) kry_forward(const KryItem *__restrict_
   const cd *Q = it.Q + (size_t)j * it.npad * KS;
   const cd *__restrict__ M = SUB ? it.A : it.Xi;
   const cd *__restrict__ V = SUB ? it.W : (part == 0 ? Q : it.Z);
-  const int ra = min(r0 + li, n - 1), rc = min(r0 + 16 + li, n - 1);
-  Acc3 acc[2];
+  Acc3 acc[KT];
   kry_depth(SUB ? 0 : start, SUB ? start : min(r0 + KR, end),
-            [&](int kg, cd *a, cd *b, cd *c) {
+            [&](int kg, cd (&a)[4], cd (&b)[KT][4]) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const int k = kg + 4 * q + lk;
                 const size_t kc = (size_t)min(k, n - 1) * ld;   // V has zero rows beyond n
                 a[q] = gld(V, (size_t)k * KS + li);
-                b[q] = gld(M, kc + ra);
-                c[q] = gld(M, kc + rc);
+#pragma unroll
+                for (int t = 0; t < KT; ++t) b[t][q] = gld(M, kc + min(r0 + 16 * t + li, n - 1));
               }
             },
             acc);
-  cd s[2];
+  cd s[KT];
   kry_sum(sm, acc, s);
-  const int r = r0 + 16 * (wv & 1) + li;
+  const int r = r0 + 16 * (wv % KT) + li;
   if (r < n) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const size_t e = (size_t)r * KS + lk + 4 * (2 * (wv >> 1) + h);
+    for (int h = 0; h < KT; ++h) {
+      const size_t e = (size_t)r * KS + lk + 4 * (KT * (wv / KT) + h);
       if (SUB)
         gst(it.Z, e, gld(Q, e) - s[h]);
       else
@@ -618,39 +627,37 @@ __global__ void __launch_bounds__(256, 2) kry_forward(const KryItem *__restrict_
 }
 
 template <bool SUB>
-__global__ void __launch_bounds__(256, 2) kry_backward(const KryItem *__restrict__ items, int n_items, int S, int part,
-                                                       int parts) {
+__global__ void __launch_bounds__(256) kry_backward(const KryItem *__restrict__ items, int n_items, int S, int part) {
   __shared__ KrySum sm;
   int item, slot;
   if (!xcd_slot(S, n_items, item, slot)) return;
   const KryItem it = items[item];
-  const int n = it.n, w = KB * kry_part_blocks(n, parts), start = w * part, end = min(start + w, n);
+  const int n = it.n, w = KB * kry_part_blocks(n), start = w * part, end = min(start + w, n);
   const int r0 = start + KR * slot;
   if (r0 >= end || (SUB && end >= n) || gld(it.status, 0)) return;
   const size_t ld = (size_t)n;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
   const cd *__restrict__ M = SUB ? it.A : it.Xi;
   const cd *__restrict__ V = SUB ? it.Z : it.W;
-  const size_t ca = (size_t)min(r0 + li, n - 1) * ld, cb = (size_t)min(r0 + 16 + li, n - 1) * ld;
-  Acc3 acc[2];
+  Acc3 acc[KT];
   kry_depth(SUB ? end : r0, SUB ? n : end,
-            [&](int kg, cd *a, cd *b, cd *c) {
+            [&](int kg, cd (&a)[4], cd (&b)[KT][4]) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const int k = kg + 8 * (q >> 1) + 2 * lk + (q & 1), kc = min(k, n - 1);   // V: zero rows beyond n
                 a[q] = gld(V, (size_t)k * KS + li);
-                b[q] = conj(gld(M, ca + kc));
-                c[q] = conj(gld(M, cb + kc));
+#pragma unroll
+                for (int t = 0; t < KT; ++t) b[t][q] = conj(gld(M, (size_t)min(r0 + 16 * t + li, n - 1) * ld + kc));
               }
             },
             acc);
-  cd s[2];
+  cd s[KT];
   kry_sum(sm, acc, s);
-  const int r = r0 + 16 * (wv & 1) + li;
+  const int r = r0 + 16 * (wv % KT) + li;
   if (r < n) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const size_t e = (size_t)r * KS + lk + 4 * (2 * (wv >> 1) + h);
+    for (int h = 0; h < KT; ++h) {
+      const size_t e = (size_t)r * KS + lk + 4 * (KT * (wv / KT) + h);
       if (SUB)
         gst(it.W, e, gld(it.W, e) - s[h]);
       else
@@ -660,12 +667,16 @@ __global__ void __launch_bounds__(256, 2) kry_backward(const KryItem *__restrict
 }
 
 // P_i = Q_i^H Z of one basis block i <= j: one workgroup per (block, item), the
-// rows over its eight wavefronts.
-__global__ void __launch_bounds__(512) kry_project(const KryItem *__restrict__ items) {
+// rows over its eight wavefronts; the workgroups of an item on one XCD, so that Z
+// is fetched into one L2 (it is read once per basis block).  Bound by reading the
+// basis.
+__global__ void __launch_bounds__(512) kry_project(const KryItem *__restrict__ items, int n_items, int j) {
   __shared__ cd red[8][4][64];
-  const KryItem it = items[blockIdx.y];
+  int item, i;
+  if (!xcd_slot(j + 1, n_items, item, i)) return;
+  const KryItem it = items[item];
   if (gld(it.status, 0)) return;
-  const int n = it.n, i = blockIdx.x;
+  const int n = it.n;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
   const cd *__restrict__ Q = it.Q + (size_t)i * it.npad * KS;
   const cd *__restrict__ Z = it.Z;
@@ -843,22 +854,8 @@ int krylov_steps(int nb, int dim, bool modes) {
   return 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0) + (modes ? 2 + nb / 12 : 0);
 }
 
-// Parts of the inverse factor: the time of the whole inverse (a third of n^3
-// multiply-adds per item at the rate of kry_chol_step, 50 TFLOP/s counting four
-// real products per complex one) falls with the square of the parts, and every
-// part adds four launches to a Krylov step (about 7 us each, with the tail of a
-// launch).  At 60 items of n = 882: 1 part 11.4 ms, 2 parts (chosen) 10.6; of
-// n = 1922: 1 part 52.1, 4 parts (chosen) 41.8 ms per call.
-static int krylov_parts(double n3_sum, int n_max, int s) {
-  const double inv = 8.0 / 6.0 * n3_sum / 50e12, step = 4.0 * 7e-6 * s;
-  int best = 1;
-  for (int p = 2; p <= 8 && p * 2 * KB <= n_max; ++p)
-    if (inv / (p * p) + (p - 1) * step < inv / (best * best) + (best - 1) * step) best = p;
-  return best;
-}
-
-hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, double n3_sum, int s, hipStream_t st) {
-  const int nblk = (n_max + KB - 1) / KB, parts = krylov_parts(n3_sum, n_max, s);
+hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st) {
+  const int nblk = (n_max + KB - 1) / KB, parts = kry_parts(n_max);
   {
     ProfScope ps(K_FACTOR, st);
     hipLaunchKernelGGL(kry_shift, dim3(n_items), dim3(1024), 0, st, items);
@@ -866,26 +863,25 @@ hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, double n3
       hipLaunchKernelGGL(kry_chol_diag, dim3(n_items), dim3(256), 0, st, items, j * KB);
       if (nblk > 1)
         hipLaunchKernelGGL(kry_chol_step, dim3(xcd_grid(nblk - 1, n_items)), dim3(256), 0, st, items, n_items,
-                           nblk - 1, j * KB, parts);
+                           nblk - 1, j * KB);
     }
   }
   ProfScope ps(K_KRYLOV, st);
-  // rows of a part: items of fewer blocks have parts of at most as many
-  const int nch = kry_chunks(n_max), nrb = KB / KR * kry_part_blocks(n_max, parts);
+  const int nch = kry_chunks(n_max), nrb = KB / KR * std::min(nblk, KPB);
   const size_t red = sizeof(cd) * 8 * 256;
   const dim3 g(xcd_grid(nrb, n_items)), b(256);
   hipLaunchKernelGGL(kry_update<true>, dim3(nch, n_items), dim3(512), red, st, items, 0);
   for (int j = 0; j < s; ++j) {
     hipLaunchKernelGGL(kry_norm, dim3(nch, n_items), dim3(512), 0, st, items, j);
     for (int p = 0; p < parts; ++p) {
-      if (p > 0) hipLaunchKernelGGL(kry_forward<true>, g, b, 0, st, items, n_items, nrb, p, parts, j);
-      hipLaunchKernelGGL(kry_forward<false>, g, b, 0, st, items, n_items, nrb, p, parts, j);
+      if (p > 0) hipLaunchKernelGGL(kry_forward<true>, g, b, 0, st, items, n_items, nrb, p, j);
+      hipLaunchKernelGGL(kry_forward<false>, g, b, 0, st, items, n_items, nrb, p, j);
     }
     for (int p = parts - 1; p >= 0; --p) {
-      if (p < parts - 1) hipLaunchKernelGGL(kry_backward<true>, g, b, 0, st, items, n_items, nrb, p, parts);
-      hipLaunchKernelGGL(kry_backward<false>, g, b, 0, st, items, n_items, nrb, p, parts);
+      if (p < parts - 1) hipLaunchKernelGGL(kry_backward<true>, g, b, 0, st, items, n_items, nrb, p);
+      hipLaunchKernelGGL(kry_backward<false>, g, b, 0, st, items, n_items, nrb, p);
     }
-    hipLaunchKernelGGL(kry_project, dim3(j + 1, n_items), dim3(512), 0, st, items);
+    hipLaunchKernelGGL(kry_project, dim3(xcd_grid(j + 1, n_items)), dim3(512), 0, st, items, n_items, j);
     hipLaunchKernelGGL(kry_update<false>, dim3(nch, n_items), dim3(512),
                        std::max(red, sizeof(cd) * 256 * (size_t)(j + 1)), st, items, j);
   }

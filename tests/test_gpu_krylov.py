@@ -31,9 +31,10 @@ def _cell(seed, n=24, phases=4):
     return rng.integers(0, phases, (n, n)).astype(np.int32), random_iso_props(phases, rng)
 
 
-# (M1, M2, bands): 2N = 198 (3 blocks and 6), 242, 310 = 2 x 128 + 54, 378, 510 = 512 - 2, 518 = 512 + 6, 578, 650
-@pytest.mark.parametrize("M1,M2,nb", [(4, 5, 1), (5, 5, 4), (2, 15, 3), (4, 10, 9), (7, 8, 6), (3, 18, 20), (8, 8, 24),
-                                      (6, 12, 33)])
+# (M1, M2, bands): 2N = 198 (3 blocks and 6), 162 and 198 at the most steps that the route takes, 242,
+# 310 = 2 x 128 + 54, 378, 510 = 512 - 2, 518 = 512 + 6, 578, 650
+@pytest.mark.parametrize("M1,M2,nb", [(4, 5, 1), (4, 4, 5), (4, 5, 11), (5, 5, 4), (2, 15, 3), (4, 10, 9), (7, 8, 6),
+                                      (3, 18, 20), (8, 8, 24), (6, 12, 33)])
 def test_krylov_bands_match_oracle(ctx, M1, M2, nb):
     phase, props = _cell(M1 * 31 + M2)
     Q = np.array([[0.0, 0.0], [0.31, 0.12], [0.5, 0.5]])
@@ -117,3 +118,21 @@ def test_krylov_modes(ctx):
         orth = np.abs(V.conj().T @ B - np.eye(nb)).max()
         print("  residual", res, "orthonormality", orth, flush=True)
         assert res <= 1e-7 and orth <= 1e-10
+
+
+# (M1, M2, bands): 2N = 510 (8 blocks) and 578 = 9 x 64 + 2, one part; 650 = 10 x 64 + 10 in 2 of 5; 1250 = 19 x 64 + 34
+# in 3 of 7, 7 and 6; all of them in one call with orders that the small and the general reduction take
+def test_krylov_parts_mixed_with_other_routes(ctx):
+    """The inverse factor in its parts, orders of one to three parts in one
+    batch with orders that other routes take: as each plan alone."""
+    Ms, nb = [(12, 12), (6, 12), (8, 8), (7, 8), (3, 3), (4, 4), (3, 18)], 5
+    phase, props = _cell(77)
+    cell = ctx.cell(phase, props, OBLIQUE)
+    Q = np.random.default_rng(7).uniform(0.02, 0.5, (4, 2))
+    print("parts", Ms, nb, flush=True)
+    plans = [cell.plan(*M) for M in Ms]
+    for M, plan, om in zip(Ms, plans, ctx.solve_batch(plans, [Q] * len(plans), nb)):
+        assert np.array_equal(om, plan.solve(Q, nb)), M
+        ref, _ = mo.bands(phase, props, OBLIQUE, *M, Q[:1], nb)
+        print("  error", M, band_error(om[:1], ref), flush=True)
+        assert band_error(om[:1], ref) <= TOL64
