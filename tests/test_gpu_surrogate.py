@@ -196,3 +196,33 @@ def test_surrogate_ranking_beats_random_selection(ctx):
           f"random solves to reach the surrogate's best ~ {1.0 / max(frac, 1e-9):.0f}", flush=True)
     assert best_s >= np.percentile(best_r, 90)
     assert mean_s > np.percentile(mean_r, 99)
+
+
+# one cell, a cell more than one per workgroup of the fused convolutions, ragged rows of every product
+@pytest.mark.parametrize("B", [1, 257, 301])
+def test_bf16_batches_match_single_cells(ctx, B):
+    """A cell's outputs do not depend on the batch around it; gradients of ragged
+    batches against the reference."""
+    from paper_1310_6380_amd import mvpb
+    print("surrogate batch", B, flush=True)
+    net = mvpb.Surrogate(ctx, max_batch=B, precision=1, seed=B)
+    net.set_params(_nudge_biases(net.get_params().astype(np.float64), np.random.default_rng(B)))
+    theta = net.get_params().astype(np.float64)
+    cells, target = _batch(B, B)
+    cells[0] *= 3                                         # any non-zero pixel counts as one
+    out = net.infer(cells)
+    for i in (0, B // 2, B - 1):
+        assert np.array_equal(net.infer(cells[i:i + 1])[0], out[i]), i
+    ones = (cells != 0).astype(np.float64)
+    ref = sr.forward(theta, ones)
+    assert np.linalg.norm(out - ref) <= 2e-2 * np.linalg.norm(ref)
+    n = min(B, 33)
+    loss, g = net.gradients(cells[:n], target[:n])
+    L, gref = sr.gradients(theta, ones[:n], target[:n].astype(np.float64))
+    assert abs(loss - L) <= 2e-2 * L
+    o = 0
+    for s in sr.param_shapes():
+        k = int(np.prod(s))
+        assert np.linalg.norm(g[o:o + k] - gref[o:o + k]) <= 2e-2 * max(np.linalg.norm(gref[o:o + k]), 1e-30), s
+        o += k
+    net.close()
