@@ -849,6 +849,16 @@ extern "C" int mvpb_structure_factors_noalloc(mvpb_cell c, int M1, int M2, int p
   return MVPB_OK;
 }
 
+// Products of the isotropic plan that need not be whole.  P = L_R^-1 diag(G) L_x^-H:
+// both factors are triangular.  X_lm = P_l P_m^H, number x 9 + l 3 + m: the diagonal
+// blocks of C(k) and the block below them take, of the upper triangle, only S_00,
+// S_01, S_20, S_21 and D_01, D_02, D_10, D_12, D_20, D_21 (combine_coefficients, form_operator).
+static unsigned long long factor_product_shape(int N) { return gemm_shape(N, GEMM_A_LOWER | GEMM_B_UPPER); }
+static unsigned long long coefficient_product_shape(int N, int i) {
+  constexpr int LOWER = 1 << 2 | 1 << 3 | 1 << 4 | 1 << 5 | 1 << 8 | 1 << 9 | 1 << 13 | 1 << 17;
+  return gemm_shape(N, LOWER >> i & 1 ? GEMM_C_LOWER : 0);
+}
+
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
@@ -966,6 +976,10 @@ static int build_plan_group(mvpb_ctx ctx, const mvpb_cell *cells, int g, int M1,
     for (int x = 0; x < 2; ++x)
       for (int l = 0; l < 3; ++l)
         for (int m = 0; m < 3; ++m) hp.push_back(Xm + (18 * c + x * 9 + l * 3 + m) * NN);
+  const size_t o_pH = hp.size();
+  for (int i = 0; i < 6 * g; ++i) hp.push_back((void *)factor_product_shape(N));
+  const size_t o_xH = hp.size();
+  for (int i = 0; i < 18 * g; ++i) hp.push_back((void *)coefficient_product_shape(N, i % 18));
   HIP_TRY(ptrs.alloc(sizeof(void *) * hp.size()));
   HIP_TRY(hipMemcpyAsync(ptrs.p, hp.data(), sizeof(void *) * hp.size(), hipMemcpyHostToDevice, st));
   void **dp = ptrs.as<void *>();
@@ -981,12 +995,12 @@ static int build_plan_group(mvpb_ctx ctx, const mvpb_cell *cells, int g, int M1,
                      names[i % 3], hstat[i] - 1);
   {
     GemmBatch bt{(const cd *const *)(dp + o_pA), (const cd *const *)(dp + o_pB), (cd *const *)(dp + o_pC),
-                 (const double *const *)(dp + o_pS), N, N, N};
+                 (const double *const *)(dp + o_pS), N, N, N, (const unsigned long long *)(dp + o_pH)};
     HIP_TRY(launch_zgemm(OP_N, OP_C, N, N, N, mk(1.0, 0.0), bt, mk(0.0, 0.0), 6 * g, st));
   }
   {
     GemmBatch bt{(const cd *const *)(dp + o_xA), (const cd *const *)(dp + o_xB), (cd *const *)(dp + o_xC),
-                 nullptr, N, N, N};
+                 nullptr, N, N, N, (const unsigned long long *)(dp + o_xH)};
     HIP_TRY(launch_zgemm(OP_N, OP_C, N, N, N, mk(1.0, 0.0), bt, mk(0.0, 0.0), 18 * g, st));
   }
   std::vector<mvpb_plan> made;
@@ -1106,55 +1120,71 @@ static int build_plan_general(mvpb_cell c, int M1, int M2, int M3, int precision
   };
   // B_s = (columns s N .. (s+1) N - 1 of L_P^-1)^H (N x nsig)
   auto Bs = [&](int s_) { return (const void *)(LP + (size_t)s_ * N * nsig); };
+  auto shp = [](int K, int flags, int off = 0) { return (const void *)gemm_shape(K, flags, off); };
+  // B_s starts with s N zero columns and its columns from there are upper triangular
   // Z_0 block a = sum_b L_R^-1 diag(G_b) B_{voigt(a,b)}: one launch per b over a
-  size_t z0[3][4];
+  size_t z0[3][5];
   for (int b = 0; b < d; ++b) {
-    std::vector<const void *> A, B, C, S;
+    std::vector<const void *> A, B, C, S, H;
     for (int a = 0; a < d; ++a) {
       A.push_back(LR);
       B.push_back(Bs(voigt_index(d, a, b)));
       C.push_back(Zm + (size_t)a * N);
       S.push_back(gd + (size_t)b * N);
+      H.push_back(shp(N, GEMM_A_LOWER | GEMM_B_UPPER, voigt_index(d, a, b) * N));
     }
     z0[b][0] = list(A);
     z0[b][1] = list(B);
     z0[b][2] = list(C);
     z0[b][3] = list(S);
+    z0[b][4] = list(H);
   }
   // Z_l block a = L_R^-1 B_{voigt(a, l-1)}, l = 1 .. d: one launch
-  size_t zl[3];
+  size_t zl[4];
   {
-    std::vector<const void *> A, B, C;
+    std::vector<const void *> A, B, C, H;
     for (int l = 1; l <= d; ++l)
       for (int a = 0; a < d; ++a) {
         A.push_back(LR);
         B.push_back(Bs(voigt_index(d, a, l - 1)));
         C.push_back(Zm + (size_t)l * n * nsig + (size_t)a * N);
+        H.push_back(shp(N, GEMM_A_LOWER | GEMM_B_UPPER, voigt_index(d, a, l - 1) * N));
       }
     zl[0] = list(A);
     zl[1] = list(B);
     zl[2] = list(C);
+    zl[3] = list(H);
   }
-  // coefficients |Omega|^2 Z_l Z_m^H for l <= m, then + |Omega|^2 Z_m Z_l^H for l < m
-  size_t c1[3], c2[3];
-  int n2 = 0;
-  {
-    std::vector<const void *> A1, B1, C1, A2, B2, C2;
+  // coefficients |Omega|^2 (Z_l Z_m^H [+ Z_m Z_l^H for l < m]), the N x N blocks on
+  // and below the diagonal only (all that the formation of C(k) reads), each from
+  // the first column where both of its factors' blocks are not zero
+  auto first = [&](int l, int a) {   // of block row a of Z_l, in blocks of N columns
+    int f = l > 0 ? voigt_index(d, a, l - 1) : ns;
+    for (int b = 0; l == 0 && b < d; ++b) f = std::min(f, voigt_index(d, a, b));
+    return f;
+  };
+  size_t cf[2][4];
+  int n_cf[2];
+  for (int two = 0; two < 2; ++two) {
+    std::vector<const void *> A, B, C, H;
     int q = 0;
     for (int l = 0; l <= d; ++l)
-      for (int m = l; m <= d; ++m, ++q) {
-        A1.push_back(Zm + (size_t)l * n * nsig);
-        B1.push_back(Zm + (size_t)m * n * nsig);
-        C1.push_back(coef + (size_t)q * nn);
-        if (l < m) {
-          A2.push_back(Zm + (size_t)m * n * nsig);
-          B2.push_back(Zm + (size_t)l * n * nsig);
-          C2.push_back(coef + (size_t)q * nn);
-        }
-      }
-    n2 = (int)A2.size();
-    c1[0] = list(A1); c1[1] = list(B1); c1[2] = list(C1);
-    c2[0] = list(A2); c2[1] = list(B2); c2[2] = list(C2);
+      for (int m = l; m <= d; ++m, ++q)
+        for (int a = 0; a < d; ++a)
+          for (int b = 0; b <= a; ++b) {
+            if (two && l == m) continue;
+            const int r = two ? m : l, c = two ? l : m;
+            const int k0 = std::max(first(r, a), first(c, b)) * N;
+            A.push_back(Zm + ((size_t)r * nsig + k0) * n + (size_t)a * N);
+            B.push_back(Zm + ((size_t)c * nsig + k0) * n + (size_t)b * N);
+            C.push_back(coef + (size_t)q * nn + (size_t)b * N * n + (size_t)a * N);
+            H.push_back(shp(nsig - k0, a == b ? GEMM_C_LOWER : 0));
+          }
+    n_cf[two] = (int)A.size();
+    cf[two][0] = list(A);
+    cf[two][1] = list(B);
+    cf[two][2] = list(C);
+    cf[two][3] = list(H);
   }
   HIP_TRY(ptrs.alloc(sizeof(void *) * tab.size()));
   HIP_TRY(hipMemcpyAsync(ptrs.p, tab.data(), sizeof(void *) * tab.size(), hipMemcpyHostToDevice, st));
@@ -1168,23 +1198,20 @@ static int build_plan_general(mvpb_cell c, int M1, int M2, int M3, int precision
   if (hstat[0] || hstat[1])
     return set_err(MVPB_E_NOT_PD, "%s is not positive definite (pivot %d)",
                    hstat[0] ? "compliance matrix Phi" : "density matrix Omega", (hstat[0] ? hstat[0] : hstat[1]) - 1);
+  auto sp = [&](size_t o) { return (const unsigned long long *)(dp + o); };
   for (int b = 0; b < d; ++b) {
     GemmBatch bt{cp(z0[b][0]), cp(z0[b][1]), (cd *const *)(dp + z0[b][2]), (const double *const *)(dp + z0[b][3]),
-                 N, nsig, n};
+                 N, nsig, n, sp(z0[b][4])};
     HIP_TRY(launch_zgemm(OP_N, OP_C, N, nsig, N, mk(1.0, 0.0), bt, mk(b == 0 ? 0.0 : 1.0, 0.0), d, st));
   }
   {
-    GemmBatch bt{cp(zl[0]), cp(zl[1]), (cd *const *)(dp + zl[2]), nullptr, N, nsig, n};
+    GemmBatch bt{cp(zl[0]), cp(zl[1]), (cd *const *)(dp + zl[2]), nullptr, N, nsig, n, sp(zl[3])};
     HIP_TRY(launch_zgemm(OP_N, OP_C, N, nsig, N, mk(1.0, 0.0), bt, mk(0.0, 0.0), d * d, st));
   }
   const double v2 = c->area * c->area;
-  {
-    GemmBatch bt{cp(c1[0]), cp(c1[1]), (cd *const *)(dp + c1[2]), nullptr, n, n, n};
-    HIP_TRY(launch_zgemm(OP_N, OP_C, n, n, nsig, mk(v2, 0.0), bt, mk(0.0, 0.0), nc, st));
-  }
-  {
-    GemmBatch bt{cp(c2[0]), cp(c2[1]), (cd *const *)(dp + c2[2]), nullptr, n, n, n};
-    HIP_TRY(launch_zgemm(OP_N, OP_C, n, n, nsig, mk(v2, 0.0), bt, mk(1.0, 0.0), n2, st));
+  for (int two = 0; two < 2; ++two) {
+    GemmBatch bt{cp(cf[two][0]), cp(cf[two][1]), (cd *const *)(dp + cf[two][2]), nullptr, n, n, n, sp(cf[two][3])};
+    HIP_TRY(launch_zgemm(OP_N, OP_C, N, N, nsig, mk(v2, 0.0), bt, mk(two ? 1.0 : 0.0, 0.0), n_cf[two], st));
   }
   pl->M1 = M1;
   pl->M2 = M2;
@@ -2012,6 +2039,35 @@ extern "C" int mvpb_band_sensitivities(mvpb_plan p, int n_k, const double *Q, in
   return MVPB_OK;
 }
 
+// Z_q = alpha L_q^-H (L_q^-1 X_q) over cols columns of order N each (Y_q: scratch,
+// ptrs: the pointer tables' buffer).  All columns are one product: with one product
+// per k, of n_bands columns, most of a 64-wide tile is empty (18 bands, 60 k, N =
+// 441: 344 + 336 us then, 138 + 135 now).
+static int solve_columns(mvpb_ctx ctx, size_t cols, int N, const std::vector<const cd *> &Li, const std::vector<cd *> &X,
+                         const std::vector<cd *> &Y, const std::vector<cd *> &Z, double alpha, DevBuf &ptrs) {
+  constexpr size_t MOST = (size_t)1 << 21;   // columns of a launch (its grid has at most 65535 tiles of 64)
+  const size_t m = Li.size(), chunks = (cols + MOST - 1) / MOST;
+  std::vector<const void *> hp;
+  for (size_t c = 0; c < chunks; ++c) {
+    const size_t o = c * MOST * N;
+    for (size_t q = 0; q < m; ++q) hp.push_back(Li[q]);
+    for (size_t q = 0; q < m; ++q) hp.push_back(X[q] + o);
+    for (size_t q = 0; q < m; ++q) hp.push_back(Y[q] + o);
+    for (size_t q = 0; q < m; ++q) hp.push_back(Z[q] + o);
+  }
+  HIP_TRY(ptrs.alloc(sizeof(void *) * hp.size()));
+  HIP_TRY(hipMemcpyAsync(ptrs.p, hp.data(), sizeof(void *) * hp.size(), hipMemcpyHostToDevice, ctx->stream));
+  for (size_t c = 0; c < chunks; ++c) {
+    void **dp = ptrs.as<void *>() + 4 * m * c;
+    const int w = (int)std::min(MOST, cols - c * MOST);
+    GemmBatch b1{(const cd *const *)dp, (const cd *const *)(dp + m), (cd *const *)(dp + 2 * m), nullptr, N, N, N};
+    HIP_TRY(launch_zgemm(OP_N, OP_N, N, w, N, mk(1.0, 0.0), b1, mk(0.0, 0.0), (int)m, ctx->stream));
+    GemmBatch b2{(const cd *const *)dp, (const cd *const *)(dp + 2 * m), (cd *const *)(dp + 3 * m), nullptr, N, N, N};
+    HIP_TRY(launch_zgemm(OP_C, OP_N, N, w, N, mk(alpha, 0.0), b2, mk(0.0, 0.0), (int)m, ctx->stream));
+  }
+  return MVPB_OK;
+}
+
 extern "C" int mvpb_stress_modes(mvpb_plan p, int n_k, const double *Q, int n_bands, const double *U, double *S,
                                  unsigned flags) {
   if (!p || !Q || !U || !S) return set_err(MVPB_E_INVALID, "NULL argument");
@@ -2044,27 +2100,16 @@ extern "C" int mvpb_stress_modes(mvpb_plan p, int n_k, const double *Q, int n_ba
     HIP_TRY(Y.alloc(s_bytes));
     HIP_TRY(launch_stress_rhs_general(u_in, qd_.as<double>(), n_k, nb, p->dim, p->M1, p->M2, p->M3, p->T3, p->area,
                                       X.as<cd>(), st));
-    std::vector<const void *> hp;
-    for (int t = 0; t < n_k; ++t) hp.push_back(p->linvPhi.p);
-    for (int t = 0; t < n_k; ++t) hp.push_back(X.as<cd>() + (size_t)t * nb * ns);
-    for (int t = 0; t < n_k; ++t) hp.push_back(Y.as<cd>() + (size_t)t * nb * ns);
-    for (int t = 0; t < n_k; ++t) hp.push_back(s_out + (size_t)t * nb * ns);
-    HIP_TRY(ptrs.alloc(sizeof(void *) * hp.size()));
-    HIP_TRY(hipMemcpyAsync(ptrs.p, hp.data(), sizeof(void *) * hp.size(), hipMemcpyHostToDevice, st));
-    void **dp = ptrs.as<void *>();
-    GemmBatch b1{(const cd *const *)dp, (const cd *const *)(dp + n_k), (cd *const *)(dp + 2 * n_k), nullptr, ns, ns,
-                 ns};
-    HIP_TRY(launch_zgemm(OP_N, OP_N, ns, nb, ns, mk(1.0, 0.0), b1, mk(0.0, 0.0), n_k, st));
-    GemmBatch b2{(const cd *const *)dp, (const cd *const *)(dp + 2 * n_k), (cd *const *)(dp + 3 * n_k), nullptr, ns,
-                 ns, ns};
-    HIP_TRY(launch_zgemm(OP_C, OP_N, ns, nb, ns, mk(-1.0, 0.0), b2, mk(0.0, 0.0), n_k, st));
+    const int rc = solve_columns(ctx, (size_t)n_k * nb, ns, {p->linvPhi.as<cd>()}, {X.as<cd>()}, {Y.as<cd>()}, {s_out},
+                                 -1.0, ptrs);
+    if (rc) return rc;
     if (!dev) HIP_TRY(hipMemcpyAsync(S, s_out, s_bytes, hipMemcpyDeviceToHost, st));
     if (!(flags & MVPB_F_ASYNC) || !dev) HIP_TRY(hipStreamSynchronize(st));
     return MVPB_OK;
   }
   const int N = p->N, nb = n_bands;
-  const size_t NN = (size_t)N * N, blk = (size_t)3 * N * nb;   // one k: three N x nb blocks
-  const size_t u_bytes = sizeof(cd) * (size_t)n_k * nb * 2 * N, s_bytes = sizeof(cd) * (size_t)n_k * blk;
+  const size_t NN = (size_t)N * N;
+  const size_t u_bytes = sizeof(cd) * (size_t)n_k * nb * 2 * N, s_bytes = sizeof(cd) * (size_t)n_k * nb * 3 * N;
   DevBuf qd(&ctx->pool), ud(&ctx->pool), sd(&ctx->pool), X(&ctx->pool), Y(&ctx->pool), ptrs(&ctx->pool);
   HIP_TRY(qd.alloc(sizeof(double) * 2 * (size_t)n_k));
   HIP_TRY(hipMemcpyAsync(qd.p, Q, sizeof(double) * 2 * (size_t)n_k, hipMemcpyHostToDevice, st));
@@ -2080,22 +2125,13 @@ extern "C" int mvpb_stress_modes(mvpb_plan p, int n_k, const double *Q, int n_ba
   HIP_TRY(X.alloc(s_bytes));
   HIP_TRY(Y.alloc(s_bytes));
   HIP_TRY(launch_stress_rhs(u_in, qd.as<double>(), n_k, nb, p->M1, p->M2, p->T, p->area, X.as<cd>(), st));
-  // Y = L^-1 X, then X = L^-H Y: Sigma^-1 on block 0, Delta^-1 on blocks 1, 2
-  std::vector<const void *> hp;
-  for (int j = 0; j < 3; ++j)
-    for (int t = 0; t < n_k; ++t) hp.push_back(p->linvSD.as<cd>() + (j == 0 ? 0 : NN));
-  for (int j = 0; j < 3; ++j)
-    for (int t = 0; t < n_k; ++t) hp.push_back(X.as<cd>() + (size_t)t * blk + (size_t)j * N * nb);
-  for (int j = 0; j < 3; ++j)
-    for (int t = 0; t < n_k; ++t) hp.push_back(Y.as<cd>() + (size_t)t * blk + (size_t)j * N * nb);
-  const size_t m = (size_t)3 * n_k;
-  HIP_TRY(ptrs.alloc(sizeof(void *) * hp.size()));
-  HIP_TRY(hipMemcpyAsync(ptrs.p, hp.data(), sizeof(void *) * hp.size(), hipMemcpyHostToDevice, st));
-  void **dp = ptrs.as<void *>();
-  GemmBatch b1{(const cd *const *)dp, (const cd *const *)(dp + m), (cd *const *)(dp + 2 * m), nullptr, N, N, N};
-  HIP_TRY(launch_zgemm(OP_N, OP_N, N, nb, N, mk(1.0, 0.0), b1, mk(0.0, 0.0), (int)m, st));
-  GemmBatch b2{(const cd *const *)dp, (const cd *const *)(dp + 2 * m), (cd *const *)(dp + m), nullptr, N, N, N};
-  HIP_TRY(launch_zgemm(OP_C, OP_N, N, nb, N, mk(1.0, 0.0), b2, mk(0.0, 0.0), (int)m, st));
+  // Sigma^-1 on block 0, Delta^-1 on blocks 1, 2
+  const cd *Li = p->linvSD.as<cd>();
+  const size_t bs = (size_t)N * nb * n_k;
+  cd *x = X.as<cd>(), *y = Y.as<cd>();
+  const int rc = solve_columns(ctx, (size_t)n_k * nb, N, {Li, Li + NN, Li + NN}, {x, x + bs, x + 2 * bs},
+                               {y, y + bs, y + 2 * bs}, {x, x + bs, x + 2 * bs}, 1.0, ptrs);
+  if (rc) return rc;
   HIP_TRY(launch_stress_combine(X.as<cd>(), n_k, nb, N, s_out, st));
   if (!dev) HIP_TRY(hipMemcpyAsync(S, s_out, s_bytes, hipMemcpyDeviceToHost, st));
   if (!(flags & MVPB_F_ASYNC) || !dev) HIP_TRY(hipStreamSynchronize(st));
@@ -2303,7 +2339,7 @@ struct CellGroup {
   int M1, M2, N, c0, c1;
   size_t o_coef;                      // coefficient matrices of cell c0
   size_t t_ptrs;                      // pointer table of the factorisations and GEMMs
-  size_t n_ptrs, o_inv, o_pA, o_pB, o_pC, o_pS, o_xA, o_xB, o_xC;   // entries in it
+  size_t n_ptrs, o_inv, o_pA, o_pB, o_pC, o_pS, o_xA, o_xB, o_xC, o_pH, o_xH;   // entries in it
   size_t t_gvec, t_scale;             // G vectors (3 N per cell), combine scales
   struct Run {                        // structure-factor launch: cells of one grid
     int k0, cnt;
@@ -2400,7 +2436,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
                      4 * align256(sizeof(cd) * 3 * NN * cnt) /* mats, linv: 3 NN each; P: 6 NN */ +
                      align256(sizeof(cd) * 18 * NN * cnt);
     temp_bytes = std::max(temp_bytes, t);
-    g.n_ptrs = 6 * cnt + 4 * 6 * cnt + 3 * 18 * cnt;
+    g.n_ptrs = 6 * cnt + 5 * 6 * cnt + 4 * 18 * cnt;
     g.t_ptrs = take_tab(sizeof(void *) * g.n_ptrs);
     g.t_gvec = take_tab(sizeof(double) * 3 * (size_t)g.N * cnt);
     g.t_scale = take_tab(sizeof(double) * cnt);
@@ -2536,6 +2572,10 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       for (int x = 0; x < 2; ++x)
         for (int l = 0; l < 3; ++l)
           for (int m = 0; m < 3; ++m) push(Xm + (18 * c + x * 9 + l * 3 + m) * NN);
+    g.o_pH = e;
+    for (size_t i = 0; i < 6 * cnt; ++i) push((const void *)factor_product_shape(g.N));
+    g.o_xH = e;
+    for (size_t i = 0; i < 18 * cnt; ++i) push((const void *)coefficient_product_shape(g.N, (int)(i % 18)));
     if (e != g.n_ptrs) return set_err(MVPB_E_DEVICE, "internal: pointer table of %zu entries, expected %zu", e, g.n_ptrs);
     // G_l vectors at Q = 0 and the coefficient scales |Omega|^2 / 2
     for (size_t c = 0; c < cnt; ++c) {
@@ -2632,12 +2672,12 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       if (e == hipSuccess) e = launch_identity_if_failed((cd *const *)(dp + g.o_inv), gstat, 3 * cnt, g.N, st);
       if (e == hipSuccess) {
         GemmBatch bt{(const cd *const *)(dp + g.o_pA), (const cd *const *)(dp + g.o_pB), (cd *const *)(dp + g.o_pC),
-                     (const double *const *)(dp + g.o_pS), g.N, g.N, g.N};
+                     (const double *const *)(dp + g.o_pS), g.N, g.N, g.N, (const unsigned long long *)(dp + g.o_pH)};
         e = launch_zgemm(OP_N, OP_C, g.N, g.N, g.N, mk(1.0, 0.0), bt, mk(0.0, 0.0), 6 * cnt, st);
       }
       if (e == hipSuccess) {
         GemmBatch bt{(const cd *const *)(dp + g.o_xA), (const cd *const *)(dp + g.o_xB), (cd *const *)(dp + g.o_xC),
-                     nullptr, g.N, g.N, g.N};
+                     nullptr, g.N, g.N, g.N, (const unsigned long long *)(dp + g.o_xH)};
         e = launch_zgemm(OP_N, OP_C, g.N, g.N, g.N, mk(1.0, 0.0), bt, mk(0.0, 0.0), 18 * cnt, st);
       }
       if (e == hipSuccess)

@@ -219,10 +219,11 @@ __global__ void __launch_bounds__(256) stress_rhs(const cd *__restrict__ U, cons
   // -i |Omega| z = |Omega| (z.im, -z.re)
   auto mi = [&](cd z) { return mk(area * z.im, -area * z.re); };
   const cd v11 = mi(k1 * u1), v22 = mi(k2 * u2), v12 = mi(k2 * u1 + k1 * u2);
-  cd *x = X + (size_t)t * 3 * N * nb;
-  x[(size_t)b * N + r] = v11 + v22;
-  x[(size_t)N * nb + (size_t)b * N + r] = v11 - v22;
-  x[(size_t)2 * N * nb + (size_t)b * N + r] = v12;
+  const size_t blk = (size_t)gridDim.y * nb * N;   // one of the three blocks: every mode of every k
+  cd *x = X + ((size_t)t * nb + b) * N + r;
+  x[0] = v11 + v22;
+  x[blk] = v11 - v22;
+  x[2 * blk] = v12;
 }
 
 __global__ void __launch_bounds__(256) stress_combine(const cd *__restrict__ Z, int nb, int N, cd *__restrict__ S) {
@@ -230,8 +231,9 @@ __global__ void __launch_bounds__(256) stress_combine(const cd *__restrict__ Z, 
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= N * nb) return;
   const int r = e % N, b = e / N;
-  const cd *z = Z + (size_t)t * 3 * N * nb + (size_t)b * N + r;
-  const cd zs = z[0], zd = z[(size_t)N * nb], z12 = z[(size_t)2 * N * nb];
+  const size_t blk = (size_t)gridDim.y * nb * N;
+  const cd *z = Z + ((size_t)t * nb + b) * N + r;
+  const cd zs = z[0], zd = z[blk], z12 = z[2 * blk];
   cd *s = S + ((size_t)t * nb + b) * 3 * N;
   s[r] = -0.5 * (zs + zd);
   s[N + r] = -0.5 * (zs - zd);

@@ -123,7 +123,7 @@ size_t sf_poly_scratch_bytes(int n_edges, int M1, int M2);
 // Stress modes S = -Phi^-1 H* U (isotropic cells).  stress_rhs: from U
 // [n_k][nb][2N] (complex) the three right-hand sides X[t][j] (N x nb,
 // column-major), j = 0: V11 + V22, 1: V11 - V22, 2: V12 with V = H* U;
-// stress_combine: S[t][b][3N] from Z[t][j] = (Sigma^-1, Delta^-1, Delta^-1)
+// stress_combine: S[t][b][3N] from Z[j][t] = (Sigma^-1, Delta^-1, Delta^-1)
 // applied to X[t][j].  Q: device [n_k][2].
 hipError_t launch_stress_rhs(const cd *U, const double *Q, int n_k, int nb, int M1, int M2, const double T[4],
                              double area, cd *X, hipStream_t st);
@@ -182,7 +182,15 @@ struct GemmBatch {
   cd *const *C;
   const double *const *s;
   int lda, ldb, ldc;
+  const unsigned long long *shape = nullptr;   // per item, see gemm_shape; NULL: every product whole
 };
+// What of a product is known to be zero or not wanted: its own depth K, op(A)
+// lower triangular, op(B)[k][j] zero beyond k = j - off, only the tiles on and
+// below the diagonal of C.
+enum { GEMM_A_LOWER = 1, GEMM_B_UPPER = 2, GEMM_C_LOWER = 4 };
+constexpr unsigned long long gemm_shape(int K, int flags, int off = 0) {
+  return (unsigned long long)(unsigned)K | (unsigned long long)(unsigned)off << 24 | (unsigned long long)(unsigned)flags << 48;
+}
 hipError_t launch_zgemm(Op opA, Op opB, int M, int N, int K, cd alpha, GemmBatch bt, cd beta, int count,
                         hipStream_t st);
 
