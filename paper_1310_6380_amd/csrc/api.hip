@@ -984,7 +984,8 @@ static int build_plan_group(mvpb_ctx ctx, const mvpb_cell *cells, int g, int M1,
   HIP_TRY(hipMemcpyAsync(ptrs.p, hp.data(), sizeof(void *) * hp.size(), hipMemcpyHostToDevice, st));
   void **dp = ptrs.as<void *>();
 
-  HIP_TRY(launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + o_inv), stat.as<int>(), 3 * g, N, st));
+  HIP_TRY(launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + o_inv), stat.as<int>(), 3 * g, N,
+                             (precision & MVPB_PREC_EIG_FP32_RR64) != 0, st));
   std::vector<int> hstat(3 * g, 0);
   HIP_TRY(hipMemcpyAsync(hstat.data(), stat.p, sizeof(int) * 3 * g, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1054,6 +1055,18 @@ static int voigt_index(int dim, int a, int b) {
   if (dim == 2) return 2;
   const int lo = std::min(a, b), hi = std::max(a, b);
   return lo == 1 ? 3 : (hi == 2 ? 4 : 5);   // (1,2) -> 3, (0,2) -> 4, (0,1) -> 5
+}
+
+// Grow the context's step-event pool to at least `count` events (outside any
+// capture).
+static hipError_t reserve_la_events(mvpb_ctx ctx, size_t count) {
+  while (ctx->la_events.size() < count) {
+    hipEvent_t ev;
+    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+    ctx->la_events.push_back(ev);
+  }
+  return hipSuccess;
 }
 
 // Plan of the general layout for one pixel or voxel cell: weight fields on the
@@ -1190,8 +1203,19 @@ static int build_plan_general(mvpb_cell c, int M1, int M2, int M3, int precision
   HIP_TRY(hipMemcpyAsync(ptrs.p, tab.data(), sizeof(void *) * tab.size(), hipMemcpyHostToDevice, st));
   void **dp = ptrs.as<void *>();
   auto cp = [&](size_t o) { return (const cd *const *)(dp + o); };
-  HIP_TRY(launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + 1), stat.as<int>(), 1, nsig, st));
-  HIP_TRY(launch_potrf_trtri((cd *const *)(dp + 2), (cd *const *)(dp + 3), stat.as<int>() + 1, 1, N, st));
+  const bool keep = (precision & MVPB_PREC_EIG_FP32_RR64) != 0;
+  // the density matrix's factorisation, a chain of N / 64 steps that leaves the chip
+  // idle, beside the compliance matrix's (of a 3 N = 1029 cell 6 of 33 steps)
+  HIP_TRY(reserve_la_events(ctx, 2));
+  HIP_TRY(hipEventRecord(ctx->la_events[0], st));
+  HIP_TRY(hipStreamWaitEvent(ctx->la[0], ctx->la_events[0], 0));
+  const hipError_t eR =
+      launch_potrf_trtri((cd *const *)(dp + 2), (cd *const *)(dp + 3), stat.as<int>() + 1, 1, N, keep, ctx->la[0]);
+  const hipError_t eP = launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + 1), stat.as<int>(), 1, nsig, keep, st);
+  HIP_TRY(hipEventRecord(ctx->la_events[1], ctx->la[0]));
+  HIP_TRY(hipStreamWaitEvent(st, ctx->la_events[1], 0));
+  HIP_TRY(eR);
+  HIP_TRY(eP);
   int hstat[2] = {0, 0};
   HIP_TRY(hipMemcpyAsync(hstat, stat.p, sizeof hstat, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1710,18 +1734,6 @@ static std::string launch_signature(const std::vector<Job> &jobs, int nb, bool f
 // in `parts` parts: two per stage-1 step and part, then the fork and join of
 // the tridiagonal eigenvectors.
 static size_t la_events_needed(int n_max, int parts) { return (size_t)2 * parts * stage1_steps(n_max) + 2; }
-
-// Grow the context's step-event pool to at least `count` events (outside any
-// capture).
-static hipError_t reserve_la_events(mvpb_ctx ctx, size_t count) {
-  while (ctx->la_events.size() < count) {
-    hipEvent_t ev;
-    hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e != hipSuccess) return e;
-    ctx->la_events.push_back(ev);
-  }
-  return hipSuccess;
-}
 
 // The eigensolve launch sequence over the items of a device table whose
 // operator orders are `orders` (table order).  Reduction: operator formation,
@@ -2668,7 +2680,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       cd *Xm = reinterpret_cast<cd *>(tp);
       void **dp = reinterpret_cast<void **>(W + g.t_ptrs);
       if (e == hipSuccess) e = launch_toeplitz_scatter(F, g.M1, g.M2, g.N, Tm, cnt, st);
-      if (e == hipSuccess) e = launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + g.o_inv), gstat, 3 * cnt, g.N, st);
+      if (e == hipSuccess) e = launch_potrf_trtri((cd *const *)dp, (cd *const *)(dp + g.o_inv), gstat, 3 * cnt, g.N, fp32, st);
       if (e == hipSuccess) e = launch_identity_if_failed((cd *const *)(dp + g.o_inv), gstat, 3 * cnt, g.N, st);
       if (e == hipSuccess) {
         GemmBatch bt{(const cd *const *)(dp + g.o_pA), (const cd *const *)(dp + g.o_pB), (cd *const *)(dp + g.o_pC),

@@ -170,7 +170,8 @@ hipError_t launch_sensitivities(const cd *U, const cd *S, const double *omega, i
 // matrices A[b] (N x N, column-major); Linv[b] receives L^-1 (lower, the
 // strict upper part zeroed).  status[b] = 0 on success, j+1 if the pivot of
 // column j was not positive.
-hipError_t launch_potrf_trtri(cd *const *A, cd *const *Linv, int *status, int count, int N, hipStream_t st);
+hipError_t launch_potrf_trtri(cd *const *A, cd *const *Linv, int *status, int count, int N, bool keep_order,
+                              hipStream_t st);
 hipError_t launch_identity_if_failed(cd *const *Linv, const int *status, int count, int N, hipStream_t st);
 
 enum Op { OP_N = 0, OP_C = 1 };
