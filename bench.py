@@ -80,12 +80,29 @@ def backtransform_flops(n: int, nb: int) -> float:
     return CMAC * (s2 + s1)
 
 
+def krylov_counts(n: int, nb: int):
+    """(flops of the factorisation, bytes of the block steps) of one item of the
+    shift-invert route: the Cholesky factor (n^3 / 6 complex MACs) and its inverse
+    within parts of at most 9 blocks of 64; per step the factor and the parts read
+    twice (forward and backward, a triangle in all), and the basis of 16-vector
+    blocks read twice by the orthogonalisation."""
+    blocks = -(-n // 64)
+    width = 64 * -(-blocks // -(-blocks // 9))
+    parts = [min(width, n - r) for r in range(0, n, width)]
+    s = 6 + (9 * nb + 24) // 25
+    return (CMAC * (n ** 3 + sum(w ** 3 for w in parts)) / 6.0,
+            16.0 * (s * n * n + s * (s + 1) * HB * n))
+
+
 # Roofline models of the kernels that can dominate a step: (bound, unit, peak,
 # algorithmic amount of one item of order n).  Bytes are complex FP64 entries
 # moved once: the Hermitian trailing matrix is stored by its lower triangle.
 def roofline_models(n: int, nb: int):
     tr = _trailing(n)
+    factor, steps = krylov_counts(n, nb)
     return {
+        "krylov_factor": ("mfma", "TFLOP/s", FP64_PEAK_TFLOPS, factor),
+        "krylov_steps": ("hbm", "GB/s", HBM_PEAK_GBS, steps),
         "hb2st": ("alu", "TFLOP/s", FP64_PEAK_TFLOPS, hb2st_flops(n)),
         "he2hb_her2k": ("hbm", "GB/s", HBM_PEAK_GBS,
                         sum(16.0 * m * (m + 1) + 2 * 16.0 * m * kq for m, kq in tr)),

@@ -36,11 +36,12 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-SHARED_HEADERS = ("common.h", "kernels.h")
+SHARED_HEADERS = ("common.h", "kernels.h", "chol64.h")
 # kernel families timed as one launch -> a kernel of the family
 FAMILY = {"backtransform": "backtransform_2s", "tridiag_eig": "tridiag_invit", "rayleigh_ritz": "rr_product",
           "potrf_trtri": "potrf_diag", "zgemm": "zgemm_kernel", "structure_factors": "sf_mfma_pass_a",
-          "combine_coefficients": "combine_coefficients"}
+          "combine_coefficients": "combine_coefficients", "krylov_factor": "kry_chol_step",
+          "krylov_steps": "kry_forward"}
 
 
 def kernel_source(name: str):
