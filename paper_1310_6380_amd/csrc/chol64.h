@@ -158,7 +158,6 @@ MVPB_DEV int chol64(cd *A, cd *X, size_t ld, int nb, Chol64 &sm) {
       Acc3 s, o;
       s.clear();
       o.clear();
-#pragma unroll 4
       for (int k = c0; k < p0; k += 4) s.step(D[(p0 + li) * LD + k + lk], I[(k + lk) * LD + c0 + li]);
 #pragma unroll
       for (int v = 0; v < 4; ++v) o.step(I[(p0 + li) * LD + p0 + 4 * v + lk], s.get(v));

@@ -118,10 +118,10 @@ MVPB_DEV void load_tiles(const GemmArgs &g, int m0, int n0, int k0, int k1, floa
 
 // Store one result: straight (with alpha, beta, the column's bias bj, ReLU)
 // or into the split's partial slice.
-MVPB_DEV void gemm_store(const GemmArgs &g, int i, int j, float acc, float bj) {
+MVPB_DEV void gemm_store(const GemmArgs &g, int z, int i, int j, float acc, float bj) {
   if (i >= g.M || j >= g.N) return;
   if (g.kchunk < g.K) {
-    g.C[((size_t)blockIdx.z * g.M + i) * g.N + j] = acc;
+    g.C[((size_t)z * g.M + i) * g.N + j] = acc;
     return;
   }
   float *c = g.C + (size_t)i * g.ldc + j;
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(256) sgemm_f32(GemmArgs g) {
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) gemm_store(g, m0 + ty + 16 * p, n0 + tx + 16 * q, acc[p][q], bj[q]);
+    for (int q = 0; q < 4; ++q) gemm_store(g, blockIdx.z, m0 + ty + 16 * p, n0 + tx + 16 * q, acc[p][q], bj[q]);
 }
 
 typedef float f4v __attribute__((ext_vector_type(4)));
@@ -236,14 +236,16 @@ MVPB_DEV void load_col8(const ConvA &cv, int dy, int dx, int c, bool in, int gk,
 // The weight gradient of the second convolution at 256 cells 53 -> 41 us (inputs
 // held as FP32 in LDS and one step's loads in flight before), fc1 of 4096 cells
 // 30 -> 15 us.
+struct GemmLds {
+  __attribute__((aligned(16))) __bf16 A[2][GBM * 40], B[2][GBN * 40];
+};
+// Tile (bx, by) of split bz.
 template <int TA, int TB, bool VEC, bool CONV>
-__global__ void __launch_bounds__(256) sgemm_bf16(GemmArgs g) {
+MVPB_DEV void gemm_bf16_tile(const GemmArgs &g, int bx, int by, int bz, GemmLds &sm) {
   static_assert(!CONV || TA == 1, "the column matrix is only read transposed");
   constexpr int BK = 32, LD = BK + 8;
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][GBM * LD];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][GBN * LD];
-  const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
-  const int kb = blockIdx.z * g.kchunk, ke = min(g.K, kb + g.kchunk);
+  const int m0 = by * GBM, n0 = bx * GBN;
+  const int kb = bz * g.kchunk, ke = min(g.K, kb + g.kchunk);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
   // this thread's entries of a step: row (column) ia (ib), eight k from ka (kb8)
@@ -272,7 +274,7 @@ __global__ void __launch_bounds__(256) sgemm_bf16(GemmArgs g) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       if (k0 + BK * u >= ke) break;
-      __bf16 *Au = As[u & 1], *Bu = Bs[u & 1];
+      __bf16 *Au = sm.A[u & 1], *Bu = sm.B[u & 1];
       *(bf8v *)&Au[ia * LD + ka] = to_bf16(va[u]);
       *(bf8v *)&Bu[ib * LD + kq] = to_bf16(vb[u]);
       lds_barrier();
@@ -299,19 +301,19 @@ __global__ void __launch_bounds__(256) sgemm_bf16(GemmArgs g) {
     for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        gemm_store(g, m0 + wr + 16 * p + 4 * (lane >> 4) + v, n0 + wc + 16 * q + (lane & 15), acc[p][q][v], bj[q]);
+        gemm_store(g, bz, m0 + wr + 16 * p + 4 * (lane >> 4) + v, n0 + wc + 16 * q + (lane & 15), acc[p][q][v], bj[q]);
+}
+
+template <int TA, int TB, bool VEC, bool CONV>
+__global__ void __launch_bounds__(256) sgemm_bf16(GemmArgs g) {
+  __shared__ GemmLds sm;
+  gemm_bf16_tile<TA, TB, VEC, CONV>(g, blockIdx.x, blockIdx.y, blockIdx.z, sm);
 }
 
 // C = act(alpha sum_z P[z] + beta C + bias), slices added in order z = 0, 1, ...
-__global__ void __launch_bounds__(256) gemm_reduce(const float *__restrict__ P, int splits, int M, int N, float alpha,
-                                                   float beta, float *__restrict__ C, int ldc,
-                                                   const float *__restrict__ bias, int relu) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= M * N) return;
-  const int i = e / N, j = e % N;
+MVPB_DEV float slice_sum(const float *__restrict__ P, int splits, size_t MN, int e) {
   // eight slices' loads in flight at a time, added in slice order
   constexpr int U = 8;
-  const size_t MN = (size_t)M * N;
   float acc = 0.f;
   int z = 0;
   for (; z + U <= splits; z += U) {
@@ -322,6 +324,15 @@ __global__ void __launch_bounds__(256) gemm_reduce(const float *__restrict__ P, 
     for (int u = 0; u < U; ++u) acc += v[u];
   }
   for (; z < splits; ++z) acc += P[(size_t)z * MN + e];
+  return acc;
+}
+__global__ void __launch_bounds__(256) gemm_reduce(const float *__restrict__ P, int splits, int M, int N, float alpha,
+                                                   float beta, float *__restrict__ C, int ldc,
+                                                   const float *__restrict__ bias, int relu) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= M * N) return;
+  const int i = e / N, j = e % N;
+  const float acc = slice_sum(P, splits, (size_t)M * N, e);
   float *c = C + (size_t)i * ldc + j;
   float v = alpha * acc + (beta != 0.f ? beta * *c : 0.f) + (bias ? bias[j] : 0.f);
   *c = relu ? fmaxf(v, 0.f) : v;
@@ -338,15 +349,21 @@ static int gemm_splits(int M, int N, int K) {
   return sp;
 }
 
+// Chunk of K of one split and the number of splits (align: the K step).
+static int gemm_chunk(int M, int N, int K, int align, size_t split_cap, int *splits) {
+  int sp = gemm_splits(M, N, K);
+  if ((size_t)sp * M * N > split_cap) sp = 1;
+  const int kchunk = sp == 1 ? K : ((K + sp - 1) / sp + align - 1) / align * align;
+  *splits = (K + kchunk - 1) / kchunk;
+  return kchunk;
+}
+
 static hipError_t gemm(bool bf16, int ta, int tb, int M, int N, int K, float alpha, const float *A, int lda,
                        const float *B, int ldb, float beta, float *C, int ldc, hipStream_t st,
                        const float *bias = nullptr, int relu = 0, float *split_buf = nullptr,
                        size_t split_cap = 0, const ConvA &conv = ConvA()) {
-  int sp = gemm_splits(M, N, K);
-  if ((size_t)sp * M * N > split_cap || !split_buf) sp = 1;
-  const int align = bf16 ? 32 : 16;
-  const int kchunk = sp == 1 ? K : ((K + sp - 1) / sp + align - 1) / align * align;
-  sp = (K + kchunk - 1) / kchunk;
+  int sp = 1;
+  const int kchunk = gemm_chunk(M, N, K, bf16 ? 32 : 16, split_buf ? split_cap : 0, &sp);
   GemmArgs g{M, N, K, alpha, beta, A, lda, B, ldb, sp == 1 ? C : split_buf, ldc, kchunk, bias, relu, conv};
   dim3 grid((N + GBN - 1) / GBN, (M + GBM - 1) / GBM, sp);
   if (bf16) {
@@ -357,7 +374,7 @@ static hipError_t gemm(bool bf16, int ta, int tb, int M, int N, int K, float alp
     };
     const bool vec = ok(ta == 0, A, lda) && ok(tb == 1, B, ldb);
 #define MVPB_GEMM_CASE(TA, TB)                                                            \
-  if (ta == TA && tb == TB && !conv.in) {                                                 \
+  if (ta == TA && tb == TB) {                                                 \
     if (vec)                                                                              \
       hipLaunchKernelGGL((sgemm_bf16<TA, TB, true, false>), grid, dim3(256), 0, st, g);   \
     else                                                                                  \
@@ -367,7 +384,6 @@ static hipError_t gemm(bool bf16, int ta, int tb, int M, int N, int K, float alp
     MVPB_GEMM_CASE(0, 1)
     MVPB_GEMM_CASE(1, 0)
 #undef MVPB_GEMM_CASE
-    if (conv.in) hipLaunchKernelGGL((sgemm_bf16<1, 0, false, true>), grid, dim3(256), 0, st, g);
   } else {
 #define MVPB_GEMM_CASE(TA, TB) \
   if (ta == TA && tb == TB) hipLaunchKernelGGL((sgemm_f32<TA, TB>), grid, dim3(256), 0, st, g);
@@ -521,7 +537,7 @@ __global__ void __launch_bounds__(512) conv_chain(ConvChain c) {
 // below).  One wavefront per 16 output pixels: the pixel's own and its right, lower
 // and diagonal neighbours' dz serve the four input pixels of its 2 x 2 cell, one,
 // two, two and four taps.  Bound by writing da.  256 cells,
-// grid 32: 29 us, before (product to a column buffer, gather, mask) 140 us.
+// grid 32: 23 us, before (product to a column buffer, gather, mask) 140 us.
 struct ConvDx {
   const float *dz, *W, *act;
   float *da;
@@ -627,15 +643,15 @@ __global__ void relu_mask(float *__restrict__ d, const float *__restrict__ a, si
 
 // Partial column sums: block (x, y) sums rows y, y + gridDim.y, ... of the
 // 64-column slab x into part[y][c]; column_sums_fin adds the parts in order.
-__global__ void __launch_bounds__(256) column_sums(const float *__restrict__ d, size_t rows, int C,
-                                                   float *__restrict__ part) {
+MVPB_DEV void column_part(const float *__restrict__ d, size_t rows, int C, float *__restrict__ part, int slab, int y,
+                          int parts) {
   __shared__ float red[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
+  const int c = slab * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
   float acc = 0.f;
   if (c < C) {
     // eight rows' loads in flight at a time, added in row order
     constexpr int U = 8;
-    const size_t r0 = (size_t)blockIdx.y * 4 + g, step = (size_t)gridDim.y * 4;
+    const size_t r0 = (size_t)y * 4 + g, step = (size_t)parts * 4;
     size_t r = r0;
     for (; r + (U - 1) * step < rows; r += U * step) {
       float v[U];
@@ -648,13 +664,15 @@ __global__ void __launch_bounds__(256) column_sums(const float *__restrict__ d, 
   }
   red[g][threadIdx.x & 63] = acc;
   __syncthreads();
-  if (g == 0 && c < C) part[(size_t)blockIdx.y * C + c] = red[0][threadIdx.x] + red[1][threadIdx.x] +
-                                                           red[2][threadIdx.x] + red[3][threadIdx.x];
+  if (g == 0 && c < C) part[(size_t)y * C + c] = red[0][threadIdx.x] + red[1][threadIdx.x] +
+                                                 red[2][threadIdx.x] + red[3][threadIdx.x];
+}
+__global__ void __launch_bounds__(256) column_sums(const float *__restrict__ d, size_t rows, int C,
+                                                   float *__restrict__ part) {
+  column_part(d, rows, C, part, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
-__global__ void column_sums_fin(const float *__restrict__ part, int parts, int C, float *__restrict__ db) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
+MVPB_DEV float part_sum(const float *__restrict__ part, int parts, int C, int c) {
   // eight parts' loads in flight at a time, added in part order
   constexpr int U = 8;
   float acc = 0.f;
@@ -667,7 +685,43 @@ __global__ void column_sums_fin(const float *__restrict__ part, int parts, int C
     for (int u = 0; u < U; ++u) acc += v[u];
   }
   for (; p < parts; ++p) acc += part[(size_t)p * C + c];
-  db[c] = acc;
+  return acc;
+}
+__global__ void column_sums_fin(const float *__restrict__ part, int parts, int C, float *__restrict__ db) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < C) db[c] = part_sum(part, parts, C, c);
+}
+
+// The weight and bias gradients of the four convolutions, BF16 products: with dz of
+// every layer at hand, one launch for all partial sums and one for their sums in
+// order, instead of four launches per layer of which no weight gradient but one
+// fills the chip (256 cells: 20, 80, 320 and 128 workgroups of 33 to 61 us each).
+// Workgroups of the first launch: the tiles and splits of each layer's product, then
+// the row blocks of each layer's bias gradient.  At 256 cells 71 + 14 us
+// against 245 us of the sixteen.
+struct ConvGrads {
+  GemmArgs g[4];         // C: the layer's partial slices, or dW itself when not split
+  int splits[4], tiles[4];
+  const float *dz[4];
+  float *part[4];        // partial column sums
+  int rows[4], parts[4];
+  float *dW[4], *db[4];
+  int end[8];            // of each layer's workgroups, products then row blocks
+};
+__global__ void __launch_bounds__(256) conv_grads(ConvGrads c) {
+  __shared__ GemmLds sm;
+  int q = 0;
+  while ((int)blockIdx.x >= c.end[q]) ++q;   // the grid is c.end[7]
+  const int l = q & 3, r = blockIdx.x - (q > 0 ? c.end[q - 1] : 0);
+  if (q < 4)
+    gemm_bf16_tile<1, 0, false, true>(c.g[l], 0, r % c.tiles[l], r / c.tiles[l], sm);
+  else
+    column_part(c.dz[l], (size_t)c.rows[l], 32, c.part[l], 0, r, c.parts[l]);
+}
+__global__ void __launch_bounds__(256) conv_grads_fin(ConvGrads c) {
+  const int l = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x, mn = c.g[l].M * 32;
+  if (e < mn && c.splits[l] > 1) c.dW[l][e] = slice_sum(c.g[l].C, c.splits[l], (size_t)mn, e);
+  if (blockIdx.x == 0 && threadIdx.x < 32) c.db[l][threadIdx.x] = part_sum(c.part[l], c.parts[l], 32, threadIdx.x);
 }
 
 // dout = 2 (out - y) / n and per-block partial sums of (out - y)^2
@@ -727,7 +781,7 @@ struct Layer {
 };
 const Layer kConv[4] = {{1, 32, 1, 32, 32}, {32, 32, 2, 32, 32}, {32, 32, 2, 16, 16}, {32, 32, 2, 8, 8}};
 constexpr int kFcIn = 512, kFcHid = 256, kOut = 400, kPix = 32 * 32;
-constexpr size_t kSplitCap = (size_t)2 << 20;   // floats of split-K partial slices
+constexpr size_t kSplitCap = (size_t)3 << 20;   // floats of split-K partial slices (of the convolutions together 2.9 M at most)
 constexpr int kColParts = 256;                  // row blocks of the bias-gradient sums
 
 int param_offsets(int *off) {  // 12 tensors
@@ -813,8 +867,9 @@ static ConvA conv_operand(const Layer &L, const float *in) {
 }
 
 // db[c] = sum over rows of d[r][c] (blocks of rows, then the blocks in order).
+static int col_parts(size_t rows) { return (int)std::min<size_t>(kColParts, (rows + 511) / 512); }
 static void col_sums(mvpb_sur net, const float *d, size_t rows, int C, float *db) {
-  const int parts = (int)std::min<size_t>(kColParts, (rows + 511) / 512);
+  const int parts = col_parts(rows);
   hipLaunchKernelGGL(column_sums, dim3((C + 63) / 64, parts), dim3(256), 0, net->st, d, rows, C, net->colpart.p);
   hipLaunchKernelGGL(column_sums_fin, dim3((C + 255) / 256), dim3(256), 0, net->st, net->colpart.p, parts, C, db);
 }
@@ -871,9 +926,48 @@ static int sur_backward(mvpb_sur net, int B) {
   if (e == hipSuccess)
     e = net_gemm(net, 1, 0, kFcIn, kFcHid, B, net->act[4].p, kFcIn, net->dh.p, kFcHid, G + net->off[8], kFcHid);
   col_sums(net, net->dh.p, (size_t)B, kFcHid, G + net->off[9]);
+  // BF16: dz of the first layer in dact, of the others in dact2; else the two in turn
+  float *dz[4] = {net->dact.p, net->dact2.p, net->dact2.p + (size_t)B * 8192, net->dact2.p + (size_t)B * 10240};
   if (e == hipSuccess)
-    e = net_gemm(net, 0, 1, B, kFcIn, kFcHid, net->dh.p, kFcHid, P + net->off[8], kFcHid, net->dact.p, kFcIn);
+    e = net_gemm(net, 0, 1, B, kFcIn, kFcHid, net->dh.p, kFcHid, P + net->off[8], kFcHid,
+                 net->bf16 ? dz[3] : net->dact.p, kFcIn);
   if (e != hipSuccess) return set_error(MVPB_E_DEVICE, "surrogate backward: %s", hipGetErrorString(e));
+  if (net->bf16) {
+    hipLaunchKernelGGL(relu_mask, dim3((B * kFcIn + 255) / 256), dim3(256), 0, st, dz[3], net->act[4].p,
+                       (size_t)B * kFcIn);
+    ConvGrads c{};
+    size_t slices = 0;
+    for (int l = 3; l >= 0; --l) {
+      const Layer &L = kConv[l];
+      const int rows = B * (L.H / L.s) * (L.W / L.s), K = 9 * L.ci;
+      if (l > 0) {
+        ConvDx x{dz[l], P + net->off[2 * l], net->act[l].p, dz[l - 1], rows / 16, ilog2_exact(L.H)};
+        hipLaunchKernelGGL(conv_dx, dim3(std::min((x.tiles + 3) / 4, 512)), dim3(256), 0, st, x);
+      }
+      int sp = 1;
+      const int kchunk = gemm_chunk(K, L.co, rows, 32, net->split.n, &sp);
+      c.dW[l] = G + net->off[2 * l];
+      c.db[l] = G + net->off[2 * l + 1];
+      c.g[l] = GemmArgs{K, L.co, rows, 1.f, 0.f, nullptr, K, dz[l], L.co, sp > 1 ? net->split.p + slices : c.dW[l], L.co,
+                        kchunk, nullptr, 0, conv_operand(L, net->act[l].p)};
+      if (sp > 1) slices += (size_t)sp * K * L.co;
+      c.splits[l] = sp;
+      c.tiles[l] = (K + GBM - 1) / GBM;
+      c.dz[l] = dz[l];
+      c.part[l] = net->colpart.p + (size_t)l * kColParts * L.co;
+      c.rows[l] = rows;
+      c.parts[l] = col_parts(rows);
+    }
+    if (slices > net->split.n) return set_error(MVPB_E_DEVICE, "internal: %zu floats of partial sums", slices);
+    int end = 0;
+    for (int l = 0; l < 4; ++l) c.end[l] = end += c.splits[l] * c.tiles[l];
+    for (int l = 0; l < 4; ++l) c.end[4 + l] = end += c.parts[l];
+    hipLaunchKernelGGL(conv_grads, dim3(end), dim3(256), 0, st, c);
+    hipLaunchKernelGGL(conv_grads_fin, dim3((9 * 32 * 32 + 255) / 256, 4), dim3(256), 0, st, c);
+    e = hipGetLastError();
+    if (e != hipSuccess) return set_error(MVPB_E_DEVICE, "surrogate backward: %s", hipGetErrorString(e));
+    return MVPB_OK;
+  }
   float *da = net->dact.p, *da_next = net->dact2.p;
   for (int l = 3; l >= 0; --l) {
     const Layer &L = kConv[l];
@@ -881,18 +975,13 @@ static int sur_backward(mvpb_sur net, int B) {
     const size_t rows = (size_t)B * Ho * Wo;
     const int K = 9 * L.ci;
     // dz = da * relu'(act[l+1])
-    if (!net->bf16 || l == 3)   // else masked by the layer above
-      hipLaunchKernelGGL(relu_mask, dim3((unsigned)std::min<size_t>((rows * L.co + 255) / 256, 65535)), dim3(256), 0, st,
+    hipLaunchKernelGGL(relu_mask, dim3((unsigned)std::min<size_t>((rows * L.co + 255) / 256, 65535)), dim3(256), 0, st,
                        da, net->act[l + 1].p, rows * L.co);
     // dW = col^T dz over the implicit column matrix (split over the output pixels), db = column sums of dz
     e = net_gemm(net, 1, 0, K, L.co, (int)rows, nullptr, K, da, L.co, G + net->off[2 * l], L.co, nullptr, 0,
                  conv_operand(L, net->act[l].p));
     col_sums(net, da, rows, L.co, G + net->off[2 * l + 1]);
-    if (l > 0 && e == hipSuccess && net->bf16) {
-      ConvDx c{da, P + net->off[2 * l], net->act[l].p, da_next, (int)(rows / 16), ilog2_exact(L.H)};
-      hipLaunchKernelGGL(conv_dx, dim3(std::min((c.tiles + 3) / 4, 512)), dim3(256), 0, st, c);
-      std::swap(da, da_next);
-    } else if (l > 0 && e == hipSuccess) {
+    if (l > 0 && e == hipSuccess) {
       // dcol = dz W^T, then gather back onto the input pixels
       e = net_gemm(net, 0, 1, (int)rows, K, L.co, da, L.co, P + net->off[2 * l], L.co, net->dcol.p, K);
       const size_t tin = (size_t)B * L.H * L.W * L.ci;
