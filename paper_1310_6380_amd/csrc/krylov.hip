@@ -21,8 +21,8 @@
 // grow like a power of the frequency), and every item checks it: an item that
 // misses the bar is solved again, with more steps or by the reduction.
 // Measured, plan build included, against the reduction: 60 points of 2N = 882,
-// 18 bands, 20.4 -> 10.8 ms; 60 points of 2N = 1922, 24 bands, 123.6 -> 45.7 ms;
-// 960 points of 2N = 242 .. 1250, 10 bands, 229 -> 95.6 ms.
+// 18 bands, 20.3 -> 10.4 ms; 60 points of 2N = 1922, 24 bands, 123.6 -> 44.6 ms;
+// 960 points of 2N = 242 .. 1250, 10 bands, 228 -> 95.9 ms.
 #include <float.h>
 
 #include <algorithm>

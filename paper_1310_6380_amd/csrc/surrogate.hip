@@ -5,16 +5,17 @@
 //   conv1 3x3  1->32 s1, conv2..4 3x3 32->32 s2 (circular padding, ReLU)
 //   flatten 4x4x32 = 512 -> fc1 256 (ReLU) -> fc2 400, mean squared error.
 //
-// Activations are NHWC FP32; a convolution is one GEMM whose A operand is
-// the implicit im2col of its input (the tile loads gather the taps straight
-// from the activations, circular padding, power-of-two grids), also for the
-// weight gradients; the backward data pass is a GEMM into a column buffer
-// and a gather col2im (every input pixel collects its taps, so no atomics
-// and bitwise-reproducible results).  GEMMs run either as FP32 FMA
-// tiles or on the matrix cores with BF16 inputs and FP32 accumulation
-// (v_mfma_f32_16x16x32_bf16), bias and ReLU applied in the GEMM epilogue,
-// long reductions split over workgroups; master weights and Adam moments
-// stay FP32.
+// Activations are NHWC FP32.  With FP32 products a convolution is one GEMM of FMA
+// tiles whose A operand is the implicit im2col of its input (the tile loads gather
+// the taps straight from the activations, circular padding, power-of-two grids),
+// also for the weight gradients; the backward data pass is a GEMM into a column
+// buffer and a gather col2im (every input pixel collects its taps, so no atomics
+// and bitwise-reproducible results).  With BF16 products and FP32 accumulation
+// (v_mfma_f32_16x16x32_bf16) the four convolutions of a cell run in one workgroup
+// (conv_chain), the data pass gathers its taps directly (conv_dx), the gradients of
+// all four layers share a launch (conv_grads), and the fully connected layers are
+// GEMMs.  Bias and ReLU are applied in the epilogues, long reductions split over
+// workgroups; master weights and Adam moments stay FP32.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -184,14 +185,14 @@ MVPB_DEV bf8v to_bf16(const float (&v)[8]) {
 }
 
 // Eight consecutive k (from gk) of one row of op(A) or column of op(B), zero
-// outside.  KC: k contiguous in memory, with VEC (base, leading dimension and K
-// allow it; all eight or none then exist) read as two vectors; else one load per
+// outside.  KC: k contiguous in memory, read as two vectors (base, leading
+// dimension and K allow it, see gemm: all eight or none exist); else one load per
 // k, consecutive threads on consecutive rows.  No branches: a load under one is
 // waited for where the paths meet.
-template <bool KC, bool VEC>
+template <bool KC>
 MVPB_DEV void load_k8(const float *__restrict__ p, int ld, int row, int rows, int gk, int k1, float (&v)[8]) {
   const bool in = row < rows;
-  if constexpr (KC && VEC) {
+  if constexpr (KC) {
     const bool ok = in && gk < k1;
     const size_t x = ok ? (size_t)row * ld + gk : 0;
     const f4v a = gld4(p, x), b = gld4(p, ok ? x + 4 : 0);
@@ -204,7 +205,7 @@ MVPB_DEV void load_k8(const float *__restrict__ p, int ld, int row, int rows, in
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const bool ok = in && gk + u < k1;
-      const float x = gld(p, ok ? (KC ? (size_t)row * ld + gk + u : (size_t)(gk + u) * ld + row) : 0);
+      const float x = gld(p, ok ? (size_t)(gk + u) * ld + row : 0);
       v[u] = ok ? x : 0.f;
     }
   }
@@ -240,7 +241,7 @@ struct GemmLds {
   __attribute__((aligned(16))) __bf16 A[2][GBM * 40], B[2][GBN * 40];
 };
 // Tile (bx, by) of split bz.
-template <int TA, int TB, bool VEC, bool CONV>
+template <int TA, int TB, bool CONV>
 MVPB_DEV void gemm_bf16_tile(const GemmArgs &g, int bx, int by, int bz, GemmLds &sm) {
   static_assert(!CONV || TA == 1, "the column matrix is only read transposed");
   constexpr int BK = 32, LD = BK + 8;
@@ -260,8 +261,8 @@ MVPB_DEV void gemm_bf16_tile(const GemmArgs &g, int bx, int by, int bz, GemmLds 
     if constexpr (CONV)
       load_col8(g.conv, dy, dx, ci, m0 + ia < g.M, k0 + ka, ke, va);
     else
-      load_k8<KA, VEC>(g.A, g.lda, m0 + ia, g.M, k0 + ka, ke, va);
-    load_k8<KBC, VEC>(g.B, g.ldb, n0 + ib, g.N, k0 + kq, ke, vb);
+      load_k8<KA>(g.A, g.lda, m0 + ia, g.M, k0 + ka, ke, va);
+    load_k8<KBC>(g.B, g.ldb, n0 + ib, g.N, k0 + kq, ke, vb);
   };
   f4v acc[2][2];
 #pragma unroll
@@ -304,10 +305,10 @@ MVPB_DEV void gemm_bf16_tile(const GemmArgs &g, int bx, int by, int bz, GemmLds 
         gemm_store(g, bz, m0 + wr + 16 * p + 4 * (lane >> 4) + v, n0 + wc + 16 * q + (lane & 15), acc[p][q][v], bj[q]);
 }
 
-template <int TA, int TB, bool VEC, bool CONV>
+template <int TA, int TB>
 __global__ void __launch_bounds__(256) sgemm_bf16(GemmArgs g) {
   __shared__ GemmLds sm;
-  gemm_bf16_tile<TA, TB, VEC, CONV>(g, blockIdx.x, blockIdx.y, blockIdx.z, sm);
+  gemm_bf16_tile<TA, TB, false>(g, blockIdx.x, blockIdx.y, blockIdx.z, sm);
 }
 
 // C = act(alpha sum_z P[z] + beta C + bias), slices added in order z = 0, 1, ...
@@ -367,19 +368,14 @@ static hipError_t gemm(bool bf16, int ta, int tb, int M, int N, int K, float alp
   GemmArgs g{M, N, K, alpha, beta, A, lda, B, ldb, sp == 1 ? C : split_buf, ldc, kchunk, bias, relu, conv};
   dim3 grid((N + GBN - 1) / GBN, (M + GBM - 1) / GBM, sp);
   if (bf16) {
-    // 16-byte reads along k where every operand that has k contiguous allows them
-    // (splits are multiples of 32)
+    // 16-byte reads along k of the operands that have it contiguous (splits are
+    // multiples of 32); the convolutions have kernels of their own
     auto ok = [&](bool along, const float *p, int ld) {
       return !along || (ld % 4 == 0 && K % 8 == 0 && (uintptr_t)p % 16 == 0);
     };
-    const bool vec = ok(ta == 0, A, lda) && ok(tb == 1, B, ldb);
-#define MVPB_GEMM_CASE(TA, TB)                                                            \
-  if (ta == TA && tb == TB) {                                                 \
-    if (vec)                                                                              \
-      hipLaunchKernelGGL((sgemm_bf16<TA, TB, true, false>), grid, dim3(256), 0, st, g);   \
-    else                                                                                  \
-      hipLaunchKernelGGL((sgemm_bf16<TA, TB, false, false>), grid, dim3(256), 0, st, g);  \
-  }
+    if (conv.in || !ok(ta == 0, A, lda) || !ok(tb == 1, B, ldb)) return hipErrorInvalidValue;
+#define MVPB_GEMM_CASE(TA, TB) \
+  if (ta == TA && tb == TB) hipLaunchKernelGGL((sgemm_bf16<TA, TB>), grid, dim3(256), 0, st, g);
     MVPB_GEMM_CASE(0, 0)
     MVPB_GEMM_CASE(0, 1)
     MVPB_GEMM_CASE(1, 0)
@@ -714,7 +710,7 @@ __global__ void __launch_bounds__(256) conv_grads(ConvGrads c) {
   while ((int)blockIdx.x >= c.end[q]) ++q;   // the grid is c.end[7]
   const int l = q & 3, r = blockIdx.x - (q > 0 ? c.end[q - 1] : 0);
   if (q < 4)
-    gemm_bf16_tile<1, 0, false, true>(c.g[l], 0, r % c.tiles[l], r / c.tiles[l], sm);
+    gemm_bf16_tile<1, 0, true>(c.g[l], 0, r % c.tiles[l], r / c.tiles[l], sm);
   else
     column_part(c.dz[l], (size_t)c.rows[l], 32, c.part[l], 0, r, c.parts[l]);
 }
