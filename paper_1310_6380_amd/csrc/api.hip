@@ -263,6 +263,7 @@ struct mvpb_cell_s {
   bool general = false; // compliance given as a full matrix or spatial cell: only the general plan applies
   int nf = 0;           // weight fields of the general structure factors
   DevBuf gwtab;         // double [n_phases][nf]: Voigt compliance (upper triangle), rho (pixel/voxel cells)
+  KryMedium medium;
 };
 
 struct mvpb_plan_s {
@@ -281,6 +282,7 @@ struct mvpb_plan_s {
   double T3[9] = {}; // A^-1 row-major, qdim x qdim packed
   DevBuf linvPhi;    // general layout: L_Phi^-1 (nsig x nsig)
   int gx = 0, gy = 0, gz = 0;   // pixel / voxel grid of the cell (0: polygon cell)
+  KryMedium medium;  // of the cell
 };
 
 namespace mvpb {
@@ -463,6 +465,42 @@ static int general_weight_table(int dim, int n_phases, int prop_kind, const doub
   return MVPB_OK;
 }
 
+// KryMedium of a cell from its phases' weights (gw: general_weight_table) and their
+// shares of the cell; the isotropic average of an anisotropic mean is that of the
+// compliances.  Where heavy parts are stiff and light ones soft, the product of the
+// means of density and compliance is far above the mean of their product, and the
+// start block holds little of the modes in the light parts: each factor of four
+// costs about one step.
+static KryMedium mean_slowness(int dim, const std::vector<double> &gw, const std::vector<double> &share) {
+  const int ns = dim == 2 ? 3 : 6, nt = ns * (ns + 1) / 2, nf = nt + 1;
+  double S[6][6] = {}, sum = 0.0, rho = 0.0, trace = 0.0, mean = 0.0;
+  for (double v : share) sum += v;
+  for (size_t p = 0; p < share.size(); ++p) {
+    const double *w = gw.data() + p * nf, f = share[p] / sum;
+    rho += f * w[nt];
+    for (int a = 0, k = 0; a < ns; ++a)
+      for (int b = a; b < ns; ++b, ++k) {
+        S[a][b] += f * w[nt] * w[k];
+        if (a == b) {
+          trace += f * w[k];
+          mean += f * w[nt] * w[k];
+        }
+      }
+  }
+  KryMedium m;
+  if (dim == 2) {
+    m.ct2 = 2.0 / (S[0][0] + S[1][1] - 2.0 * S[0][1] + S[2][2]);
+    m.cl2 = m.ct2 + 1.0 / (S[0][0] + S[1][1] + 2.0 * S[0][1]);
+  } else {
+    const double diag = S[0][0] + S[1][1] + S[2][2], off = S[0][1] + S[0][2] + S[1][2];
+    m.ct2 = 15.0 / (4.0 * (diag - off) + 3.0 * (S[3][3] + S[4][4] + S[5][5]));
+    m.cl2 = 4.0 / 3.0 * m.ct2 + 1.0 / (diag + 2.0 * off);
+  }
+  const double g = rho * trace / mean;
+  if (g >= 4.0) m.extra = (int)std::min(4.0, floor(log(g) / log(4.0)));
+  return m;
+}
+
 static int prop_stride(int dim, int prop_kind) {
   if (prop_kind == MVPB_PROP_ISO_E_NU_RHO) return 3;
   return dim == 2 ? 7 : 22;
@@ -480,9 +518,12 @@ extern "C" int mvpb_cell_create_pixels(mvpb_ctx ctx, const double lattice[4], in
     return set_err(MVPB_E_UNSUPPORTED, "property kind %d not supported", prop_kind);
   double T[4], area;
   if (!lattice_ok(lattice, T, &area)) return set_err(MVPB_E_INVALID, "degenerate or non-finite lattice");
-  for (size_t i = 0; i < (size_t)nx * ny; ++i)
+  std::vector<double> share(n_phases, 0.0);
+  for (size_t i = 0; i < (size_t)nx * ny; ++i) {
     if (phase[i] < 0 || phase[i] >= n_phases)
       return set_err(MVPB_E_INVALID, "phase id %d at pixel %zu out of range [0,%d)", phase[i], i, n_phases);
+    share[phase[i]] += 1.0;
+  }
   const bool iso = prop_kind == MVPB_PROP_ISO_E_NU_RHO;
   std::vector<double> w, gw;
   if (iso) {
@@ -504,6 +545,7 @@ extern "C" int mvpb_cell_create_pixels(mvpb_ctx ctx, const double lattice[4], in
   c->n_phases = n_phases;
   c->general = !iso;
   c->nf = nf;
+  c->medium = mean_slowness(2, gw, share);
   c->phase.pool = &ctx->pool;
   c->wtab.pool = &ctx->pool;
   c->gwtab.pool = &ctx->pool;
@@ -561,9 +603,12 @@ extern "C" int mvpb_cell_create_voxels(mvpb_ctx ctx, const double lattice[9], in
   double T[9], vol;
   if (!lattice3_ok(lattice, T, &vol)) return set_err(MVPB_E_INVALID, "degenerate or non-finite lattice");
   const size_t nvox = (size_t)nx * ny * nz;
-  for (size_t i = 0; i < nvox; ++i)
+  std::vector<double> share(n_phases, 0.0);
+  for (size_t i = 0; i < nvox; ++i) {
     if (phase[i] < 0 || phase[i] >= n_phases)
       return set_err(MVPB_E_INVALID, "phase id %d at voxel %zu out of range [0,%d)", phase[i], i, n_phases);
+    share[phase[i]] += 1.0;
+  }
   std::vector<double> gw;
   int nf = 0;
   rc = general_weight_table(3, n_phases, prop_kind, props, gw, &nf);
@@ -580,6 +625,7 @@ extern "C" int mvpb_cell_create_voxels(mvpb_ctx ctx, const double lattice[9], in
   c->n_phases = n_phases;
   c->general = true;
   c->nf = nf;
+  c->medium = mean_slowness(3, gw, share);
   c->phase.pool = &ctx->pool;
   c->gwtab.pool = &ctx->pool;
   hipError_t e = c->phase.alloc(sizeof(int32_t) * nvox);
@@ -642,8 +688,11 @@ extern "C" int mvpb_cell_create_polygons(mvpb_ctx ctx, const double lattice[4], 
                    area);
   for (int p = 0; p < n_phases; ++p)
     if (aph[p] < -tol) return set_err(MVPB_E_INVALID, "phase %d has negative signed area %.6g", p, aph[p]);
-  std::vector<double> w;
+  std::vector<double> w, gw;
   rc = phase_weight_table(n_phases, props, w);
+  if (rc) return rc;
+  int nf = 0;
+  rc = general_weight_table(2, n_phases, prop_kind, props, gw, &nf);
   if (rc) return rc;
   HIP_TRY(hipSetDevice(ctx->device));
   mvpb_cell c = new mvpb_cell_s();
@@ -653,6 +702,7 @@ extern "C" int mvpb_cell_create_polygons(mvpb_ctx ctx, const double lattice[4], 
   c->area = area;
   c->n_phases = n_phases;
   c->polygons = true;
+  c->medium = mean_slowness(2, gw, aph);
   c->n_edges = (int)ep.size();
   for (int k = 0; k < 4; ++k) {
     double f = 0.0;
@@ -1023,6 +1073,7 @@ static int build_plan_group(mvpb_ctx ctx, const mvpb_cell *cells, int g, int M1,
     memcpy(pl->T, cells[c]->T, sizeof pl->T);
     memcpy(pl->T3, cells[c]->T, sizeof pl->T);
     pl->area = cells[c]->area;
+    pl->medium = cells[c]->medium;
     pl->coef.pool = &ctx->pool;
     pl->linvR.pool = &ctx->pool;
     pl->linvSD.pool = &ctx->pool;
@@ -1252,6 +1303,7 @@ static int build_plan_general(mvpb_cell c, int M1, int M2, int M3, int precision
   pl->gz = c->nz;
   memcpy(pl->T, c->T, sizeof pl->T);
   memcpy(pl->T3, c->T3, sizeof pl->T3);
+  pl->medium = c->medium;
   ctx->children++;
   *out = pl.release();
   return MVPB_OK;
@@ -1436,9 +1488,8 @@ struct Route {
 };
 
 // Attempts at a set of points: the Krylov route, the points whose pairs miss its
-// bar (about one cell in sixty of the inclusion study, those with stiffness
-// ratios near 100) with RETRY_STEPS more, and what is left by the reduction.
-// Without a caller that waits for the results only the last.
+// bar with RETRY_STEPS more, and what is left by the reduction.  Without a caller
+// that waits for the results only the last.
 enum Attempt { TRY_KRYLOV = 0, TRY_LONGER, TRY_REDUCTION };
 constexpr int RETRY_STEPS = 4;
 
@@ -1454,10 +1505,10 @@ constexpr int RETRY_STEPS = 4;
 // most where the next value is close), a mode's is the residual over the relative
 // gap.  A bar of 3e-8 sends more points into a second attempt: small cells of
 // stiffness ratio near 100 4.05 -> 5.11 and 6.80 -> 7.80 ms, for errors of 2e-13.
-static Route krylov_route(int n, int nb, int dim, bool fp32, bool modes, Attempt at) {
+static Route krylov_route(int n, int nb, int dim, int extra, bool fp32, bool modes, Attempt at) {
   Route rt;
   if (fp32 || nb > RR_MAX_BANDS || at == TRY_REDUCTION) return rt;
-  int s = krylov_steps(nb, dim, modes);
+  int s = krylov_steps(nb, dim, modes) + extra;
   if (s + RETRY_STEPS > KRY_MAX_STEPS || 20 * HB * s > 17 * n) return rt;
   if (at == TRY_LONGER && 10 * HB * (s += RETRY_STEPS) > 9 * n) return rt;
   rt.steps = s;
@@ -1468,8 +1519,8 @@ static Route krylov_route(int n, int nb, int dim, bool fp32, bool modes, Attempt
 // What an operator of order n is solved by (0 and -1 the reductions, else the
 // Krylov steps): the operators of one launch sequence share it, so that a point
 // takes the same route alone and among others.
-static int route_class(int n, int nb, int dim, bool fp32, bool modes, Attempt at) {
-  return !fp32 && n <= SMALL_MAX_N ? -1 : krylov_route(n, nb, dim, fp32, modes, at).steps;
+static int route_class(int n, int nb, int dim, int extra, bool fp32, bool modes, Attempt at) {
+  return !fp32 && n <= SMALL_MAX_N ? -1 : krylov_route(n, nb, dim, extra, fp32, modes, at).steps;
 }
 
 // Sizes of the per-item buffers of the Krylov route (the projection's own item
@@ -1485,7 +1536,7 @@ static void krylov_layout(int n, int nb, int steps, size_t *sz, int *count) {
   sz[k++] = sizeof(cd) * npad * HB;                  // Z
   sz[k++] = sizeof(cd) * (size_t)steps * HB * HB;    // P
   sz[k++] = sizeof(cd) * nch * HB * HB;              // G
-  sz[k++] = 2 * sizeof(double);                      // shift, status
+  sz[k++] = sizeof(int);                             // status
   sz[k++] = sizeof(int) * 2;                         // flag
   sz[k++] = sizeof(double) * nb;                     // lam
   sz[k++] = sizeof(double) * nb;                     // omega
@@ -1559,12 +1610,33 @@ static EigItem carve_item(char *base, int n, int nb, bool fp32) {
   return it;
 }
 
+// Where an item's operator comes from: displacement components, cutoffs, A^-1 (d x d
+// packed), Cartesian Bloch vector 2 pi T Q, medium.
+struct Origin {
+  int d, M1, M2, M3;
+  const double *T;
+  double kap[3];
+  const KryMedium *medium;
+};
+
 // Carve item i of a table of n_items (host image `table`, bytes as
 // table_bytes) from `base`; returns the item for the caller to fill in the
-// operator's fields (put_item).
-static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Route &rt, size_t n_items, size_t i,
-                                char *table) {
-  if (!rt.steps) return carve_item(base, n, nb, fp32);
+// operator's other fields (put_item).
+static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Origin &og, const Route &rt, size_t n_items,
+                                size_t i, char *table) {
+  auto operator_of = [&](EigItem &it) {
+    it.kap1 = og.kap[0];
+    it.kap2 = og.kap[1];
+    it.kap3 = og.kap[2];
+    it.n = n;
+    it.nb = nb;
+    it.N = n / og.d;
+  };
+  if (!rt.steps) {
+    EigItem it = carve_item(base, n, nb, fp32);
+    operator_of(it);
+    return it;
+  }
   size_t sz[32];
   int cnt = 0;
   krylov_layout(n, nb, rt.steps, sz, &cnt);
@@ -1587,8 +1659,8 @@ static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Rout
   ky.Z = (cd *)take();
   ky.P = (cd *)take();
   ky.G = (cd *)take();
-  ky.sigma = (double *)take();
-  ky.status = (int *)(ky.sigma + 1);
+  ky.weight = (double *)ky.W;
+  ky.status = (int *)take();
   it.flag = (int *)take();
   it.lam = (double *)take();
   it.omega = (double *)take();
@@ -1598,6 +1670,16 @@ static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Rout
   it.Lr = (cd *)take();
   it.acc = (double *)take();
   it.Yb = it.Y;
+  operator_of(it);
+  ky.d = og.d;
+  ky.M1 = og.M1;
+  ky.M2 = og.M2;
+  ky.M3 = og.M3;
+  for (int l = 0; l < og.d; ++l)
+    for (int c = 0; c < og.d; ++c) ky.B[3 * l + c] = 2.0 * M_PI * og.T[l * og.d + c];
+  memcpy(ky.kap, og.kap, sizeof ky.kap);
+  ky.ct2 = og.medium->ct2;
+  ky.cl2 = og.medium->cl2;
   const int m = HB * rt.steps;
   EigItem sm = carve_item(base + o, m, nb, false);
   sm.n = m;
@@ -1878,25 +1960,17 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
   for (int i = 0; i < n_items; ++i) {
     const Job &j = jobs[i];
     const int n = j.plan->n;
-    EigItem it = carve_route_item(ctx->ws.as<char>() + off, n, nb, fp32, rt, n_items, i, table.data());
+    const int qd = j.plan->qdim;
+    const double q[3] = {j.Q1, j.Q2, j.Q3};
+    Origin og{qd, j.plan->M1, j.plan->M2, j.plan->M3, j.plan->T3, {0.0, 0.0, 0.0}, &j.plan->medium};
+    for (int l = 0; l < qd; ++l)
+      for (int m = 0; m < qd; ++m) og.kap[l] += 2.0 * M_PI * og.T[l * qd + m] * q[m];
+    EigItem it = carve_route_item(ctx->ws.as<char>() + off, n, nb, fp32, og, rt, n_items, i, table.data());
     off += route_item_bytes(n, nb, fp32, rt);
     it.coef = j.plan->coef.as<cd>();
-    it.N = j.plan->N;
-    it.n = n;
     it.dim = j.plan->dim;
     it.check = fp32 ? 1 : 0;
-    it.nb = nb;
     it.slot = j.out_index;
-    // kappa = 2 pi T Q (Cartesian Bloch vector)
-    const int qd = j.plan->qdim;
-    const double *T = j.plan->T3;
-    const double q[3] = {j.Q1, j.Q2, j.Q3};
-    double kap[3] = {0.0, 0.0, 0.0};
-    for (int l = 0; l < qd; ++l)
-      for (int m = 0; m < qd; ++m) kap[l] += 2.0 * M_PI * T[l * qd + m] * q[m];
-    it.kap1 = kap[0];
-    it.kap2 = kap[1];
-    it.kap3 = kap[2];
     put_item(table.data(), i, it);
     vecs[i] = nb <= RR_MAX_BANDS ? it.Z : it.Y;
   }
@@ -2184,10 +2258,12 @@ static int run_sorted(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double
   for (size_t j0 = 0, j1 = 0; j0 < jobs.size(); j0 = j1) {
     const int n0 = jobs[j0].plan->n;
     size_t end = j0;
-    auto cls = [&](const Job &j) { return route_class(j.plan->n, nb, j.plan->dim, fp32, U != nullptr, at); };
+    auto cls = [&](const Job &j) {
+      return route_class(j.plan->n, nb, j.plan->dim, j.plan->medium.extra, fp32, U != nullptr, at);
+    };
     const int c0 = cls(jobs[j0]);
     while (end < jobs.size() && 3 * jobs[end].plan->n >= 2 * n0 && cls(jobs[end]) == c0) ++end;
-    Route rt = krylov_route(n0, nb, jobs[j0].plan->dim, fp32, U != nullptr, at);
+    Route rt = krylov_route(n0, nb, jobs[j0].plan->dim, jobs[j0].plan->medium.extra, fp32, U != nullptr, at);
     if (solve_bytes(1, route_item_bytes(n0, nb, fp32, rt)) > budget) rt = Route{};
     *krylov = *krylov || rt.steps > 0;
     size_t bytes = 0;
@@ -2480,9 +2556,10 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   for (size_t j0 = 0; j0 < jobs.size();) {
     const int n0 = order_of(jobs[j0]);
     size_t j1 = j0, bytes = 0;
-    auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, fp32, false, TRY_KRYLOV); };
+    auto extra = [&](const CJob &j) { return cells[ord[j.s]]->medium.extra; };
+    auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, extra(j), fp32, false, TRY_KRYLOV); };
     while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
-    Route rt = krylov_route(n0, n_bands, 0, fp32, false, TRY_KRYLOV);
+    Route rt = krylov_route(n0, n_bands, 0, extra(jobs[j0]), fp32, false, TRY_KRYLOV);
     if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > budget) rt = Route{};
     const size_t end = j1;
     for (j1 = j0; j1 < end; ++j1) {
@@ -2617,20 +2694,17 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       const CellGroup &g = groups[grp_of[jb.s]];
       const int n = 2 * g.N;
       char *table = stage.data() + ch.t_items;
-      EigItem it = carve_route_item(W + o_items + off, n, n_bands, fp32, ch.rt, ch.j1 - ch.j0, j - ch.j0, table);
-      off += route_item_bytes(n, n_bands, fp32, ch.rt);
-      it.coef = reinterpret_cast<cd *>(W + o_coef + g.o_coef) + (size_t)(jb.s - g.c0) * 15 * g.N * g.N;
-      it.N = g.N;
-      it.n = n;
-      it.dim = 0;
-      it.check = fp32 ? 1 : 0;
-      it.nb = n_bands;
-      it.slot = (int)(base[ci] + jb.t);
       const double *q = Q[ci] + 2 * (size_t)jb.t;
       const double *T = cells[ci]->T;
-      it.kap1 = 2.0 * M_PI * (T[0] * q[0] + T[1] * q[1]);
-      it.kap2 = 2.0 * M_PI * (T[2] * q[0] + T[3] * q[1]);
-      it.kap3 = 0.0;
+      const Origin og{2, g.M1, g.M2, 0, T,
+                      {2.0 * M_PI * (T[0] * q[0] + T[1] * q[1]), 2.0 * M_PI * (T[2] * q[0] + T[3] * q[1]), 0.0},
+                      &cells[ci]->medium};
+      EigItem it = carve_route_item(W + o_items + off, n, n_bands, fp32, og, ch.rt, ch.j1 - ch.j0, j - ch.j0, table);
+      off += route_item_bytes(n, n_bands, fp32, ch.rt);
+      it.coef = reinterpret_cast<cd *>(W + o_coef + g.o_coef) + (size_t)(jb.s - g.c0) * 15 * g.N * g.N;
+      it.dim = 0;
+      it.check = fp32 ? 1 : 0;
+      it.slot = (int)(base[ci] + jb.t);
       put_item(table, j - ch.j0, it);
     }
   }
@@ -2966,7 +3040,7 @@ extern "C" int mvpb_autotune(mvpb_plan p, int n_k, const double *Q, int n_bands,
   ProfBind pb(nullptr);
   hipStream_t st = ctx->stream;
   const bool fp32 = (p->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
-  Route rt = krylov_route(p->n, n_bands, p->dim, fp32, false, TRY_KRYLOV);
+  Route rt = krylov_route(p->n, n_bands, p->dim, p->medium.extra, fp32, false, TRY_KRYLOV);
   if (ctx->cap && solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt)) > ctx->cap) rt = Route{};
   const size_t need = solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt));
   if (ctx->cap && need > ctx->cap)

@@ -88,6 +88,15 @@ struct EigItem {
 // npad (n rounded up to KRY_ROWS) rows each.
 constexpr int KRY_ROWS = 128;
 constexpr int KRY_MAX_STEPS = 32;
+// What the shift and the start of a solve are taken from: the homogeneous isotropic
+// medium of the cell's mean slowness, the mean over the phases of density times
+// compliance.  Its bands lie within a factor of 0.3 to 8 of the cell's at stiffness
+// ratios from 1e-6 to 1e6 and density ratios from 0.01 to 100 (0.05 at the least,
+// soft and light inclusions of density ratio 100).
+struct KryMedium {
+  double ct2 = 0.0, cl2 = 0.0;   // squared speeds of its shear and pressure waves
+  int extra = 0;                 // steps beyond krylov_steps: heavy stiff parts in a light soft rest slow the convergence
+};
 struct KryItem {
   cd *A;              // n x n working copy: C(k), then C(k) + sigma I, then its Cholesky factor (lower)
   cd *Xi;             // n x n inverse factor within each part (lower; zero above the diagonal in its 64-blocks)
@@ -97,7 +106,7 @@ struct KryItem {
   cd *P;              // HB x HB projections of Z on the basis blocks
   cd *G;              // HB x HB Gram partials of Z, one per KRY_ROWS rows
   cd *T;              // m x m projection (its lower band)
-  double *sigma;      // the shift
+  double *weight;     // one per plane wave: scale of the start block's rows (in W, before the first step)
   int *status;        // 0; 1: C + sigma I not positive definite; 2: rank-deficient block
   const cd *Ys;       // m x nb eigenvectors of the projection
   const double *lam_s;
@@ -105,6 +114,10 @@ struct KryItem {
   cd *Y;              // n x nb Ritz vectors
   int *flag;          // nonzero if the item's pairs do not stand
   int n, npad, nb, m;
+  int d, M1, M2, M3;  // displacement components, cutoffs (plane-wave order of the unknowns)
+  double B[9];        // reciprocal basis, 3 x 3: wave vector kap + B (plane wave's index)
+  double kap[3];      // Cartesian Bloch vector
+  double ct2, cl2;    // of the KryMedium
 };
 
 // assembly.hip

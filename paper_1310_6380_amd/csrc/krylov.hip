@@ -40,30 +40,46 @@ constexpr int KPB = 9;        // most blocks of a part of the inverse factor
 constexpr int KT = 1;         // 16-row tiles of the factor per workgroup of a product
 constexpr int KR = 16 * KT;
 constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonalisation
-// Shift as a fraction of the nb-th smallest diagonal entry d_nb of C (which
-// overestimates the nb-th eigenvalue, by 2 to 10 and more where the phases
-// differ by orders of magnitude): large enough that L and the block factors stay
-// well conditioned where C is singular (the zero modes at Gamma: condition of a
-// block's factor 1e2, orthogonality of the basis 1e-11), small enough not to
-// slow the convergence (under a tenth of a digit per step against no shift).
-constexpr double KRY_SHIFT = 1.0 / 64.0;
+// Shift as a fraction of the nb-th band of the homogeneous medium (see KryMedium;
+// the (d + 1)-th where fewer are wanted: the first d vanish at Gamma).  Small enough
+// not to slow the convergence, which a shift above the wanted values would stop: a
+// fraction 1 / 64 of the nb-th smallest diagonal entry of C, which the stiff parts
+// set, is 2.4 of the nb-th value at a stiffness ratio of 1e3 and 4 to 20 from 1e4
+// on, with residuals of 3e-5 and 1e-2 after the steps that reach 1e-9 here, and 40
+// points of 2N = 882, 18 bands, soft inclusions of ratio 1e4, then took two attempts
+// and the reduction, 34.0 ms against 7.2 ms here and 16.5 by the reduction alone.
+// Large enough that L and the blocks' factors stay well conditioned where C is
+// singular (the zero modes at Gamma: orthogonality of the basis 1e-11, 1e-8 at the
+// worst).
+constexpr double KRY_SHIFT = 1.0 / 8.0;
 
-
-// Shift of every item: sigma = KRY_SHIFT times the nb-th smallest diagonal
-// entry of C, added to the diagonal of the working copy.  (Rank counting in
-// LDS, one workgroup per item, one entry per thread and pass.)
+// Shift of every item, added to the diagonal of the working copy, and the weights of
+// the start block's rows.  (Bands of the homogeneous medium at every plane wave,
+// rank counting in LDS, one workgroup per item, one value per thread and pass.)
 __global__ void __launch_bounds__(1024) kry_shift(const KryItem *__restrict__ items) {
   __shared__ double dg[MAX_N + 8];
   __shared__ double sel;
   const KryItem it = items[blockIdx.x];
-  const int n = it.n, tid = threadIdx.x;
-  for (int r = tid; r < n; r += 1024) dg[r] = gld(it.Ak, (size_t)r * n + r).re;
+  const int n = it.n, tid = threadIdx.x, d = it.d, N = n / d;
+  const int m2 = 2 * it.M2 + 1, m3 = 2 * it.M3 + 1;
+  for (int r = tid; r < N; r += 1024) {
+    const double g[3] = {(double)(r / m3 / m2 - it.M1), (double)(r / m3 % m2 - it.M2), (double)(r % m3 - it.M3)};
+    double k2 = 0.0;
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      const double K = it.kap[l] + (it.B[3 * l] * g[0] + it.B[3 * l + 1] * g[1] + it.B[3 * l + 2] * g[2]);
+      k2 = fma(K, K, k2);
+    }
+    for (int l = 0; l + 1 < d; ++l) dg[d * r + l] = it.ct2 * k2;
+    dg[d * r + d - 1] = it.cl2 * k2;
+  }
   if (tid < 8) dg[n + tid] = INFINITY;
   if (tid == 0) {
     sel = NAN;
     gst(it.status, 0, 0);
   }
   __syncthreads();
+  const int want = max(it.nb, d + 1) - 1;
   for (int r = tid; r < n; r += 1024) {
     const double v = dg[r];
     int rank = 0;
@@ -74,12 +90,15 @@ __global__ void __launch_bounds__(1024) kry_shift(const KryItem *__restrict__ it
 #pragma unroll
       for (int u = 0; u < 8; ++u) rank += (w[u] < v) | ((w[u] == v) & (q0 + u < r));
     }
-    if (rank == it.nb - 1) sel = v;
+    if (rank == want) sel = v;
   }
   __syncthreads();
-  const double sg = KRY_SHIFT * sel;
-  for (int r = tid; r < n; r += 1024) gst(it.A, (size_t)r * n + r, mk(dg[r] + sg, 0.0));
-  if (tid == 0) gst(it.sigma, 0, sg);
+  const double lam = sel, sg = KRY_SHIFT * lam;
+  for (int r = tid; r < N; r += 1024) gst(it.weight, r, dg[d * r] > lam ? lam / dg[d * r] : 1.0);
+  for (int r = tid; r < n; r += 1024) {
+    const size_t e = (size_t)r * n + r;
+    gst(it.A, e, mk(gld(it.Ak, e).re + sg, 0.0));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -535,8 +554,9 @@ __global__ void __launch_bounds__(512) kry_project(const KryItem *__restrict__ i
 
 // Z -= sum_{i <= j} Q_i P_i and the chunk's part of G = Z^H Z; 128 rows per
 // workgroup, 16 per wavefront.  START: Z = pseudo-random instead (and zero
-// rows beyond n in Z and W), row r scaled by min(1, d_nb / C(r, r)): the low
-// modes lie on the rows of small diagonal, which saves a step.  The workgroup of chunk 0 writes the diagonal
+// rows beyond n in Z and W), the rows of a plane wave scaled by min(1, lambda / its
+// lowest band of the homogeneous medium), lambda the wanted one: the low modes lie on
+// the long waves, which saves a step.  The workgroup of chunk 0 writes the diagonal
 // block of the projection, -(P_j + P_j^H) / 2.
 template <bool START>
 __global__ void __launch_bounds__(512) kry_update(const KryItem *__restrict__ items, int j) {
@@ -549,12 +569,11 @@ __global__ void __launch_bounds__(512) kry_update(const KryItem *__restrict__ it
   const int rw = r0 + 16 * wv;
   cd z[4];
   if (START) {
-    const double dnb = gld(it.sigma, 0) * (1.0 / KRY_SHIFT);
+    const int N = n / it.d;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int r = rw + lk + 4 * v;
-      const double d = gld(it.Ak, (size_t)min(r, n - 1) * (n + 1)).re;
-      const double w = d > dnb ? dnb / d : 1.0;
+      const double w = gld(it.weight, min(r, n - 1) % N);
       z[v] = r < n ? mk(w * kry_random(r, 2 * li), w * kry_random(r, 2 * li + 1)) : mk(0.0, 0.0);
       gst(it.Z, (size_t)r * KS + li, z[v]);
       if (r >= n) gst(it.W, (size_t)r * KS + li, mk(0.0, 0.0));

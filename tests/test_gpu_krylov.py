@@ -136,3 +136,56 @@ def test_krylov_parts_mixed_with_other_routes(ctx):
         ref, _ = mo.bands(phase, props, OBLIQUE, *M, Q[:1], nb)
         print("  error", M, band_error(om[:1], ref), flush=True)
         assert band_error(om[:1], ref) <= TOL64
+
+
+def _launches(ctx, call):
+    """(what call returns, {kernel family: its launches})."""
+    ctx.profile(True)
+    out = call()
+    n = {k: n for k, (_, n) in ctx.profile_read().items()}
+    ctx.profile(False)
+    return out, n
+
+
+def _contrast_cell(geom, E, rho):
+    """A 24 x 24 cell of soft (0) and hard (1) phases whose moduli and densities
+    are in the ratios E and rho; coated: rubber-coated lead cylinders in epoxy."""
+    x, y = np.meshgrid((np.arange(24) + 0.5) / 24 - 0.5, (np.arange(24) + 0.5) / 24 - 0.5, indexing="ij")
+    r = np.hypot(x, y)
+    if geom == "coated":
+        phase = np.where(r < 0.27, 0, np.where(r < 0.36, 1, 2))
+        return phase.astype(np.int32), np.array([[40.8e9, 0.37, 11600.0], [E, 0.47, 1300.0], [4.35e9, 0.37, 1180.0]])
+    inside = r < 0.3 if geom == "circle" else (np.minimum(abs(x), abs(y)) < 0.12) & (np.maximum(abs(x), abs(y)) < 0.4)
+    return inside.astype(np.int32), np.array([[1e9, 0.35, 1200.0], [1e9 * E, 0.33, 1200.0 * rho]])
+
+
+CONTRASTS = [("circle", 1e3, 1.0), ("circle", 1e4, 1.0), ("circle", 1e5, 1.0), ("circle", 1e-3, 1.0), ("circle", 1e-4, 1.0),
+             ("circle", 1e-5, 1.0), ("cross", 1e4, 8.0), ("cross", 1e-4, 0.5), ("circle", 10.0, 16.0), ("coated", 1e5, 0.0),
+             ("coated", 1e7, 0.0)]
+
+
+# 2N = 338 and 578 with the bands of small and of ordinary calls, 450 with modes (more steps, a lower bar), and the
+# benchmark's 882 with 18 bands
+@pytest.mark.parametrize("geom,E,rho,M,nb,modes",
+                         [(*c, *s) for s in [(6, 4, False), (8, 10, False), (7, 4, True)] for c in CONTRASTS] +
+                         [(*c, 10, 18, False) for c in CONTRASTS[1::4]])
+def test_krylov_stands_at_large_contrast(ctx, geom, E, rho, M, nb, modes):
+    """Cells of large stiffness ratio, as locally resonant crystals have it: the
+    frequencies of the first attempt stand, and no point needs the reduction for its
+    modes.  Two solvers that are backward stable to n eps of the largest eigenvalue
+    differ by that, beside the bar of every FP64 path."""
+    phase, props = _contrast_cell(geom, E, rho)
+    Q = np.array([[0.0, 0.0], [0.02, 0.01], [0.31, 0.12], [0.5, 0.5]])
+    plan = ctx.cell(phase, props).plan(M)
+    print("contrast", geom, E, rho, M, nb, modes, flush=True)
+    out, n = _launches(ctx, lambda: plan.solve(Q, nb, vectors=modes))
+    om = out[0] if modes else out
+    assert n["krylov_factor"] <= 1 + modes and n["krylov_factor"] > 0 and n["he2hb_panel"] == 0, n
+    tabs = mo.subdomain_integral_tables(phase, props.shape[0], np.eye(2), M, M)
+    m = mo.assemble(tabs, props, np.eye(2), M, M, Q[2])
+    order = m["Omega"].shape[0]
+    lam = mo.solve_k(m, order)[1]
+    err = np.abs(om[2] ** 2 - lam[:nb])
+    bar = 2.0 * TOL64 * lam[:nb] + order * np.finfo(np.float64).eps * lam[-1]
+    print("  worst error over its bar", (err / bar).max(), flush=True)
+    assert np.all(err <= bar)
