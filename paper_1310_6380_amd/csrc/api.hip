@@ -1500,11 +1500,12 @@ constexpr int RETRY_STEPS = 4;
 // n = 242, 0.79, 2.15 and 2.36 against 2.78 and 2.94; n = 450, 0.75, 4.96 and 5.86
 // against 6.38 and 6.75; the line at 0.85 leaves room for the basis among n
 // vectors, as a longer attempt has to.  The route is for FP64 solves that end with
-// the Rayleigh-Ritz step.  The bars: a frequency's error is about ten times the
-// residual's square (1e-13 at 1e-7, the rounding level of the solve; 1.4e-12 at
-// most where the next value is close), a mode's is the residual over the relative
-// gap.  A bar of 3e-8 sends more points into a second attempt: small cells of
-// stiffness ratio near 100 4.05 -> 5.11 and 6.80 -> 7.80 ms, for errors of 2e-13.
+// the Rayleigh-Ritz step.  The bars are on the residual before the last step of
+// inverse iteration (kry_ritz).  A frequency's error is the square of what that step
+// leaves: rounding of the operator up to residuals of 1e-6 (without it 3e-12 at 1e-7 and
+// 6e-10 at 1e-6; 1800 points of stiffness ratios 1e-5 .. 1e5, where a dense solver's is
+// 1e-12).  A mode's is the residual over the relative gap, as a dense solver's is eps
+// lambda_max / lambda over it (kry_check raises the bar to that).
 static Route krylov_route(int n, int nb, int dim, int extra, bool fp32, bool modes, Attempt at) {
   Route rt;
   if (fp32 || nb > RR_MAX_BANDS || at == TRY_REDUCTION) return rt;
@@ -1512,7 +1513,7 @@ static Route krylov_route(int n, int nb, int dim, int extra, bool fp32, bool mod
   if (s + RETRY_STEPS > KRY_MAX_STEPS || 20 * HB * s > 17 * n) return rt;
   if (at == TRY_LONGER && 10 * HB * (s += RETRY_STEPS) > 9 * n) return rt;
   rt.steps = s;
-  rt.tol = modes ? 1e-11 : 1e-7;
+  rt.tol = modes ? 2e-12 : 1e-7;
   return rt;
 }
 
@@ -1536,7 +1537,7 @@ static void krylov_layout(int n, int nb, int steps, size_t *sz, int *count) {
   sz[k++] = sizeof(cd) * npad * HB;                  // Z
   sz[k++] = sizeof(cd) * (size_t)steps * HB * HB;    // P
   sz[k++] = sizeof(cd) * nch * HB * HB;              // G
-  sz[k++] = sizeof(int);                             // status
+  sz[k++] = 2 * sizeof(double);                      // largest diagonal entry, status
   sz[k++] = sizeof(int) * 2;                         // flag
   sz[k++] = sizeof(double) * nb;                     // lam
   sz[k++] = sizeof(double) * nb;                     // omega
@@ -1660,7 +1661,8 @@ static EigItem carve_route_item(char *base, int n, int nb, bool fp32, const Orig
   ky.P = (cd *)take();
   ky.G = (cd *)take();
   ky.weight = (double *)ky.W;
-  ky.status = (int *)take();
+  ky.top = (double *)take();
+  ky.status = (int *)(ky.top + 1);
   it.flag = (int *)take();
   it.lam = (double *)take();
   it.omega = (double *)take();

@@ -107,6 +107,7 @@ struct KryItem {
   cd *G;              // HB x HB Gram partials of Z, one per KRY_ROWS rows
   cd *T;              // m x m projection (its lower band)
   double *weight;     // one per plane wave: scale of the start block's rows (in W, before the first step)
+  double *top;        // largest diagonal entry of C
   int *status;        // 0; 1: C + sigma I not positive definite; 2: rank-deficient block
   const cd *Ys;       // m x nb eigenvectors of the projection
   const double *lam_s;

@@ -52,13 +52,14 @@ constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonal
 // singular (the zero modes at Gamma: orthogonality of the basis 1e-11, 1e-8 at the
 // worst).
 constexpr double KRY_SHIFT = 1.0 / 8.0;
+constexpr double KRY_TOL_MODES = 1e-10;
 
 // Shift of every item, added to the diagonal of the working copy, and the weights of
 // the start block's rows.  (Bands of the homogeneous medium at every plane wave,
 // rank counting in LDS, one workgroup per item, one value per thread and pass.)
 __global__ void __launch_bounds__(1024) kry_shift(const KryItem *__restrict__ items) {
   __shared__ double dg[MAX_N + 8];
-  __shared__ double sel;
+  __shared__ double sel, peak[16];
   const KryItem it = items[blockIdx.x];
   const int n = it.n, tid = threadIdx.x, d = it.d, N = n / d;
   const int m2 = 2 * it.M2 + 1, m3 = 2 * it.M3 + 1;
@@ -95,9 +96,19 @@ __global__ void __launch_bounds__(1024) kry_shift(const KryItem *__restrict__ it
   __syncthreads();
   const double lam = sel, sg = KRY_SHIFT * lam;
   for (int r = tid; r < N; r += 1024) gst(it.weight, r, dg[d * r] > lam ? lam / dg[d * r] : 1.0);
+  double top = 0.0;
   for (int r = tid; r < n; r += 1024) {
     const size_t e = (size_t)r * n + r;
-    gst(it.A, e, mk(gld(it.Ak, e).re + sg, 0.0));
+    const double c = gld(it.Ak, e).re;
+    top = fmax(top, c);
+    gst(it.A, e, mk(c + sg, 0.0));
+  }
+  for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+  if ((tid & 63) == 0) peak[tid >> 6] = top;
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 16; ++w) top = fmax(top, peak[w]);
+    gst(it.top, 0, top);
   }
 }
 
@@ -622,27 +633,37 @@ __global__ void __launch_bounds__(512) kry_update(const KryItem *__restrict__ it
   }
 }
 
-// Ritz vectors Y = [Q_0 .. Q_{s-1}] Ys, 128 rows and 16 bands per workgroup.
+// Ritz vectors, once more by B: with Z the next block, B [Q_0 .. Q_{s-1}] y =
+// theta [Q_0 .. Q_{s-1}] y + Z y_last (y_last: the last 16 entries of y), so Y =
+// [Q_0 .. Q_{s-1}] y + Z y_last / theta is a step of inverse iteration at the price
+// of one more block here.  It takes a vector's error along an eigenvector of value
+// lambda' down by (lambda + sigma) / (lambda' + sigma): the residual in C of modes at
+// their bar from 1e3 times a dense solver's to a few times.  128 rows and 16 bands per
+// workgroup.
 __global__ void __launch_bounds__(512) kry_ritz(const KryItem *__restrict__ items) {
   extern __shared__ __align__(16) unsigned char kry_raw[];
-  cd *Yl = (cd *)kry_raw;   // [m][16]
+  cd *Yl = (cd *)kry_raw;   // [m + 16][16]
   const KryItem it = items[blockIdx.z];
   const int n = it.n, nb = it.nb, m = it.m, r0 = KCH * blockIdx.x, b0 = 16 * blockIdx.y;
   if (r0 >= n || b0 >= nb) return;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, li = lane & 15, lk = lane >> 4;
   for (int e = tid; e < 16 * m; e += 512) {
     const int k = e % m, b = e / m;
-    Yl[k * 16 + b] = b0 + b < nb ? gld(it.Ys, (size_t)(b0 + b) * m + k) : mk(0.0, 0.0);
+    const cd y = b0 + b < nb ? gld(it.Ys, (size_t)(b0 + b) * m + k) : mk(0.0, 0.0);
+    Yl[k * 16 + b] = y;
+    if (k >= m - KS) Yl[(k + KS) * 16 + b] = b0 + b < nb ? (-1.0 / gld(it.lam_s, b0 + b)) * y : mk(0.0, 0.0);
   }
   __syncthreads();
   const int r = r0 + 16 * wv + li;
   const cd *q0 = it.Q + (size_t)min(r, n - 1) * KS;
   Acc3 acc;
   acc.clear();
-  for (int i = 0; i < m / KS; ++i) {
+  const cd *z0 = it.Z + (size_t)min(r, n - 1) * KS;
+  for (int i = 0; i <= m / KS; ++i) {
+    const cd *p = i < m / KS ? q0 + (size_t)i * it.npad * KS : z0;
     cd b[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) b[q] = gld(q0, (size_t)i * it.npad * KS + 4 * q + lk);
+    for (int q = 0; q < 4; ++q) b[q] = gld(p, 4 * q + lk);
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc.step(Yl[(KS * i + 4 * q + lk) * 16 + li], b[q]);
   }
@@ -655,7 +676,8 @@ __global__ void __launch_bounds__(512) kry_ritz(const KryItem *__restrict__ item
 
 // Whether an item's pairs stand: for each, the residual |B y - theta y| =
 // |R_s y_last| (y_last: the last 16 entries of the projection's eigenvector)
-// is at most tol theta, and no run of nearly equal values is so long that the
+// is at most tol theta (with modes, or as much as eps |C| moves the value in a
+// dense solver, up to KRY_TOL_MODES theta), and no run of nearly equal values is so long that the
 // block of 16 could have missed copies (a block Krylov space holds at most 16
 // vectors of one eigenvalue).  Failing items are flagged: their frequencies
 // come out NaN and the host solves them again by the reduction.
@@ -663,6 +685,7 @@ __global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ item
   __shared__ cd Gs[256];
   const KryItem it = items[blockIdx.x];
   const int lane = threadIdx.x, nb = it.nb, m = it.m;
+  const double top = gld(it.top, 0);
   int bad = gld(it.status, 0) | gld(it.flag_s, 0);
   for (int e = lane; e < 256; e += 64) {
     Gs[e] = kry_gram(it, e);
@@ -679,7 +702,8 @@ __global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ item
         s += yr.re * t.re + yr.im * t.im;
       }
       const double th = -gld(it.lam_s, b);
-      if (!(th > 0.0) || !(s <= tol * tol * th * th)) bad = 1;
+      const double bar = fmax(tol, fmin(DBL_EPSILON * top * th, KRY_TOL_MODES));
+      if (!(th > 0.0) || !(s <= bar * bar * th * th)) bad = 1;
       // a run of KS - 1 neighbouring values within 1e-4
       if (b + KS - 2 < nb && !(gld(it.lam_s, b + KS - 2) - gld(it.lam_s, b) > 1e-4 * th)) bad = 1;
     }
@@ -739,13 +763,13 @@ hipError_t launch_krylov_ritz(const KryItem *items, int n_items, int n_max, int 
                               hipStream_t st) {
   ProfScope ps(K_KRYLOV, st);
   hipLaunchKernelGGL(kry_ritz, dim3(kry_chunks(n_max), (nb + 15) / 16, n_items), dim3(512),
-                     sizeof(cd) * 16 * KS * (size_t)s, st, items);
+                     sizeof(cd) * 16 * KS * (size_t)(s + 1), st, items);
   hipLaunchKernelGGL(kry_check, dim3(n_items), dim3(64), 0, st, items, tol);
   return hipGetLastError();
 }
 
 hipError_t init_krylov_attributes() {
-  const int most = (int)(sizeof(cd) * 256 * KRY_MAX_STEPS);
+  const int most = (int)(sizeof(cd) * 256 * (KRY_MAX_STEPS + 1));
   hipError_t e = hipFuncSetAttribute((const void *)kry_update<false>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void *)kry_ritz, hipFuncAttributeMaxDynamicSharedMemorySize, most);

@@ -189,3 +189,24 @@ def test_krylov_stands_at_large_contrast(ctx, geom, E, rho, M, nb, modes):
     bar = 2.0 * TOL64 * lam[:nb] + order * np.finfo(np.float64).eps * lam[-1]
     print("  worst error over its bar", (err / bar).max(), flush=True)
     assert np.all(err <= bar)
+
+
+# ratios below, at and above the benchmark's inclusion cells', few and more bands
+@pytest.mark.parametrize("M,nb", [(7, 4), (8, 10)])
+@pytest.mark.parametrize("E", [20.0, 100.0, 0.01])
+def test_krylov_modes_to_rounding(ctx, E, M, nb):
+    """Modes as a dense solve gives them: |C y - lambda y| within rounding of the
+    largest eigenvalue, 4 sqrt(n) eps lambda_max, for C and y of the reduced problem."""
+    phase, props = _contrast_cell("circle", E, 2.0)
+    Q = np.array([[0.21, 0.35], [0.02, -0.4]])
+    om, U = ctx.cell(phase, props).plan(M).solve(Q, nb, vectors=True)
+    tabs = mo.subdomain_integral_tables(phase, 2, np.eye(2), M, M)
+    for t, q in enumerate(Q):
+        m = mo.assemble(tabs, props, np.eye(2), M, M, q)
+        L = np.linalg.cholesky(0.5 * (m["Omega"] + m["Omega"].conj().T))
+        C = np.linalg.solve(L, np.linalg.solve(L, mo.reduced_operator(m)).conj().T)
+        y = L.conj().T @ U[t].T
+        res = np.linalg.norm(C @ y - y * om[t] ** 2, axis=0)
+        bar = 4.0 * np.sqrt(len(C)) * np.finfo(np.float64).eps * np.linalg.eigvalsh(C)[-1]
+        print("modes", E, M, nb, "residual over its bar", (res / bar).max(), flush=True)
+        assert np.all(res <= bar)
