@@ -2864,12 +2864,12 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   std::vector<int> hstat(3 * (size_t)n_cells, 0);
   HIP_TRY(hipMemcpyAsync(hstat.data(), stat, sizeof(int) * 3 * n_cells, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  const char *names[3] = {"compliance block Phi(d11+d12)", "compliance block Phi(d11-d12)", "density matrix Omega"};
-  for (int i = 0; i < n_cells; ++i)
+  // the block of cell i that did not factor, or -1
+  auto not_pd = [&](int i) {
     for (int m = 0; m < 3; ++m)
-      if (hstat[3 * (size_t)pos[i] + m])
-        return set_err(MVPB_E_NOT_PD, "cell %d: %s is not positive definite (pivot %d)", i, names[m],
-                       hstat[3 * (size_t)pos[i] + m] - 1);
+      if (hstat[3 * (size_t)pos[i] + m]) return m;
+    return -1;
+  };
   if (std::any_of(chunks.begin(), chunks.end(), [](const CellChunk &c) { return c.rt.steps > 0; })) {
     // points whose Krylov pairs do not stand (NaN): again from a plan of their cell
     std::vector<double> seen(base[n_cells] * n_bands);
@@ -2877,6 +2877,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
     HIP_TRY(hipStreamSynchronize(st));
     for (int i = 0; i < n_cells; ++i) {
       std::vector<int> bad;
+      if (not_pd(i) >= 0) continue;
       for (int t = 0; t < n_k[i]; ++t)
         if (isnan(seen[(base[i] + t) * n_bands])) bad.push_back(t);
       if (bad.empty()) continue;
@@ -2896,6 +2897,11 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       HIP_TRY(e);
     }
   }
+  const char *names[3] = {"compliance block Phi(d11+d12)", "compliance block Phi(d11-d12)", "density matrix Omega"};
+  for (int i = 0; i < n_cells; ++i)
+    if (const int m = not_pd(i); m >= 0)
+      return set_err(MVPB_E_NOT_PD, "cell %d: %s is not positive definite (pivot %d)", i, names[m],
+                     hstat[3 * (size_t)pos[i] + m] - 1);
   if (!dev)
     for (int i = 0; i < n_cells; ++i) {
       rc = check_failed_items(omega[i], (size_t)n_k[i] * n_bands, n_bands);
