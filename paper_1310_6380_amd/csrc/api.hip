@@ -2553,36 +2553,55 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       return set_err(MVPB_E_NOMEM, "plan build of %d cells needs %zu bytes, cap is %zu", n_cells, fixed + tab, ctx->cap);
     budget = std::min(budget, ctx->cap - fixed - tab);
   }
+  // workspace: tables | coefficients | status | temporaries | frequencies | items.
+  // Item tables and items of the Krylov route are larger: a call that fits the cap
+  // only without it is laid out without it.
   std::vector<CellChunk> chunks;
-  size_t item_region = 0;
-  for (size_t j0 = 0; j0 < jobs.size();) {
-    const int n0 = order_of(jobs[j0]);
-    size_t j1 = j0, bytes = 0;
-    auto extra = [&](const CJob &j) { return cells[ord[j.s]]->medium.extra; };
-    auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, extra(j), fp32, false, TRY_KRYLOV); };
-    while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
-    Route rt = krylov_route(n0, n_bands, 0, extra(jobs[j0]), fp32, false, TRY_KRYLOV);
-    if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > budget) rt = Route{};
-    const size_t end = j1;
-    for (j1 = j0; j1 < end; ++j1) {
-      const size_t b = route_item_bytes(order_of(jobs[j1]), n_bands, fp32, rt);
-      if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > budget) break;
-      bytes += b;
+  const size_t plan_tab = tab;
+  size_t item_region = 0, o_coef = 0, o_stat = 0, o_temp = 0, o_om = 0, o_items = 0, total = 0;
+  auto lay_out = [&](Attempt at, size_t room) -> int {
+    chunks.clear();
+    tab = plan_tab;
+    item_region = 0;
+    for (size_t j0 = 0; j0 < jobs.size();) {
+      const int n0 = order_of(jobs[j0]);
+      size_t j1 = j0, bytes = 0;
+      auto extra = [&](const CJob &j) { return cells[ord[j.s]]->medium.extra; };
+      auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, extra(j), fp32, false, at); };
+      while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
+      Route rt = krylov_route(n0, n_bands, 0, extra(jobs[j0]), fp32, false, at);
+      if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > room) rt = Route{};
+      const size_t end = j1;
+      for (j1 = j0; j1 < end; ++j1) {
+        const size_t b = route_item_bytes(order_of(jobs[j1]), n_bands, fp32, rt);
+        if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > room) break;
+        bytes += b;
+      }
+      bytes += ctl_bytes(j1 - j0);
+      if (bytes > room) return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, the budget is %zu", bytes, room);
+      CellChunk ch{j0, j1, take_tab(table_bytes(j1 - j0, rt)), TuneParams{}, rt};
+      auto f = ctx->tune.find(size_class(n0));
+      if (f != ctx->tune.end()) ch.tp = f->second;
+      chunks.push_back(ch);
+      item_region = std::max(item_region, bytes);
+      j0 = j1;
     }
-    bytes += ctl_bytes(j1 - j0);
-    if (bytes > budget) return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, the budget is %zu", bytes, budget);
-    CellChunk ch{j0, j1, take_tab(table_bytes(j1 - j0, rt)), TuneParams{}, rt};
-    auto f = ctx->tune.find(size_class(n0));
-    if (f != ctx->tune.end()) ch.tp = f->second;
-    chunks.push_back(ch);
-    item_region = std::max(item_region, bytes);
-    j0 = j1;
-  }
-  // workspace: tables | coefficients | status | temporaries | frequencies | items
-  const size_t o_coef = align256(tab), o_stat = o_coef + coef_bytes, o_temp = o_stat + stat_bytes,
-               o_om = o_temp + temp_bytes, o_items = o_om + om_bytes, total = o_items + item_region;
-  if (ctx->cap && total > ctx->cap)
-    return set_err(MVPB_E_NOMEM, "workspace %zu bytes exceeds the cap of %zu bytes", total, ctx->cap);
+    o_coef = align256(tab);
+    o_stat = o_coef + coef_bytes;
+    o_temp = o_stat + stat_bytes;
+    o_om = o_temp + temp_bytes;
+    o_items = o_om + om_bytes;
+    total = o_items + item_region;
+    if (ctx->cap && total > ctx->cap)
+      return set_err(MVPB_E_NOMEM, "workspace %zu bytes exceeds the cap of %zu bytes", total, ctx->cap);
+    return MVPB_OK;
+  };
+  Route any;
+  any.steps = 1;
+  const size_t tables = table_bytes(jobs.size(), any) + 256 * jobs.size();   // each chunk's aligned
+  rc = ctx->cap && budget <= tables ? MVPB_E_NOMEM : lay_out(TRY_KRYLOV, ctx->cap ? budget - tables : budget);
+  if (rc) rc = lay_out(TRY_REDUCTION, budget);
+  if (rc) return rc;
   // the staging may still feed an earlier copy; graphs point into the workspace
   HIP_TRY(hipStreamSynchronize(st));
   if (total > ctx->cws.bytes) {

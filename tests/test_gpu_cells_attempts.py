@@ -63,3 +63,31 @@ def test_points_stand_beside_a_cell_that_does_not_factor(ctx):
     print("status", rc, flush=True)
     assert rc == mvpb.E_NOT_PD
     assert band_error(out[0], _folded(QS)) <= TOL64
+
+
+def test_every_cap_above_an_accepted_one_is_accepted():
+    """60 points of 2N = 242, 4 bands, under caps from the least that a single item of
+    the reduction fits to well above one of the Krylov route."""
+    from paper_1310_6380_amd import mvpb
+    rng = np.random.default_rng(5)
+    phase, props = rng.integers(0, 3, (16, 16)).astype(np.int32), random_iso_props(3, rng)
+    Q = rng.uniform(0.05, 0.5, (60, 2))
+
+    def accepted(cap):
+        c = mvpb.Context(0, workspace_cap=cap)
+        try:
+            rc, out = _solve_cells(c, [c.cell(phase, props)], [5], [Q], 4)
+            assert rc in (mvpb.OK, mvpb.E_NOMEM)
+            assert rc != mvpb.OK or np.all(np.isfinite(out[0]))
+            return rc == mvpb.OK
+        finally:
+            c.close()
+
+    lo, hi = 1 << 20, 64 << 20
+    assert accepted(hi) and not accepted(lo)
+    while hi - lo > 4096:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if accepted(mid) else (mid, hi)
+    refused = [cap for cap in range(hi, hi + (5 << 19), 40 << 10) if not accepted(cap)]
+    print("least cap", hi, "refused above it", refused, flush=True)
+    assert not refused
