@@ -2842,6 +2842,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       put(ch.tp.group);
       put(ch.tp.wg_max);
       put(ch.rt.steps);
+      put((long long)ch.j1);   // the route depends on the cells' materials: so do the chunks
     }
   }
   hipGraphExec_t exec = nullptr;

@@ -91,3 +91,24 @@ def test_every_cap_above_an_accepted_one_is_accepted():
     refused = [cap for cap in range(hi, hi + (5 << 19), 40 << 10) if not accepted(cap)]
     print("least cap", hi, "refused above it", refused, flush=True)
     assert not refused
+
+
+def test_calls_of_one_shape_and_other_routes(ctx):
+    """Cells of one shape whose materials ask for more steps, in other places of the
+    call: its launch sequence is that of the chunks, not of the shape alone."""
+    x, y = np.meshgrid((np.arange(16) + 0.5) / 16 - 0.5, (np.arange(16) + 0.5) / 16 - 0.5, indexing="ij")
+    phase = (x * x + y * y < 0.09).astype(np.int32)
+    plain = np.array([[1e9, 0.35, 1200.0], [5e9, 0.33, 1500.0]])
+    heavy = np.array([[1e9, 0.35, 1200.0], [1e11, 0.33, 120000.0]])
+    Q = np.random.default_rng(3).uniform(0.05, 0.5, (7, 2))
+    ref = {}
+    for name, props in (("plain", plain), ("heavy", heavy)):
+        plan = ctx.cell(phase, props).plan(6)
+        ref[name] = plan.solve(Q, 5)
+        plan.close()
+    for names in (("plain", "plain", "heavy"), ("plain", "heavy", "heavy"), ("heavy", "plain", "plain"),
+                  ("plain", "plain", "plain"), ("plain", "heavy", "heavy")):
+        cells = [ctx.cell(phase, plain if n == "plain" else heavy) for n in names]
+        for name, om in zip(names, ctx.solve_cells(cells, [6] * 3, [Q] * 3, 5)):
+            print(names, name, band_error(om, ref[name]), flush=True)
+            assert band_error(om, ref[name]) <= 1e-10
