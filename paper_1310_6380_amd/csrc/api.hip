@@ -2290,7 +2290,9 @@ static int run_attempts(mvpb_ctx ctx, std::vector<Job> jobs, int nb, double *om,
   std::vector<double> seen;
   for (int at = first; !jobs.empty(); ++at) {
     bool krylov = false;
-    const int rc = run_sorted(ctx, jobs, nb, om, U, budget, use_graph, (Attempt)at, &krylov);
+    // a later attempt's points are others at each call: captured, their launch
+    // sequences would only push out those that callers replay
+    const int rc = run_sorted(ctx, jobs, nb, om, U, budget, use_graph && at == first, (Attempt)at, &krylov);
     if (rc || !krylov) return rc;
     seen.resize(n_om);
     HIP_TRY(hipMemcpyAsync(seen.data(), om, sizeof(double) * n_om, hipMemcpyDeviceToHost, ctx->stream));
@@ -2570,7 +2572,9 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, extra(j), fp32, false, at); };
       while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
       Route rt = krylov_route(n0, n_bands, 0, extra(jobs[j0]), fp32, false, at);
-      if (rt.steps && solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt)) > room) rt = Route{};
+      // points that the route hands on are solved again in the item region
+      const size_t last = solve_bytes(1, item_bytes(n0, n_bands, fp32));
+      if (rt.steps && std::max(last, solve_bytes(1, route_item_bytes(n0, n_bands, fp32, rt))) > room) rt = Route{};
       const size_t end = j1;
       for (j1 = j0; j1 < end; ++j1) {
         const size_t b = route_item_bytes(order_of(jobs[j1]), n_bands, fp32, rt);
@@ -2583,7 +2587,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       auto f = ctx->tune.find(size_class(n0));
       if (f != ctx->tune.end()) ch.tp = f->second;
       chunks.push_back(ch);
-      item_region = std::max(item_region, bytes);
+      item_region = std::max(item_region, std::max(bytes, last));
       j0 = j1;
     }
     o_coef = align256(tab);
@@ -2707,28 +2711,28 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   std::vector<size_t> grp_of(n_cells);
   for (size_t gi = 0; gi < groups.size(); ++gi)
     for (int s = groups[gi].c0; s < groups[gi].c1; ++s) grp_of[s] = gi;
-  for (const CellChunk &ch : chunks) {
+  auto fill_table = [&](char *table, const CJob *list, size_t count, const Route &rt) {
     size_t off = 0;
-    for (size_t j = ch.j0; j < ch.j1; ++j) {
-      const CJob &jb = jobs[j];
+    for (size_t i = 0; i < count; ++i) {
+      const CJob &jb = list[i];
       const int ci = ord[jb.s];
       const CellGroup &g = groups[grp_of[jb.s]];
       const int n = 2 * g.N;
-      char *table = stage.data() + ch.t_items;
       const double *q = Q[ci] + 2 * (size_t)jb.t;
       const double *T = cells[ci]->T;
       const Origin og{2, g.M1, g.M2, 0, T,
                       {2.0 * M_PI * (T[0] * q[0] + T[1] * q[1]), 2.0 * M_PI * (T[2] * q[0] + T[3] * q[1]), 0.0},
                       &cells[ci]->medium};
-      EigItem it = carve_route_item(W + o_items + off, n, n_bands, fp32, og, ch.rt, ch.j1 - ch.j0, j - ch.j0, table);
-      off += route_item_bytes(n, n_bands, fp32, ch.rt);
+      EigItem it = carve_route_item(W + o_items + off, n, n_bands, fp32, og, rt, count, i, table);
+      off += route_item_bytes(n, n_bands, fp32, rt);
       it.coef = reinterpret_cast<cd *>(W + o_coef + g.o_coef) + (size_t)(jb.s - g.c0) * 15 * g.N * g.N;
       it.dim = 0;
       it.check = fp32 ? 1 : 0;
       it.slot = (int)(base[ci] + jb.t);
-      put_item(table, j - ch.j0, it);
+      put_item(table, i, it);
     }
-  }
+  };
+  for (const CellChunk &ch : chunks) fill_table(stage.data() + ch.t_items, jobs.data() + ch.j0, ch.j1 - ch.j0, ch.rt);
   // fork/join events of every chunk's stage 1 (one set per chunk, so that the
   // captured dependencies of one chunk never alias another's)
   while (ctx->cell_events.size() < chunks.size() * (MAX_SIDE + 1)) {
@@ -2745,6 +2749,28 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   if (rc) return rc;
   HIP_TRY(hipMemcpyAsync(W, stage.data(), tab, hipMemcpyHostToDevice, st));
 
+  // eigensolve of the items of a table at t_items, and their frequencies
+  auto enqueue_items = [&](size_t t_items, const CJob *list, int cnt, const Route &rt, const TuneParams &tp,
+                           const hipEvent_t *ev, const hipEvent_t *la) -> hipError_t {
+    std::vector<int> orders(cnt);
+    size_t item_sum = 0;
+    for (int i = 0; i < cnt; ++i) {
+      orders[i] = order_of(list[i]);
+      item_sum += route_item_bytes(orders[i], n_bands, fp32, rt);
+    }
+    const EigItem *d_items = reinterpret_cast<const EigItem *>(W + t_items);
+    Stage2Shape sh;
+    sh.group = tp.group;
+    sh.wg_max = tp.wg_max;
+    sh.spin_limit = ctx->spin_limit;
+    const hipError_t e = enqueue_eigensolve(ctx, d_items, orders, true, false, n_bands, fp32, rt,
+                                            std::max(1, std::min(tp.parts, MAX_SIDE + 1)), sh,
+                                            reinterpret_cast<int *>(W + o_items + item_sum), st, ev[0], ev + 1, la);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gather_omega, dim3((cnt * n_bands + 255) / 256), dim3(256), 0, st, d_items, cnt, n_bands, om);
+    hipLaunchKernelGGL(max_acc, dim3(1), dim3(256), 0, st, d_items, cnt, ctx->accbuf.as<double>());
+    return hipGetLastError();
+  };
   // the launch sequence: every group's plan build, then every chunk's eigensolve
   auto enqueue = [&]() -> hipError_t {
     hipError_t e = hipSuccess;
@@ -2794,29 +2820,10 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
                                  reinterpret_cast<cd *>(W + o_coef + g.o_coef), cnt, st);
       gstat += 3 * cnt;
     }
-    int *ctl = nullptr;
-    for (const CellChunk &ch : chunks) {
-      const int cnt = (int)(ch.j1 - ch.j0);
-      std::vector<int> orders(cnt);
-      for (int i = 0; i < cnt; ++i) orders[i] = order_of(jobs[ch.j0 + i]);
-      size_t item_sum = 0;
-      for (int n : orders) item_sum += route_item_bytes(n, n_bands, fp32, ch.rt);
-      ctl = reinterpret_cast<int *>(W + o_items + item_sum);
-      const EigItem *d_items = reinterpret_cast<const EigItem *>(W + ch.t_items);
-      Stage2Shape sh;
-      sh.group = ch.tp.group;
-      sh.wg_max = ch.tp.wg_max;
-      sh.spin_limit = ctx->spin_limit;
-      const int parts = std::max(1, std::min(ch.tp.parts, MAX_SIDE + 1));
-      const hipEvent_t *ev = ctx->cell_events.data() + (size_t)(&ch - chunks.data()) * (MAX_SIDE + 1);
-      if (e == hipSuccess)
-        e = enqueue_eigensolve(ctx, d_items, orders, true, false, n_bands, fp32, ch.rt, parts, sh, ctl, st, ev[0], ev + 1,
-                               ctx->la_events.data() + la_base[&ch - chunks.data()]);
-      if (e == hipSuccess) {
-        hipLaunchKernelGGL(gather_omega, dim3((cnt * n_bands + 255) / 256), dim3(256), 0, st, d_items, cnt, n_bands, om);
-        hipLaunchKernelGGL(max_acc, dim3(1), dim3(256), 0, st, d_items, cnt, ctx->accbuf.as<double>());
-        e = hipGetLastError();
-      }
+    for (size_t c = 0; c < chunks.size() && e == hipSuccess; ++c) {
+      const CellChunk &ch = chunks[c];
+      e = enqueue_items(ch.t_items, jobs.data() + ch.j0, (int)(ch.j1 - ch.j0), ch.rt, ch.tp,
+                        ctx->cell_events.data() + c * (MAX_SIDE + 1), ctx->la_events.data() + la_base[c]);
     }
     return e;
   };
@@ -2874,49 +2881,72 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
     found->second.last_use = ++ctx->graph_clock;
   }
   HIP_TRY(hipGraphLaunch(exec, st));
-  // results, then the factorisation status of every cell
   const bool dev = flags & MVPB_F_DEVICE_PTRS;
-  for (int i = 0; i < n_cells; ++i) {
-    if (n_k[i] == 0) continue;
-    HIP_TRY(hipMemcpyAsync(omega[i], om + base[i] * n_bands, sizeof(double) * n_k[i] * n_bands,
-                           dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));
-  }
+  // the frequencies and the factorisation status of every cell
+  std::vector<double> seen(base[n_cells] * n_bands);
   std::vector<int> hstat(3 * (size_t)n_cells, 0);
+  auto read_back = [&]() -> hipError_t {
+    hipError_t e = hipSuccess;
+    if (!seen.empty()) e = hipMemcpyAsync(seen.data(), om, sizeof(double) * seen.size(), hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  };
   HIP_TRY(hipMemcpyAsync(hstat.data(), stat, sizeof(int) * 3 * n_cells, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  HIP_TRY(read_back());
   // the block of cell i that did not factor, or -1
   auto not_pd = [&](int i) {
     for (int m = 0; m < 3; ++m)
       if (hstat[3 * (size_t)pos[i] + m]) return m;
     return -1;
   };
-  if (std::any_of(chunks.begin(), chunks.end(), [](const CellChunk &c) { return c.rt.steps > 0; })) {
-    // points whose Krylov pairs do not stand (NaN): again from a plan of their cell
-    std::vector<double> seen(base[n_cells] * n_bands);
-    HIP_TRY(hipMemcpyAsync(seen.data(), om, sizeof(double) * seen.size(), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    for (int i = 0; i < n_cells; ++i) {
-      std::vector<int> bad;
-      if (not_pd(i) >= 0) continue;
-      for (int t = 0; t < n_k[i]; ++t)
-        if (isnan(seen[(base[i] + t) * n_bands])) bad.push_back(t);
-      if (bad.empty()) continue;
-      mvpb_plan p = nullptr;
-      rc = mvpb_plan_create(cells[i], M1[i], M2[i], precision, &p);
-      if (rc) return rc;
-      std::vector<Job> part;
-      for (int t : bad) part.push_back(Job{p, Q[i][2 * (size_t)t], Q[i][2 * (size_t)t + 1], 0.0, t});
-      rc = run_attempts(ctx, std::move(part), n_bands, om + base[i] * n_bands, (size_t)n_k[i] * n_bands, nullptr, budget,
-                        true, TRY_LONGER);
-      hipError_t e = rc ? hipSuccess
-                        : hipMemcpyAsync(omega[i], om + base[i] * n_bands, sizeof(double) * n_k[i] * n_bands,
-                                         dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-      mvpb_plan_destroy(p);
-      if (rc) return rc;
-      HIP_TRY(e);
+  // Points whose Krylov pairs do not stand (NaN): again, all of them together, from the
+  // coefficients in the workspace and in its item region.  Their number differs from
+  // call to call, so no graph is captured.
+  std::vector<CJob> again;
+  for (const CellChunk &ch : chunks)
+    for (size_t j = ch.j0; j < ch.j1 && ch.rt.steps; ++j)
+      if (not_pd(ord[jobs[j].s]) < 0) again.push_back(jobs[j]);
+  ProfBind pb(ctx);
+  std::vector<char> table;
+  for (int at = TRY_LONGER; at <= TRY_REDUCTION; ++at) {
+    again.erase(std::remove_if(again.begin(), again.end(),
+                               [&](const CJob &j) { return !isnan(seen[(base[ord[j.s]] + j.t) * n_bands]); }),
+                again.end());
+    if (again.empty()) break;
+    for (size_t j0 = 0, j1 = 0; j0 < again.size(); j0 = j1) {
+      const int n0 = order_of(again[j0]);
+      auto route = [&](const CJob &j) {
+        Route rt = krylov_route(order_of(j), n_bands, 0, cells[ord[j.s]]->medium.extra, fp32, false, (Attempt)at);
+        return solve_bytes(1, route_item_bytes(order_of(j), n_bands, fp32, rt)) > item_region ? Route{} : rt;
+      };
+      const Route rt = route(again[j0]);
+      size_t bytes = 0;
+      for (; j1 < again.size() && 3 * order_of(again[j1]) >= 2 * n0 && route(again[j1]).steps == rt.steps; ++j1) {
+        const size_t b = route_item_bytes(order_of(again[j1]), n_bands, fp32, rt);
+        if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > item_region) break;
+        bytes += b;
+      }
+      TuneParams tp;
+      auto f = ctx->tune.find(size_class(n0));
+      if (f != ctx->tune.end()) tp = f->second;
+      table.assign(table_bytes(j1 - j0, rt), 0);
+      fill_table(table.data(), again.data() + j0, j1 - j0, rt);
+      // in the place of the chunks' tables, which hold an entry at least as large for each of these points
+      HIP_TRY(hipMemcpyAsync(W + chunks[0].t_items, table.data(), table.size(), hipMemcpyHostToDevice, st));
+      HIP_TRY(enqueue_items(chunks[0].t_items, again.data() + j0, (int)(j1 - j0), rt, tp, ctx->cell_events.data(),
+                            ctx->la_events.data()));
+      HIP_TRY(hipStreamSynchronize(st));   // the next table takes this one's place
     }
+    HIP_TRY(read_back());
   }
+  for (int i = 0; i < n_cells; ++i) {
+    if (n_k[i] == 0) continue;
+    const size_t bytes = sizeof(double) * n_k[i] * n_bands;
+    if (dev)
+      HIP_TRY(hipMemcpyAsync(omega[i], om + base[i] * n_bands, bytes, hipMemcpyDeviceToDevice, st));
+    else
+      memcpy(omega[i], seen.data() + base[i] * n_bands, bytes);
+  }
+  if (dev) HIP_TRY(hipStreamSynchronize(st));
   const char *names[3] = {"compliance block Phi(d11+d12)", "compliance block Phi(d11-d12)", "density matrix Omega"};
   for (int i = 0; i < n_cells; ++i)
     if (const int m = not_pd(i); m >= 0)

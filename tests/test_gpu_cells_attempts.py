@@ -112,3 +112,59 @@ def test_calls_of_one_shape_and_other_routes(ctx):
         for name, om in zip(names, ctx.solve_cells(cells, [6] * 3, [Q] * 3, 5)):
             print(names, name, band_error(om, ref[name]), flush=True)
             assert band_error(om, ref[name]) <= 1e-10
+
+
+def _launches(ctx, call):
+    ctx.profile(True)
+    out = call()
+    n = {k: n for k, (_, n) in ctx.profile_read().items()}
+    ctx.profile(False)
+    return out, n
+
+
+@pytest.mark.parametrize("cap", [0, 256 << 20])   # 256 MB: the plans and two points at a time
+def test_points_handed_on_are_solved_together(ctx, cap):
+    """Points of three cells that need the reduction: one longer attempt and one
+    reduction for all of them (for the chunks of them that a cap allows), from the
+    coefficients at hand; the launches of the captured graph are not counted."""
+    from paper_1310_6380_amd import mvpb
+    own = mvpb.Context(0, workspace_cap=cap)
+    try:
+        scales = (1.0, 2.0, 0.5)
+        cells = [_even(own, s) for s in scales]
+        (rc, out), n = _launches(own, lambda: _solve_cells(own, cells, [M] * 3, [QS] * 3, NB))
+        print("cap", cap, "status", rc, {k: v for k, v in n.items() if v}, flush=True)
+        assert rc == mvpb.OK
+        for s, om in zip(scales, out):
+            assert band_error(om, _folded(QS, s)) <= TOL64
+        assert n["potrf_trtri"] == 0 and n["zgemm"] == 0 and n["hb2st"] > 0
+        if not cap:
+            assert n["krylov_factor"] == 1 and n["form_operator"] == 2
+        buf = mvpb.DeviceBuffer(out[0].nbytes * 3)
+        args = [(ctypes.c_void_p * 3)(*[c.h for c in cells]), (ctypes.c_int * 3)(*[M] * 3), (ctypes.c_int * 3)(*[3] * 3),
+                (ctypes.POINTER(ctypes.c_double) * 3)(*[QS.ctypes.data_as(ctypes.POINTER(ctypes.c_double))] * 3),
+                (ctypes.c_void_p * 3)(*[buf.value + i * out[0].nbytes for i in range(3)])]
+        assert mvpb.load().mvpb_solve_cells(own.h, 3, args[0], args[1], args[1], 0, args[2], args[3], NB, args[4],
+                                            mvpb.F_DEVICE_PTRS) == mvpb.OK
+        assert np.array_equal(buf.to_numpy(np.float64, (3,) + out[0].shape), np.stack(out))
+    finally:
+        own.close()
+
+
+def test_no_reduction_at_large_contrast(ctx):
+    """Cells of stiffness ratios 1e-5 .. 1e5 in one call: no point is handed on to the
+    reduction (8 bands take the steps that just reach the bar: one longer attempt)."""
+    x, y = np.meshgrid((np.arange(24) + 0.5) / 24 - 0.5, (np.arange(24) + 0.5) / 24 - 0.5, indexing="ij")
+    phase = (x * x + y * y < 0.09).astype(np.int32)
+    ratios = [1e-5, 1e-4, 1e-3, 1e3, 1e4, 1e5]
+    props = [np.array([[1e9, 0.35, 1200.0], [1e9 * r, 0.33, 2400.0]]) for r in ratios]
+    Ms = [8, 6, 7, 8, 6, 7]
+    Q = np.array([[0.0, 0.0], [0.02, 0.01], [0.31, 0.12], [0.5, 0.5]])
+    cells = [ctx.cell(phase, p) for p in props]
+    (rc, out), n = _launches(ctx, lambda: _solve_cells(ctx, cells, Ms, [Q] * 6, 8))
+    print({k: v for k, v in n.items() if v}, flush=True)
+    assert rc == 0 and n["krylov_factor"] <= 1 and n["he2hb_panel"] == 0, n
+    for c, m, om in zip(cells, Ms, out):
+        plan = c.plan(m)
+        assert band_error(om, plan.solve(Q, 8)) <= 1e-10
+        plan.close()
