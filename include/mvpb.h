@@ -352,24 +352,30 @@ int mvpb_kpath(const double lattice[4], const char *path, int n_k, double *Q);
  * of the operator order, n rounded up to a multiple of 128): the number of
  * independent stage-1 parts (streams), the number of consecutive
  * bulge-chasing sweeps dealt to one workgroup's wavefronts and the most
- * workgroups per item of the bulge chasing.  mvpb_autotune times the solve
- * of the plan's n_k points (Q as for mvpb_solve) under candidate shapes
- * (coordinate search from the defaults, median of three replays of the
- * captured launch sequence each, HIP events on the context stream; a
- * candidate replaces the best so far only if it is 2 % faster), keeps
- * the fastest for this context and, if cache_path is not NULL, merges it
- * into that JSON file (one entry per device name and size class).
- * *best_ms (nullable) receives its time.  The shapes change the schedule,
- * not the arithmetic: results are bitwise those of the defaults.
+ * workgroups per item of the bulge chasing.  The reduction and the
+ * shift-invert Krylov route (see mvpb_solve), which has no stage 1 and
+ * chases a smaller band matrix, have shapes of their own.  mvpb_autotune
+ * times the solve of the plan's n_k points (Q as for mvpb_solve) under
+ * candidate shapes (coordinate search from the defaults, median of three
+ * replays of the captured launch sequence each, HIP events on the context
+ * stream; a candidate replaces the best so far only if it is 2 % faster) by
+ * the reduction and, where mvpb_solve takes the plan's points by it, by the
+ * Krylov route, keeps the fastest of each for this context and, if
+ * cache_path is not NULL, merges them into that JSON file (one entry per
+ * device name and size class; a plan that the Krylov route does not take
+ * leaves its shape in the entry).  *best_ms (nullable) receives the time of
+ * the route that mvpb_solve takes.  The shapes change the schedule, not the
+ * arithmetic: results are bitwise those of the defaults.
  * mvpb_ctx_load_tuning applies the file's entries for this context's device
  * (*n_loaded, nullable: how many); MVPB_E_INVALID for a missing file or a
  * malformed entry. */
 int mvpb_autotune(mvpb_plan plan, int n_k, const double *Q, int n_bands, const char *cache_path,
                   double *best_ms);
 int mvpb_ctx_load_tuning(mvpb_ctx ctx, const char *path, int *n_loaded);
-/* The launch shape of the size class of operator order n, set explicitly
- * (parts 1..4, group 0 (= 8), 1, 2, 4 or 8, wg_max 0 (= 4) .. 4) or read
- * back (defaults 1, 0, 0 when the class has none). */
+/* The launch shape of the size class of operator order n, set explicitly for
+ * both routes (parts 1..4, group 0 (= 8), 1, 2, 4 or 8, wg_max 0 (= 4) .. 4;
+ * the Krylov route has no parts) or read back for the reduction (defaults 1,
+ * 0, 0 when the class has none). */
 int mvpb_ctx_set_launch_shape(mvpb_ctx ctx, int n, int parts, int group, int wg_max);
 int mvpb_ctx_get_launch_shape(mvpb_ctx ctx, int n, int *parts, int *group, int *wg_max);
 

@@ -145,8 +145,11 @@ struct TuneParams {
   int group = 0;    // bulge chasing: sweeps per workgroup group (0: 8)
   int wg_max = 0;   // bulge chasing: most workgroups per item (0: 4)
 };
-// Size class of an operator of order n (the key of the tuning table).
+// Size class of an operator of order n: the key of the tuning table, with
+// KRYLOV_SHAPES added for the Krylov route, whose launch sequence has no stage-1 parts
+// and chases a projection's bulges.
 static int size_class(int n) { return (n + 127) / 128; }
+constexpr int KRYLOV_SHAPES = 1 << 16;
 
 struct mvpb_ctx_s {
   int device = 0;
@@ -187,7 +190,7 @@ struct mvpb_ctx_s {
   std::map<std::string, GraphEntry> cell_graphs;
   std::vector<char> cell_stage;
   std::vector<hipEvent_t> cell_events;            // stage-1 fork/join events, MAX_SIDE + 1 per chunk
-  std::map<int, TuneParams> tune;                 // launch shapes by size class
+  std::map<int, TuneParams> tune;                 // launch shapes by size class and route
   long long spin_limit = 0;                       // bounded-wait polls of the bulge chasing (0: default)
   Profiler prof;
   int children = 0;     // live cells and plans
@@ -1524,6 +1527,12 @@ static int route_class(int n, int nb, int dim, int extra, bool fp32, bool modes,
   return !fp32 && n <= SMALL_MAX_N ? -1 : krylov_route(n, nb, dim, extra, fp32, modes, at).steps;
 }
 
+// Launch shape of a launch sequence whose largest operator is of order n.
+static TuneParams launch_shape(mvpb_ctx ctx, int n, const Route &rt) {
+  const auto f = ctx->tune.find(size_class(n) + (rt.steps ? KRYLOV_SHAPES : 0));
+  return f != ctx->tune.end() ? f->second : TuneParams{};
+}
+
 // Sizes of the per-item buffers of the Krylov route (the projection's own item
 // follows them, see krylov_item_bytes).
 static void krylov_layout(int n, int nb, int steps, size_t *sz, int *count) {
@@ -1930,11 +1939,7 @@ static int run_items(mvpb_ctx ctx, const std::vector<Job> &jobs, int nb, double 
   }
   const size_t ctl_off = total;   // bulge-chasing launch control words after the items
   // launch shape of this size class
-  TuneParams tp;
-  {
-    auto f = ctx->tune.find(size_class(n_max));
-    if (f != ctx->tune.end()) tp = f->second;
-  }
+  const TuneParams tp = launch_shape(ctx, n_max, rt);
   const int parts_wanted = std::max(1, std::min(tp.parts, MAX_SIDE + 1));
   Stage2Shape sh;
   sh.group = tp.group;
@@ -2583,10 +2588,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
       }
       bytes += ctl_bytes(j1 - j0);
       if (bytes > room) return set_err(MVPB_E_NOMEM, "one item needs %zu bytes, the budget is %zu", bytes, room);
-      CellChunk ch{j0, j1, take_tab(table_bytes(j1 - j0, rt)), TuneParams{}, rt};
-      auto f = ctx->tune.find(size_class(n0));
-      if (f != ctx->tune.end()) ch.tp = f->second;
-      chunks.push_back(ch);
+      chunks.push_back(CellChunk{j0, j1, take_tab(table_bytes(j1 - j0, rt)), launch_shape(ctx, n0, rt), rt});
       item_region = std::max(item_region, std::max(bytes, last));
       j0 = j1;
     }
@@ -2925,15 +2927,12 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
         if (j1 > j0 && bytes + b + ctl_bytes(j1 - j0 + 1) > item_region) break;
         bytes += b;
       }
-      TuneParams tp;
-      auto f = ctx->tune.find(size_class(n0));
-      if (f != ctx->tune.end()) tp = f->second;
       table.assign(table_bytes(j1 - j0, rt), 0);
       fill_table(table.data(), again.data() + j0, j1 - j0, rt);
       // in the place of the chunks' tables, which hold an entry at least as large for each of these points
       HIP_TRY(hipMemcpyAsync(W + chunks[0].t_items, table.data(), table.size(), hipMemcpyHostToDevice, st));
-      HIP_TRY(enqueue_items(chunks[0].t_items, again.data() + j0, (int)(j1 - j0), rt, tp, ctx->cell_events.data(),
-                            ctx->la_events.data()));
+      HIP_TRY(enqueue_items(chunks[0].t_items, again.data() + j0, (int)(j1 - j0), rt, launch_shape(ctx, n0, rt),
+                            ctx->cell_events.data(), ctx->la_events.data()));
       HIP_TRY(hipStreamSynchronize(st));   // the next table takes this one's place
     }
     HIP_TRY(read_back());
@@ -3042,6 +3041,13 @@ extern "C" int mvpb_ctx_load_tuning(mvpb_ctx ctx, const char *path, int *n_loade
     tp.wg_max = (int)wg;
     ctx->tune[(int)cls] = tp;
     ++n;
+    const double kg = json_number(line, "krylov_group"), kw = json_number(line, "krylov_wg");
+    if (!(kg >= 0)) continue;   // of a plan that the Krylov route does not take
+    if (!(kg <= 8) || !(kw >= 0 && kw <= 4)) return set_err(MVPB_E_INVALID, "%s: malformed tuning entry", path);
+    tp.parts = 1;
+    tp.group = (int)kg;
+    tp.wg_max = (int)kw;
+    ctx->tune[(int)cls + KRYLOV_SHAPES] = tp;
   }
   if (n_loaded) *n_loaded = n;
   return MVPB_OK;
@@ -3059,7 +3065,7 @@ extern "C" int mvpb_ctx_set_launch_shape(mvpb_ctx ctx, int n, int parts, int gro
   tp.parts = parts;
   tp.group = group;
   tp.wg_max = wg_max;
-  ctx->tune[size_class(n)] = tp;
+  ctx->tune[size_class(n)] = ctx->tune[size_class(n) + KRYLOV_SHAPES] = tp;
   return MVPB_OK;
 }
 
@@ -3067,9 +3073,7 @@ extern "C" int mvpb_ctx_get_launch_shape(mvpb_ctx ctx, int n, int *parts, int *g
   int rc = check_ctx(ctx);
   if (rc) return rc;
   if (n < 1 || n > MAX_N) return set_err(MVPB_E_INVALID, "n out of range");
-  TuneParams tp;
-  auto f = ctx->tune.find(size_class(n));
-  if (f != ctx->tune.end()) tp = f->second;
+  const TuneParams tp = launch_shape(ctx, n, Route{});
   if (parts) *parts = tp.parts;
   if (group) *group = tp.group;
   if (wg_max) *wg_max = tp.wg_max;
@@ -3100,7 +3104,7 @@ extern "C" int mvpb_autotune(mvpb_plan p, int n_k, const double *Q, int n_bands,
   const bool fp32 = (p->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
   Route rt = krylov_route(p->n, n_bands, p->dim, p->medium.extra, fp32, false, TRY_KRYLOV);
   if (ctx->cap && solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt)) > ctx->cap) rt = Route{};
-  const size_t need = solve_bytes(n_k, route_item_bytes(p->n, n_bands, fp32, rt));
+  const size_t need = solve_bytes(n_k, item_bytes(p->n, n_bands, fp32));
   if (ctx->cap && need > ctx->cap)
     return set_err(MVPB_E_NOMEM, "the %d points need %zu bytes of workspace, cap is %zu", n_k, need, ctx->cap);
   std::vector<Job> jobs(n_k);
@@ -3119,75 +3123,78 @@ extern "C" int mvpb_autotune(mvpb_plan p, int n_k, const double *Q, int n_bands,
   const auto saved = ctx->tune;
   // median of three timed runs of the captured launch sequence (the first
   // run of a shape captures it)
-  auto trial = [&](const TuneParams &tp, double *ms) -> int {
-    ctx->tune[cls] = tp;
-    int rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, rt);
+  auto trial = [&](const Route &r, const TuneParams &tp, double *ms) -> int {
+    ctx->tune[cls + (r.steps ? KRYLOV_SHAPES : 0)] = tp;
+    int rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, r);
     if (rc) return rc;
     double t[3];
-    for (int r = 0; r < 3; ++r) {
+    for (int i = 0; i < 3; ++i) {
       HIP_TRY(hipEventRecord(e0, st));
-      rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, rt);
+      rc = run_items(ctx, jobs, n_bands, om.as<double>(), nullptr, true, r);
       if (rc) return rc;
       HIP_TRY(hipEventRecord(e1, st));
       HIP_TRY(hipEventSynchronize(e1));
       float f = 0.f;
       HIP_TRY(hipEventElapsedTime(&f, e0, e1));
-      t[r] = f;
+      t[i] = f;
     }
     std::sort(t, t + 3);
     *ms = t[1];
     return MVPB_OK;
   };
-  // coordinate search from the defaults: stage-1 parts, then the sweep
-  // grouping, then the workgroups per item of the bulge chasing
-  TuneParams best;
-  double best_t = 0.0;
-  int rc = trial(best, &best_t);
-  const int parts_c[] = {2, 3, 4}, group_c[] = {1, 2, 4}, wg_c[] = {1, 2};
-  const double keep = 0.98;   // a candidate must beat the best so far by 2 % (stable choices under noise)
-  for (int v : parts_c) {
-    if (rc) break;
-    TuneParams tp = best;
-    tp.parts = v;
-    double t = 0.0;
-    rc = trial(tp, &t);
-    if (!rc && t < keep * best_t) best = tp, best_t = t;
-  }
-  for (int v : group_c) {
-    if (rc) break;
-    TuneParams tp = best;
-    tp.group = v;
-    double t = 0.0;
-    rc = trial(tp, &t);
-    if (!rc && t < keep * best_t) best = tp, best_t = t;
-  }
-  for (int v : wg_c) {
-    if (rc) break;
-    TuneParams tp = best;
-    tp.wg_max = v;
-    double t = 0.0;
-    rc = trial(tp, &t);
-    if (!rc && t < keep * best_t) best = tp, best_t = t;
-  }
+  // coordinate search from the defaults: stage-1 parts (of a reduction), then the
+  // sweep grouping, then the workgroups per item of the bulge chasing
+  auto search = [&](const Route &r, TuneParams &best, double &best_t) -> int {
+    int rc = trial(r, best, &best_t);
+    const double keep = 0.98;   // a candidate must beat the best so far by 2 % (stable choices under noise)
+    auto candidate = [&](int TuneParams::*field, int v) {
+      if (rc) return;
+      TuneParams tp = best;
+      tp.*field = v;
+      double t = 0.0;
+      rc = trial(r, tp, &t);
+      if (!rc && t < keep * best_t) best = tp, best_t = t;
+    };
+    for (int v = 2; v <= 4 && !r.steps; ++v) candidate(&TuneParams::parts, v);
+    for (int v : {1, 2, 4}) candidate(&TuneParams::group, v);
+    for (int v : {1, 2}) candidate(&TuneParams::wg_max, v);
+    if (!rc) ctx->tune[cls + (r.steps ? KRYLOV_SHAPES : 0)] = best;
+    return rc;
+  };
+  // the reduction (asynchronous calls and points handed on take it), then the route
+  // that a waiting call takes
+  TuneParams best, kbest;
+  double best_t = 0.0, ms = 0.0;
+  int rc = search(Route{}, best, best_t);
+  ms = best_t;
+  if (!rc && rt.steps) rc = search(rt, kbest, ms);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) {
     ctx->tune = saved;
     return rc;
   }
-  ctx->tune[cls] = best;
-  if (best_ms) *best_ms = best_t;
+  if (best_ms) *best_ms = ms;
   if (cache_path) {
-    // merge: every entry of the file except this device's entry for this class
+    // merge: every entry of the file except this device's entry for this class, of
+    // which the Krylov shapes stay if this plan does not take that route
     const std::string dev = device_key(ctx->device);
     std::vector<std::string> keep;
-    for (const std::string &line : read_entries(cache_path))
-      if (!(json_string(line, "device") == dev && (int)json_number(line, "n_class") == cls)) keep.push_back(line);
-    char mine[512];
+    double kg = rt.steps ? kbest.group : NAN, kw = kbest.wg_max;
+    for (const std::string &line : read_entries(cache_path)) {
+      if (!(json_string(line, "device") == dev && (int)json_number(line, "n_class") == cls)) {
+        keep.push_back(line);
+      } else if (!rt.steps) {
+        kg = json_number(line, "krylov_group");
+        kw = json_number(line, "krylov_wg");
+      }
+    }
+    char mine[512], krylov[64] = "";
+    if (kg >= 0) snprintf(krylov, sizeof krylov, "\"krylov_group\": %d, \"krylov_wg\": %d, ", (int)kg, (int)kw);
     snprintf(mine, sizeof mine,
              "{\"device\": \"%s\", \"n_class\": %d, \"n\": %d, \"n_bands\": %d, \"items\": %d, "
-             "\"parts\": %d, \"hb2st_group\": %d, \"hb2st_wg\": %d, \"ms\": %.4f}",
-             dev.c_str(), cls, p->n, n_bands, n_k, best.parts, best.group, best.wg_max, best_t);
+             "\"parts\": %d, \"hb2st_group\": %d, \"hb2st_wg\": %d, %s\"ms\": %.4f}",
+             dev.c_str(), cls, p->n, n_bands, n_k, best.parts, best.group, best.wg_max, krylov, ms);
     keep.push_back(mine);
     FILE *f = fopen(cache_path, "w");
     if (!f) return set_err(MVPB_E_INVALID, "cannot write %s", cache_path);

@@ -210,3 +210,44 @@ def test_krylov_modes_to_rounding(ctx, E, M, nb):
         bar = 4.0 * np.sqrt(len(C)) * np.finfo(np.float64).eps * np.linalg.eigvalsh(C)[-1]
         print("modes", E, M, nb, "residual over its bar", (res / bar).max(), flush=True)
         assert np.all(res <= bar)
+
+
+def test_krylov_shapes_are_its_own(tmp_path):
+    """The autotuner's entry holds a shape for the reduction and one for the Krylov
+    route; a plan that takes only the reduction leaves the other in the file, and a
+    context that loads the file gives the same bands by both."""
+    import json
+
+    from paper_1310_6380_amd import mvpb
+    phase, props = _cell(21)
+    Q, nb, path = np.array([[0.31, 0.12], [0.5, 0.5], [0.2, 0.4]]), 6, str(tmp_path / "tuning.json")
+
+    def entry():
+        with open(path) as fh:
+            lines = [json.loads(l.strip().rstrip(",")) for l in fh if '"device"' in l]
+        assert len(lines) == 1
+        return lines[0]
+
+    def bands(load):
+        c = mvpb.Context(0)
+        try:
+            if load:
+                assert c.load_tuning(path) == 1
+            plan = c.cell(phase, props).plan(7)
+            if not load:
+                plan.autotune(Q, nb, path)
+            om = plan.solve(Q, nb)
+            buf = mvpb.DeviceBuffer(om.nbytes)
+            plan.solve_device(Q, nb, buf.value, mvpb.F_DEVICE_PTRS | mvpb.F_ASYNC)
+            mvpb.device_synchronize()
+            if not load:
+                first = entry()
+                assert first["krylov_group"] in (0, 1, 2, 4, 8) and first["parts"] in (1, 2, 3, 4)
+                c.cell(phase, props).plan(7, None, mvpb.PREC_SF_FP32 | mvpb.PREC_EIG_FP32_RR64).autotune(Q, nb, path)
+                assert (entry()["krylov_group"], entry()["krylov_wg"]) == (first["krylov_group"], first["krylov_wg"])
+            return om, buf.to_numpy(np.float64, om.shape)
+        finally:
+            c.close()
+
+    for a, b in zip(bands(False), bands(True)):
+        assert np.array_equal(a, b)
