@@ -251,3 +251,46 @@ def test_krylov_shapes_are_its_own(tmp_path):
 
     for a, b in zip(bands(False), bands(True)):
         assert np.array_equal(a, b)
+
+
+# the orders of the edge cases above, planar and spatial
+@pytest.mark.parametrize("M1,M2,nb,modes", [(4, 5, 1, False), (4, 5, 11, False), (2, 15, 3, True), (7, 8, 6, True), (3, 18, 20, False),
+                                            (6, 12, 33, False), (12, 12, 5, False)])
+def test_krylov_is_the_route_taken(ctx, M1, M2, nb, modes):
+    """The bands above come from the route under test: one attempt, no reduction."""
+    phase, props = _cell(M1 * 31 + M2)
+    Q = np.array([[0.0, 0.0], [0.31, 0.12], [0.5, 0.5]])
+    plan = ctx.cell(phase, props, OBLIQUE).plan(M1, M2)
+    _, n = _launches(ctx, lambda: plan.solve(Q, nb, vectors=modes))
+    assert n["krylov_factor"] == 1 and n["he2hb_panel"] == 0 and n["small_tridiag"] == 0, n
+
+
+@pytest.mark.parametrize("spatial", [False, True])
+def test_krylov_hands_points_on(ctx, spatial):
+    """Sixteen equal frequencies (shear waves (3, 1) and pressure waves (2, 1) of a cell
+    without lateral contraction) and the homogeneous cube's twenty-four, with modes: at
+    Gamma a longer attempt, then the reduction; the other points keep what they have."""
+    if spatial:
+        E, nu, rho, M, nb = 3.5e9, 0.35, 1180.0, 3, 40
+        plan = ctx.cell_voxels(np.zeros((6, 6, 6), np.int32), np.array([[E, nu, rho]])).plan(M)
+        Q = np.array([[0.13, 0.21, 0.34], [0.0, 0.0, 0.0], [0.4, 0.1, 0.2]])
+        g = np.arange(-M, M + 1)
+        waves = np.stack(np.meshgrid(g, g, g, indexing="ij"), axis=-1).reshape(-1, 3)
+    else:
+        E, nu, rho, M, nb = 70e9, 0.0, 2700.0, 9, 60
+        plan = ctx.cell(np.zeros((8, 8), np.int32), np.array([[E, nu, rho]])).plan(M)
+        Q = np.array([[0.13, 0.21], [0.0, 0.0], [0.4, 0.1]])
+        waves = mo.plane_wave_indices(M, M)
+    lam, mu = mo.lame(E, nu)
+    ct, cl = np.sqrt(mu / rho), np.sqrt((lam + 2 * mu) / rho)
+    out, n = _launches(ctx, lambda: plan.solve(Q, nb, vectors=spatial))
+    om = out[0] if spatial else out
+    assert n["krylov_factor"] == 2 and n["he2hb_panel"] > 0, n
+    ref = np.stack([_folded((ct, ct, cl) if spatial else (ct, cl), np.eye(Q.shape[1]), waves, q, nb) for q in Q])
+    assert band_error(om, ref) <= TOL64
+    alone = plan.solve(Q[[0, 2]], nb, vectors=spatial)
+    assert np.array_equal(alone[0] if spatial else alone, om[[0, 2]])
+    if spatial:
+        assert np.array_equal(alone[1], out[1][[0, 2]])
+        U = out[1][1].T
+        assert np.abs(rho * (U.conj().T @ U) - np.eye(nb)).max() <= 1e-10
