@@ -216,7 +216,18 @@ int mvpb_plan_destroy(mvpb_plan plan);
  * the FP64 tridiagonal eigenpairs and the back-transform.  Plans with
  * MVPB_PREC_EIG_FP32_RR64 take 1 <= n_bands <= min(n_u, 64).  Q, omega and
  * U are host pointers unless MVPB_F_DEVICE_PTRS is set (then omega and U
- * are device pointers; Q stays on the host).  If the device could not finish a point (the reduction to
+ * are device pointers; Q stays on the host).
+ * An FP64 call that waits for its results and wants a small part of the
+ * spectrum (up to 64 bands, and about n_u / 7 - 17) takes it by
+ * shift-invert block Krylov.  Every point's residuals are checked:
+ * frequencies are accepted where they are converged to rounding (residual
+ * 1e-7 before the last inverse iteration, whose square remains), modes at
+ * 2e-12 or where rounding moves a value as much in a dense solver.  A point
+ * that misses its bar (values of multiplicity 15 and more always do) is
+ * solved again with more steps and then by the reduction of the whole
+ * matrix.  Calls with MVPB_F_ASYNC cannot be checked and take the reduction
+ * for every point, at up to three times the time; results of the two differ
+ * by rounding.  If the device could not finish a point (the reduction to
  * tridiagonal form gave up waiting on a hand-over), its frequencies are NaN;
  * with host pointers the call then returns MVPB_E_DEVICE. */
 int mvpb_solve(mvpb_plan plan, int n_k, const double *Q, int n_bands, double *omega, double *U,
@@ -256,8 +267,9 @@ int mvpb_stress_modes(mvpb_plan plan, int n_k, const double *Q, int n_bands, con
 int mvpb_band_sensitivities(mvpb_plan plan, int n_k, const double *Q, int n_bands, const double *omega,
                             const double *U, double *G, unsigned flags);
 
-/* Many plans at once: all (plan, k) items in one batched launch sequence
- * (captured in a HIP graph and replayed).  n_k[p] points for plan p taken
+/* Many plans at once: all (plan, k) items in batched launch sequences
+ * (captured in HIP graphs and replayed), by the routes of mvpb_solve; points
+ * solved again are not captured.  n_k[p] points for plan p taken
  * from Q[p] (host pointers), results to omega[p][t*n_bands + b] (host
  * pointers, or device pointers with MVPB_F_DEVICE_PTRS; Q[p] holds d
  * components per point as for mvpb_solve).  Every plan must belong to ctx
@@ -274,11 +286,16 @@ int mvpb_solve_batch(mvpb_ctx ctx, int n_plans, const mvpb_plan *plans, const in
  * (at most 4 per context, least recently used dropped) and replayed by a
  * later call of the same shape: the same cell count, and per cell (in
  * cutoff order) the same cutoff, pixel grid and k count, with the same
- * n_bands, precision and launch shapes.  Per-call data (phase maps, phase
- * tables, lattices, Bloch vectors) reach the kernels through device tables
- * uploaded before each launch, so a replay needs no host work beyond one
- * copy.  The plans are not kept: their matrices live in a context-owned
- * workspace (grow-only, within the context's workspace cap).
+ * n_bands, precision and launch shapes, and materials that take the same
+ * routes (cells whose heavy parts are stiff take more Krylov steps).
+ * Per-call data (phase maps, phase tables, lattices, Bloch vectors) reach
+ * the kernels through device tables uploaded before each launch.  The
+ * frequencies are then read back; points that miss the bars of mvpb_solve
+ * are solved again, all of them together, from the same coefficient
+ * matrices by launches that are not captured.  The plans are not kept:
+ * their matrices live in a context-owned workspace (grow-only, within the
+ * context's workspace cap; a call that fits it only by the reduction takes
+ * that).
  *   cells[i]: isotropic pixel cells of ctx (MVPB_E_UNSUPPORTED for polygon,
  *             voxel and general-compliance cells);
  *   M1[i], M2[i]: cutoffs, 2 N <= the plan limit;
@@ -291,7 +308,7 @@ int mvpb_solve_batch(mvpb_ctx ctx, int n_plans, const mvpb_plan *plans, const in
  * Always returns after the results are written (MVPB_F_ASYNC is ignored).
  * Errors: MVPB_E_NOT_PD names the first cell (caller's index) whose
  * compliance or density matrix failed to factor (its results are not
- * meaningful, the other cells' are); MVPB_E_NOMEM if the workspace would
+ * meaningful, the other cells' are: they are written before the error); MVPB_E_NOMEM if the workspace would
  * exceed the cap; MVPB_E_ACCURACY and MVPB_E_DEVICE as for mvpb_solve. */
 int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cells, const int *M1, const int *M2,
                      int precision, const int *n_k, const double *const *Q, int n_bands,
