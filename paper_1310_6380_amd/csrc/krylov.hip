@@ -13,13 +13,14 @@
 //
 // Why: the reduction reads and writes the trailing matrix twice per 16 columns
 // (n / 16 passes over HBM) and chases n bulges; the factorisation touches each
-// entry of the matrix in tiles of 64 x 64 on the matrix cores, (8/3) n^3 real
-// multiply-adds with the inverse instead of (16/3) n^3 bandwidth-bound ones,
-// and the chain of sequential sweeps is m long instead of n.  Convergence per
-// step is that of a gap of 16 eigenvalues: the residual of the last wanted
-// pair falls by 10 to 20 per step on the phononic spectra (eigenvalue counts
-// grow like a power of the frequency), and every item checks it: an item that
-// misses the bar is solved again, with more steps or by the reduction.
+// entry of the matrix in tiles of 64 x 64 on the matrix cores, (4/3) (n^3 + p
+// r^3) real operations with the inverse within p parts of r rows instead of
+// (16/3) n^3 bandwidth-bound ones, and the chain of sequential sweeps is m long
+// instead of n. Convergence per step is that of a gap of 16 eigenvalues: the
+// residual of the last wanted pair falls by 10 to 30 per step on the phononic
+// spectra (eigenvalue counts grow like a power of the frequency), and every item
+// checks it: an item that misses the bar is solved again, with more steps or by
+// the reduction.
 // Measured, plan build included, against the reduction: 60 points of 2N = 882,
 // 18 bands, 20.3 -> 10.4 ms; 60 points of 2N = 1922, 24 bands, 123.6 -> 44.6 ms;
 // 960 points of 2N = 242 .. 1250, 10 bands, 228 -> 95.9 ms.
@@ -37,8 +38,7 @@ namespace mvpb {
 constexpr int KB = 64;        // block of the factorisation
 constexpr int KS = HB;        // vectors of a Krylov block
 constexpr int KPB = 9;        // most blocks of a part of the inverse factor
-constexpr int KT = 1;         // 16-row tiles of the factor per workgroup of a product
-constexpr int KR = 16 * KT;
+constexpr int KR = 16;        // rows of the factor per workgroup of a product
 constexpr int KCH = KRY_ROWS; // rows of a block per workgroup of the orthogonalisation
 // Shift as a fraction of the nb-th band of the homogeneous medium (see KryMedium;
 // the (d + 1)-th where fewer are wanted: the first d vanish at Gamma).  Small enough
@@ -284,10 +284,11 @@ MVPB_DEV void chol_tile(const KryItem &it, int jb, int i0, int c0, cd (&sm)[2][2
 // Parts of the inverse factor of an operator of order n (see kry_forward) and the
 // blocks of one.  By the order alone, so that a point's result does not depend on
 // the points solved with it.  A part saves most of its blocks' inverse and costs
-// four launches per Krylov step (about 7 us each).  60 points of n = 882, 18
-// bands, in 2 parts of 7 blocks (chosen) 10.7 ms, in 3 of 5 10.9, whole 11.35; of
-// n = 1922, 24 bands, in 4 of 8 (chosen) 45.7, in 6 of 6 46.3, whole 52.1; 30
-// points of a spatial n = 1029 in 2 of 9 (chosen) 19.2, in 3 of 6 20.1, whole 19.1.
+// four launches per Krylov step (about 7 us each).  At most KPB = 9 blocks (chosen), 6
+// and 17, plan build included: 60 points of n = 882, 18 bands, in 2 parts of 7 blocks
+// 10.5 ms, 3 of 5 10.6, whole 11.1; of n = 1922, 24 bands, in 4 of 8 44.8, 6 of 6 45.5,
+// 2 of 16 46.3; 30 points of a spatial n = 1029 in 2 of 9 13.5, 3 of 6 13.6, whole 13.4;
+// 960 points of n = 242 .. 1250 95.7, 94.9 and 106.9.
 MVPB_HD int kry_parts(int n) { return ((n + KB - 1) / KB + KPB - 1) / KPB; }
 MVPB_HD int kry_part_blocks(int n) { return ((n + KB - 1) / KB + kry_parts(n) - 1) / kry_parts(n); }
 
@@ -388,56 +389,43 @@ __global__ void __launch_bounds__(512, 4) kry_norm(const KryItem *__restrict__ i
 //   W_0 = X_00 Q_0;   Z_I = Q_I - L_I,<I W_<I (SUB),  W_I = X_II Z_I
 // and the backward one
 //   Z_p = X_pp^H W_p;   W_I -= L_>I,I^H Z_>I (SUB),   Z_I = X_II^H W_I.
-// 32 rows (or columns of the factor) by 16 per workgroup, the depth dealt to its
+// 16 rows (or columns of the factor) by 16 per workgroup, the depth dealt to its
 // four wavefronts 16 at a time, the operands of the next 16 in flight during the
 // products; computed transposed (D^T = V^T M^T), so that a lane's loads of the
 // factor run down its columns, 256 bytes (forward) or, with two consecutive rows
 // per lane, 128 bytes (backward) at a time.  Bound by reading the factor and the
 // parts of its inverse once.
 struct KrySum {
-  cd red[4][KT][4][64];
+  cd red[4][4][64];
 };
 // acc += the depth [klo, khi) dealt to this wavefront; load(kg, a, b) fetches the
-// 16 deep from kg: a[q] of V, b[t][q] of tile t of the factor.
+// 16 deep from kg: a[q] of V, b[q] of the factor.
 template <typename L>
-MVPB_DEV void kry_depth(int klo, int khi, const L &load, Acc3 (&acc)[KT]) {
+MVPB_DEV void kry_depth(int klo, int khi, const L &load, Acc3 &acc) {
   const int wv = threadIdx.x >> 6, last = klo + (khi - klo - 1) / 16 * 16;
-#pragma unroll
-  for (int t = 0; t < KT; ++t) acc[t].clear();
+  acc.clear();
   int kg = klo + 16 * wv;
   if (kg >= khi) return;
-  cd a0[4], a1[4], b0[KT][4], b1[KT][4];
+  cd a0[4], a1[4], b0[4], b1[4];
   load(kg, a0, b0);
   for (; kg < khi; kg += 128) {
     load(min(kg + 64, last), a1, b1);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int t = 0; t < KT; ++t) acc[t].step(a0[q], b0[t][q]);
+    for (int q = 0; q < 4; ++q) acc.step(a0[q], b0[q]);
     load(min(kg + 128, last), a0, b0);
     if (kg + 64 < khi) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int t = 0; t < KT; ++t) acc[t].step(a1[q], b1[t][q]);
+      for (int q = 0; q < 4; ++q) acc.step(a1[q], b1[q]);
     }
   }
 }
-// Sum over the wavefronts: wavefront w receives KT of the 4 KT registers:
-// register v = KT w' + h of tile w % KT, w' = w / KT.
-MVPB_DEV void kry_sum(KrySum &sm, const Acc3 (&acc)[KT], cd (&out)[KT]) {
+// Sum over the wavefronts: wavefront w receives register w.
+MVPB_DEV cd kry_sum(KrySum &sm, const Acc3 &acc) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int t = 0; t < KT; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sm.red[wv][t][v][lane] = acc[t].get(v);
+  for (int v = 0; v < 4; ++v) sm.red[wv][v][lane] = acc.get(v);
   __syncthreads();
-  const int t = wv % KT;
-#pragma unroll
-  for (int h = 0; h < KT; ++h) {
-    const int v = KT * (wv / KT) + h;
-    out[h] = (sm.red[0][t][v][lane] + sm.red[1][t][v][lane]) + (sm.red[2][t][v][lane] + sm.red[3][t][v][lane]);
-  }
+  return (sm.red[0][wv][lane] + sm.red[1][wv][lane]) + (sm.red[2][wv][lane] + sm.red[3][wv][lane]);
 }
 
 template <bool SUB>
@@ -456,31 +444,26 @@ __global__ void __launch_bounds__(256) kry_forward(const KryItem *__restrict__ i
   const cd *Q = it.Q + (size_t)j * it.npad * KS;
   const cd *__restrict__ M = SUB ? it.A : it.Xi;
   const cd *__restrict__ V = SUB ? it.W : (part == 0 ? Q : it.Z);
-  Acc3 acc[KT];
+  Acc3 acc;
+  const int r = r0 + li;
   kry_depth(SUB ? 0 : start, SUB ? start : min(r0 + KR, end),
-            [&](int kg, cd (&a)[4], cd (&b)[KT][4]) {
+            [&](int kg, cd (&a)[4], cd (&b)[4]) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const int k = kg + 4 * q + lk;
                 const size_t kc = (size_t)min(k, n - 1) * ld;   // V has zero rows beyond n
                 a[q] = gld(V, (size_t)k * KS + li);
-#pragma unroll
-                for (int t = 0; t < KT; ++t) b[t][q] = gld(M, kc + min(r0 + 16 * t + li, n - 1));
+                b[q] = gld(M, kc + min(r, n - 1));
               }
             },
             acc);
-  cd s[KT];
-  kry_sum(sm, acc, s);
-  const int r = r0 + 16 * (wv % KT) + li;
+  const cd s = kry_sum(sm, acc);
   if (r < n) {
-#pragma unroll
-    for (int h = 0; h < KT; ++h) {
-      const size_t e = (size_t)r * KS + lk + 4 * (KT * (wv / KT) + h);
-      if (SUB)
-        gst(it.Z, e, gld(Q, e) - s[h]);
-      else
-        gst(it.W, e, s[h]);
-    }
+    const size_t e = (size_t)r * KS + lk + 4 * wv;
+    if (SUB)
+      gst(it.Z, e, gld(Q, e) - s);
+    else
+      gst(it.W, e, s);
   }
 }
 
@@ -497,30 +480,25 @@ __global__ void __launch_bounds__(256) kry_backward(const KryItem *__restrict__ 
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
   const cd *__restrict__ M = SUB ? it.A : it.Xi;
   const cd *__restrict__ V = SUB ? it.Z : it.W;
-  Acc3 acc[KT];
+  Acc3 acc;
+  const int r = r0 + li;
   kry_depth(SUB ? end : r0, SUB ? n : end,
-            [&](int kg, cd (&a)[4], cd (&b)[KT][4]) {
+            [&](int kg, cd (&a)[4], cd (&b)[4]) {
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const int k = kg + 8 * (q >> 1) + 2 * lk + (q & 1), kc = min(k, n - 1);   // V: zero rows beyond n
                 a[q] = gld(V, (size_t)k * KS + li);
-#pragma unroll
-                for (int t = 0; t < KT; ++t) b[t][q] = conj(gld(M, (size_t)min(r0 + 16 * t + li, n - 1) * ld + kc));
+                b[q] = conj(gld(M, (size_t)min(r, n - 1) * ld + kc));
               }
             },
             acc);
-  cd s[KT];
-  kry_sum(sm, acc, s);
-  const int r = r0 + 16 * (wv % KT) + li;
+  const cd s = kry_sum(sm, acc);
   if (r < n) {
-#pragma unroll
-    for (int h = 0; h < KT; ++h) {
-      const size_t e = (size_t)r * KS + lk + 4 * (KT * (wv / KT) + h);
-      if (SUB)
-        gst(it.W, e, gld(it.W, e) - s[h]);
-      else
-        gst(it.Z, e, s[h]);
-    }
+    const size_t e = (size_t)r * KS + lk + 4 * wv;
+    if (SUB)
+      gst(it.W, e, gld(it.W, e) - s);
+    else
+      gst(it.Z, e, s);
   }
 }
 
@@ -715,12 +693,11 @@ __global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ item
 // Launches
 // ---------------------------------------------------------------------------
 
-// Krylov steps for nb wanted pairs: the residual of the last pair reaches
-// about 1e-8 of its value (the frequencies' error is about ten times its square)
-// or, with modes wanted, 1e-13.  Measured on planar cells of 2N = 242 .. 1922:
-// 1e-8 after 6, 8, 9 to 10, 11 and 13 steps for nb = 4, 7, 10, 18 and 24, 1e-13
-// after 9 and 15 for nb = 4 and 18; on a spatial one (3N = 1029, nb = 12), whose
-// spectrum is denser, 11 and 15.
+// Krylov steps for nb wanted pairs: the residual of the last pair reaches 1e-9 of its
+// value in the median and 1e-7 at the worst (nb = 5 and 8, at stiffness ratios beyond
+// 1e3) or, with modes wanted, 1e-13 and 3e-12.  Measured on planar cells of 2N = 162 ..
+// 1922, ratios 1e-5 .. 1e5, and on a spatial one (3N = 1029, nb = 12), whose spectrum is
+// denser and takes one more.
 int krylov_steps(int nb, int dim, bool modes) {
   return 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0) + (modes ? 2 + nb / 12 : 0);
 }

@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(SQ * ROWS) small_tridiag(const EigItem *__rest
   const int n = it.n;
   if (n > ROWS || (ROWS > 64 && n <= 64)) return;   // the other instance's item
   const int t = threadIdx.x, r = t % ROWS, q = t / ROWS, lane = t & 63;
-  cd *const sr = sm + r, *const sq = sm + q;   // entries of this row; of the columns 8 i + q
+  cd *const sr = sm + r, *const sq = sm + q;   // entries of this row; of the columns 4 i + q
   cd a[NE];
 #pragma unroll
   for (int i = 0; i < NE; ++i) {

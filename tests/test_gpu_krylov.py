@@ -1,6 +1,6 @@
 """The shift-invert block Krylov route of FP64 solves, at the sizes where its
 tiles end: orders just around multiples of the factorisation's block (64), of
-the products' rows (32) and of the orthogonalisation's chunk (128), one block
+the products' rows (16) and of the orthogonalisation's chunk (128), one block
 and many, few and many bands.  Frequencies against the oracle to the bar of
 every FP64 path (1e-9), degenerate spectra against the folded free dispersion,
 where more copies of one eigenvalue than the block holds (16) have to come from
