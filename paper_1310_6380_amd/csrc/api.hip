@@ -1491,10 +1491,9 @@ struct Route {
 };
 
 // Attempts at a set of points: the Krylov route, the points whose pairs miss its
-// bar with RETRY_STEPS more, and what is left by the reduction.  Without a caller
+// bar with KRY_RETRY_STEPS more, and what is left by the reduction.  Without a caller
 // that waits for the results only the last.
 enum Attempt { TRY_KRYLOV = 0, TRY_LONGER, TRY_REDUCTION };
-constexpr int RETRY_STEPS = 4;
 
 // The Krylov route pays while its projection, of order m = HB steps, is smaller
 // than the operator: its chain of m sweeps and 4 steps launches against n
@@ -1513,8 +1512,8 @@ static Route krylov_route(int n, int nb, int dim, int extra, bool fp32, bool mod
   Route rt;
   if (fp32 || nb > RR_MAX_BANDS || at == TRY_REDUCTION) return rt;
   int s = krylov_steps(nb, dim, modes) + extra;
-  if (s + RETRY_STEPS > KRY_MAX_STEPS || 20 * HB * s > 17 * n) return rt;
-  if (at == TRY_LONGER && 10 * HB * (s += RETRY_STEPS) > 9 * n) return rt;
+  if (s + KRY_RETRY_STEPS > KRY_MAX_STEPS || 20 * HB * s > 17 * n) return rt;
+  if (at == TRY_LONGER && 10 * HB * (s += KRY_RETRY_STEPS) > 9 * n) return rt;
   rt.steps = s;
   rt.tol = modes ? 2e-12 : 1e-7;
   return rt;

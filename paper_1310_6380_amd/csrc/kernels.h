@@ -88,6 +88,7 @@ struct EigItem {
 // npad (n rounded up to KRY_ROWS) rows each.
 constexpr int KRY_ROWS = 128;
 constexpr int KRY_MAX_STEPS = 32;
+constexpr int KRY_RETRY_STEPS = 4;   // more of them in the second attempt at a point
 // What the shift and the start of a solve are taken from: the homogeneous isotropic
 // medium of the cell's mean slowness, the mean over the phases of density times
 // compliance.  Its bands lie within a factor of 0.3 to 8 of the cell's at stiffness

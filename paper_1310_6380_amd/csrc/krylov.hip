@@ -695,11 +695,16 @@ __global__ void __launch_bounds__(64) kry_check(const KryItem *__restrict__ item
 
 // Krylov steps for nb wanted pairs: the residual of the last pair reaches 1e-9 of its
 // value in the median and 1e-7 at the worst (nb = 5 and 8, at stiffness ratios beyond
-// 1e3) or, with modes wanted, 1e-13 and 3e-12.  Measured on planar cells of 2N = 162 ..
-// 1922, ratios 1e-5 .. 1e5, and on a spatial one (3N = 1029, nb = 12), whose spectrum is
-// denser and takes one more.
+// 1e3) or, with modes wanted, 1e-13 and 3e-12; with few modes the rounding of the first
+// formula is felt, and spatial spectra, which are denser, take two steps more.  Measured on
+// planar cells of 2N = 162 .. 1922 and ratios 1e-5 .. 1e5 and on spatial ones of 3N = 375
+// and 1029; points of high symmetry, where 16 values past the last wanted one are
+// hardly larger, miss the bar.
 int krylov_steps(int nb, int dim, bool modes) {
-  return 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0) + (modes ? 2 + nb / 12 : 0);
+  const int s = 6 + (9 * nb + 24) / 25 + (dim == 3 ? 1 : 0);
+  if (!modes) return s;
+  const int m = s + 2 + nb / 12, more = nb < 12 ? (dim == 3 ? 2 : (9 * nb + 24) % 25 >= 12) : (dim == 3 ? 1 : 0);
+  return std::max(m, std::min(m + more, KRY_MAX_STEPS - KRY_RETRY_STEPS));
 }
 
 hipError_t launch_krylov(const KryItem *items, int n_items, int n_max, int s, hipStream_t st) {
