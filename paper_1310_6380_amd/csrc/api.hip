@@ -2396,9 +2396,11 @@ extern "C" int mvpb_solve_batch(mvpb_ctx ctx, int n_plans, const mvpb_plan *plan
   if (jobs.empty()) return MVPB_OK;
   HIP_TRY(hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
-  // largest items first so the longest work starts earliest; chunks of
-  // similar size share one launch sequence (captured once, replayed)
-  std::stable_sort(jobs.begin(), jobs.end(), [](const Job &a, const Job &b) { return a.plan->n > b.plan->n; });
+  // largest items first so the longest work starts earliest; chunks of similar size
+  // and one route share one launch sequence (captured once, replayed)
+  std::stable_sort(jobs.begin(), jobs.end(), [](const Job &a, const Job &b) {
+    return a.plan->n != b.plan->n ? a.plan->n > b.plan->n : a.plan->medium.extra < b.plan->medium.extra;
+  });
   const bool fp32 = (jobs[0].plan->prec & MVPB_PREC_EIG_FP32_RR64) != 0;
   const size_t budget = ctx->cap ? ctx->cap : (size_t)24 << 30;
   rc = acc_begin(ctx);
@@ -2549,7 +2551,10 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
   for (int s = 0; s < n_cells; ++s)
     for (int t = 0; t < n_k[ord[s]]; ++t) jobs.push_back(CJob{s, t});
   auto order_of = [&](const CJob &j) { return 2 * (2 * M1[ord[j.s]] + 1) * (2 * M2[ord[j.s]] + 1); };
-  std::stable_sort(jobs.begin(), jobs.end(), [&](const CJob &a, const CJob &b) { return order_of(a) > order_of(b); });
+  auto extra = [&](const CJob &j) { return cells[ord[j.s]]->medium.extra; };
+  std::stable_sort(jobs.begin(), jobs.end(), [&](const CJob &a, const CJob &b) {
+    return order_of(a) != order_of(b) ? order_of(a) > order_of(b) : extra(a) < extra(b);
+  });
   const size_t stat_bytes = align256(sizeof(int) * 3 * n_cells);
   const size_t om_bytes = align256(sizeof(double) * base[n_cells] * n_bands);
   const size_t fixed = coef_bytes + temp_bytes + stat_bytes + om_bytes;
@@ -2572,7 +2577,6 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
     for (size_t j0 = 0; j0 < jobs.size();) {
       const int n0 = order_of(jobs[j0]);
       size_t j1 = j0, bytes = 0;
-      auto extra = [&](const CJob &j) { return cells[ord[j.s]]->medium.extra; };
       auto cls = [&](const CJob &j) { return route_class(order_of(j), n_bands, 0, extra(j), fp32, false, at); };
       while (j1 < jobs.size() && 3 * order_of(jobs[j1]) >= 2 * n0 && cls(jobs[j1]) == cls(jobs[j0])) ++j1;
       Route rt = krylov_route(n0, n_bands, 0, extra(jobs[j0]), fp32, false, at);
@@ -2916,7 +2920,7 @@ extern "C" int mvpb_solve_cells(mvpb_ctx ctx, int n_cells, const mvpb_cell *cell
     for (size_t j0 = 0, j1 = 0; j0 < again.size(); j0 = j1) {
       const int n0 = order_of(again[j0]);
       auto route = [&](const CJob &j) {
-        Route rt = krylov_route(order_of(j), n_bands, 0, cells[ord[j.s]]->medium.extra, fp32, false, (Attempt)at);
+        Route rt = krylov_route(order_of(j), n_bands, 0, extra(j), fp32, false, (Attempt)at);
         return solve_bytes(1, route_item_bytes(order_of(j), n_bands, fp32, rt)) > item_region ? Route{} : rt;
       };
       const Route rt = route(again[j0]);
