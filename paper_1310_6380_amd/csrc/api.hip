@@ -694,9 +694,10 @@ extern "C" int mvpb_cell_create_polygons(mvpb_ctx ctx, const double lattice[4], 
   std::vector<double> w, gw;
   rc = phase_weight_table(n_phases, props, w);
   if (rc) return rc;
-  int nf = 0;
-  rc = general_weight_table(2, n_phases, prop_kind, props, gw, &nf);
-  if (rc) return rc;
+  for (int p = 0; p < n_phases; ++p) {   // the general layout's row: d11, d12, d13, d22, d23, d33, rho
+    const double d11 = 0.5 * (w[4 * p] + w[4 * p + 1]), d12 = 0.5 * (w[4 * p] - w[4 * p + 1]);
+    gw.insert(gw.end(), {d11, d12, 0.0, d11, 0.0, 2.0 * w[4 * p + 1], w[4 * p + 2]});
+  }
   HIP_TRY(hipSetDevice(ctx->device));
   mvpb_cell c = new mvpb_cell_s();
   c->ctx = ctx;

@@ -294,3 +294,20 @@ def test_krylov_hands_points_on(ctx, spatial):
         assert np.array_equal(alone[1], out[1][[0, 2]])
         U = out[1][1].T
         assert np.abs(rho * (U.conj().T @ U) - np.eye(nb)).max() <= 1e-10
+
+
+def test_krylov_polygon_cells(ctx):
+    """Polygon cells take the route (their medium comes from the polygons' areas), and
+    cells of phases next to incompressible are accepted as before."""
+    from synth import hex_steel_epoxy
+    c = hex_steel_epoxy(32)
+    Q = np.array([[0.31, 0.12], [0.5, 0.25]])
+    plan = ctx.cell_polygons(c.polygons, c.poly_phase, c.props, c.lattice).plan(6)
+    om, n = _launches(ctx, lambda: plan.solve(Q, 6))
+    assert n["krylov_factor"] == 1 and n["he2hb_panel"] == 0, n
+    I = mo.polygon_integral_tables(c.polygons, c.poly_phase, c.n_phases, c.lattice, 6, 6)
+    ref, _ = mo.bands(None, c.props, c.lattice, 6, 6, Q, 6, I_p=I)
+    assert band_error(om, ref) <= TOL64
+    props = np.array(c.props, dtype=np.float64)
+    props[:, 1] = 0.5 - 2e-13
+    assert np.all(np.isfinite(ctx.cell_polygons(c.polygons, c.poly_phase, props, c.lattice).plan(2).solve(Q, 4)))
